@@ -582,16 +582,47 @@ __device__ __forceinline__ void em_block_sum(T (&x)[NV], T* buf, int& parity, in
     parity ^= 1;
 }
 
-// sum of all slots of a density-term vector (unused and dead slots hold 0)
-template <typename V>
-__device__ __forceinline__ auto resum(const V& v) -> decltype(v[0] + v[0])
-{
-    constexpr int n = sizeof(V) / sizeof(v[0]);
-    auto s = v[0];
+// The density terms of a thread's P particles in registers, e(p, j) with p a
+// constant after unrolling and j a wave-uniform slot.  A slot that is not a
+// constant is reached by one register-indexed move when the vector it lies
+// in has more than eight 32-bit values; a vector of eight is read by a chain
+// of 7 and written by 8 conditional moves.  Eight-slot particles therefore
+// share a 16-wide vector in pairs (an unpaired one gets a ninth value).
+template <typename R, int KMAX, int P>
+struct DensityTerms {
+    static constexpr bool kPair = KMAX * (int)sizeof(R) <= 32;
+    typedef R Pair __attribute__((ext_vector_type(KMAX * (kPair ? 2 : 1))));
+    typedef R Single __attribute__((ext_vector_type(KMAX + (kPair ? 1 : 0))));
+    static constexpr int kPairs = kPair ? P / 2 : P;
+    Pair pair[kPairs > 0 ? kPairs : 1];
+    Single last;
+    __device__ __forceinline__ R get(int p, int j) const
+    {
+        if constexpr (kPair)
+            return (P % 2 != 0 && p == P - 1) ? last[j] : pair[p / 2][(p % 2) * KMAX + j];
+        else
+            return pair[p][j];
+    }
+    __device__ __forceinline__ void set(int p, int j, R x)
+    {
+        if constexpr (kPair) {
+            if (P % 2 != 0 && p == P - 1)
+                last[j] = x;
+            else
+                pair[p / 2][(p % 2) * KMAX + j] = x;
+        } else {
+            pair[p][j] = x;
+        }
+    }
+    // sum of particle p's slots (unused and dead slots hold 0)
+    __device__ __forceinline__ R sum(int p) const
+    {
+        R s = get(p, 0);
 #pragma unroll
-    for (int j = 1; j < n; ++j) s += v[j];
-    return s;
-}
+        for (int j = 1; j < KMAX; ++j) s += get(p, j);
+        return s;
+    }
+};
 
 template <int D>
 __device__ __forceinline__ double sqrt_det(const double* C)
@@ -683,10 +714,7 @@ void k_em(CompressArgs A_in)
 
         // ---------------- particles into registers --------------------------
         R x[P][D], a[P], ref[P];
-        // density terms: one KMAX-vector per particle, indexed with the
-        // uniform slot number (register-indexed moves, no code per slot)
-        typedef R VecK __attribute__((ext_vector_type(KMAX)));
-        [[maybe_unused]] VecK e[STORE_E ? P : 1];
+        [[maybe_unused]] DensityTerms<R, KMAX, STORE_E ? P : 1> e;
         R Sden[P];  // sum_j e_pj, tracked incrementally and re-summed every sweep
         {
             const double wscale = N / ci->W;
@@ -795,18 +823,18 @@ void k_em(CompressArgs A_in)
                     for (int j = 0; j < K; ++j) {
                         const CompState<R, D> cj = comp[j];
 #pragma unroll
-                        for (int p = 0; p < P; ++p) e[p][j] = log2_term<R, D>(cj, x[p]);
+                        for (int p = 0; p < P; ++p) e.set(p, j, log2_term<R, D>(cj, x[p]));
                     }
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        R mx = e[p][0];
+                        R mx = e.get(p, 0);
 #pragma unroll
                         for (int j = 1; j < KMAX; ++j)
-                            if (j < K) mx = fmax(mx, e[p][j]);
+                            if (j < K) mx = fmax(mx, e.get(p, j));
                         ref[p] = mx;
 #pragma unroll
-                        for (int j = 0; j < KMAX; ++j) e[p][j] = (j < K) ? fast_exp2(e[p][j] - mx) : R(0);
-                        Sden[p] = resum(e[p]);
+                        for (int j = 0; j < KMAX; ++j) e.set(p, j, (j < K) ? fast_exp2(e.get(p, j) - mx) : R(0));
+                        Sden[p] = e.sum(p);
                     }
                 } else {
 #pragma unroll
@@ -832,21 +860,21 @@ void k_em(CompressArgs A_in)
                 // log2 space about their own maximum, as a log-sum-exp would, so
                 // that no term underflows to zero.
                 const R rebase_below = R(9.094947017729282e-13);  // 2^-40
-                auto rebase_store = [&](VecK& ep, const R (&xp)[D], R& refp) -> R {
+                auto rebase_store = [&](int p, const R (&xp)[D], R& refp) -> R {
                     R mx = R(-INFINITY);
 #pragma unroll
                     for (int j = 0; j < KMAX; ++j) {
                         const bool live = j < Kslots && ((alive >> j) & 1u);
                         const R t = live ? log2_term<R, D>(comp[j], xp) : R(-INFINITY);
-                        ep[j] = t;
+                        e.set(p, j, t);
                         mx = fmax(mx, t);
                     }
                     if (!(mx > R(-INFINITY))) return R(0);
 #pragma unroll
                     for (int j = 0; j < KMAX; ++j)
-                        ep[j] = (j < Kslots && ((alive >> j) & 1u)) ? fast_exp2(ep[j] - mx) : R(0);
+                        e.set(p, j, (j < Kslots && ((alive >> j) & 1u)) ? fast_exp2(e.get(p, j) - mx) : R(0));
                     refp = mx;
-                    return resum(ep);
+                    return e.sum(p);
                 };
                 auto rebase_sum = [&](const R (&xp)[D], R& refp) -> R {
                     R mx = R(-INFINITY);
@@ -872,10 +900,10 @@ void k_em(CompressArgs A_in)
 #pragma unroll
                         for (int p = 0; p < P; ++p) {
                             if (big[p]) {
-                                Sden[p] = rebase_store(e[p], x[p], ref[p]);
+                                Sden[p] = rebase_store(p, x[p], ref[p]);
                             } else if (low[p]) {
-                                Sden[p] = resum(e[p]);
-                                if (!(Sden[p] > rebase_below)) Sden[p] = rebase_store(e[p], x[p], ref[p]);
+                                Sden[p] = e.sum(p);
+                                if (!(Sden[p] > rebase_below)) Sden[p] = rebase_store(p, x[p], ref[p]);
                             }
                         }
                     }
@@ -917,7 +945,7 @@ void k_em(CompressArgs A_in)
                         };
                         if constexpr (STORE_E) {
 #pragma unroll
-                            for (int p = 0; p < P; ++p) accumulate(p, e[p][k], Sden[p]);
+                            for (int p = 0; p < P; ++p) accumulate(p, e.get(p, k), Sden[p]);
                         } else {
                             const CompState<R, D> ck = comp[k];
 #pragma unroll
@@ -942,8 +970,8 @@ void k_em(CompressArgs A_in)
 #pragma unroll
                                 for (int p = 0; p < P; ++p) {
                                     const R s_old = Sden[p];
-                                    const R s_new = s_old - e[p][k];
-                                    e[p][k] = R(0);
+                                    const R s_new = s_old - e.get(p, k);
+                                    e.set(p, k, R(0));
                                     Sden[p] = s_new;
                                     low[p] = !(s_new > R(1e-3) * s_old);
                                     big[p] = false;
@@ -993,8 +1021,8 @@ void k_em(CompressArgs A_in)
                                 const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
                                 const R enew = fast_exp2(fmin(dt, R(64)));
                                 const R s_old = Sden[p];
-                                const R s_new = s_old - e[p][k] + enew;
-                                e[p][k] = enew;
+                                const R s_new = s_old - e.get(p, k) + enew;
+                                e.set(p, k, enew);
                                 Sden[p] = s_new;
                                 low[p] = !(s_new > R(1e-3) * s_old);
                                 big[p] = dt > R(64);
@@ -1027,7 +1055,7 @@ void k_em(CompressArgs A_in)
                     uint32_t low = 0;
                     if constexpr (STORE_E) {
 #pragma unroll
-                        for (int p = 0; p < P; ++p) dens[p] = resum(e[p]);
+                        for (int p = 0; p < P; ++p) dens[p] = e.sum(p);
                     } else if (s % kResumSweeps != 0 && !annihilated) {
                         // the running sums, kept through the sweep's updates
                         // (each re-summed exactly where it had cancelled)
@@ -1054,7 +1082,7 @@ void k_em(CompressArgs A_in)
                         for (int p = 0; p < P; ++p) {
                             if ((low >> p) & 1u) {
                                 if constexpr (STORE_E)
-                                    dens[p] = rebase_store(e[p], x[p], ref[p]);
+                                    dens[p] = rebase_store(p, x[p], ref[p]);
                                 else
                                     dens[p] = rebase_sum(x[p], ref[p]);
                             }
@@ -1114,10 +1142,10 @@ void k_em(CompressArgs A_in)
                                 for (int j = 0; j + 1 < KMAX; ++j)
                                     if (j >= k) {
 #pragma unroll
-                                        for (int p = 0; p < P; ++p) e[p][j] = e[p][j + 1];
+                                        for (int p = 0; p < P; ++p) e.set(p, j, e.get(p, j + 1));
                                     }
 #pragma unroll
-                                for (int p = 0; p < P; ++p) e[p][KMAX - 1] = R(0);
+                                for (int p = 0; p < P; ++p) e.set(p, KMAX - 1, R(0));
                             }
                             const uint32_t low = alive & ((1u << k) - 1u);
                             const uint32_t high = (alive >> (k + 1)) << k;
