@@ -15,6 +15,10 @@ int launch_compress_d1_float(int, int, int, int, const CompressArgs&, int, hipSt
 int launch_compress_d3_float(int, int, int, int, const CompressArgs&, int, hipStream_t);
 int launch_compress_d1_double(int, int, int, int, const CompressArgs&, int, hipStream_t);
 int launch_compress_d3_double(int, int, int, int, const CompressArgs&, int, hipStream_t);
+int launch_compress_span_d1_float(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d3_float(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d1_double(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d3_double(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
 int grid_compress_d1_float(int, int, int, int);
 int grid_compress_d3_float(int, int, int, int);
 int grid_compress_d1_double(int, int, int, int);
@@ -139,77 +143,14 @@ constexpr int kNumLaneOf(int b) { return b; }
 // persistent workgroups of the big-cell launch
 constexpr int kBigGrid = 64;
 
-// Buckets of cells above 2048 particles (kmax 16) hold few cells, and one
-// long fit among them can set the length of the whole EM phase: there the
-// per-update latency of a single cell matters more than the bucket's
-// throughput.  FP32 iterations run them with a lean build of more than 8
-// waves (four waves per SIMD, the cell's CU to itself; in 3V the cells of
-// 2049-4096 particles take the register-resident builds of the next rule
-// instead).  On the Weibel-like batch one
-// 2049-particle cell running 1000 sweeps made the warm phase 9.6-10.4 ms
-// with it against 13.9-14.8 ms with the 8-wave builds, while a batch without
-// such a fit cannot tell the builds apart, so the tuner keeps this choice.
-constexpr int kChainMinN = 2048;
-inline bool chain_bucket(int kt, bool fp64, int b)
-{
-    return !fp64 && kt == 16 && gm::bucket_cfg(kt, b).max_n > kChainMinN;
-}
-
-// The cells of 1025-1792 particles (FP32, kmax 16) run as four waves,
-// one per SIMD, with 5, 6 or 7 register-resident particles per thread
-// instead of five to seven waves of 4: every update then waits for a SIMD
-// with one of the cell's waves, not two.  On the Weibel-like batch the warm
-// EM phase took 8.1 ms with them against 10.0-10.2 ms.
-inline bool four_wave_bucket(int D, int kt, bool fp64, int b)
-{
-    const int n = gm::bucket_cfg(kt, b).max_n;
-    return (void)D, kt == 16 && !fp64 && n > 1024 && n <= 1792;
-}
-
-// In 3V the cells of 2049-2560 and 2561-4096 particles (FP32, kmax 16) run
-// as eight waves with 5 and 8 register-resident particles per thread (two
-// waves per SIMD, the CU to the cell as with the 16-wave lean build): each
-// update then evaluates one density per particle instead of recomputing the
-// old one beside the new one, and a cell near 2049 particles computes 5
-// particle slots per lane, not 8.  The 8-particle build spills a few
-// per-cell values, which it reloads inside the update.  On the Weibel-like
-// batch, where these cells hold the longest cold fits, with built-in plans:
-// judged-fallback refit 20.7-20.9 ms against 26.7-29.3 ms with the lean
-// build, headline step 30.6-31.0 ms against 35.5-38.9 ms; the warm phase
-// (8.8 ms against 8.3-8.4 ms) ends on a 2049-particle cell that runs 4005
-// component updates (the sweep cap) here and 957 with the lean build's
-// rounding.  The tuner may still pick a lean build there.
-inline bool resident8_bucket(int D, int kt, bool fp64, int b)
-{
-    const int n = gm::bucket_cfg(kt, b).max_n;
-    return D == 3 && kt == 16 && !fp64 && n > 2048 && n <= 4096;
-}
-
 EmPlan default_plan(int D, int kt, bool fp64)
 {
     EmPlan p;
     for (int b = 0; b < gm::kNumBuckets; ++b) {
-        const gm::Bucket& c = gm::bucket_cfg(kt, b);
-        p.per_thread[b] = (int8_t)c.per_thread;
-        p.mode[b] = (int8_t)(c.store_e ? gm::kModeStoreE : 0);
-        p.waves[b] = (int8_t)c.waves;
-        if (four_wave_bucket(D, kt, fp64, b)) {
-            p.per_thread[b] = (int8_t)(c.max_n / 256);
-            p.mode[b] = (int8_t)gm::kModeStoreE;
-            p.waves[b] = 4;
-        }
-        if (chain_bucket(kt, fp64, b)) {
-            // the lean builds recompute 4 or 8 particles per thread
-            const int P = c.max_n <= 64 * gm::em_max_waves(true) * 4 ? 4 : 8;
-            p.per_thread[b] = (int8_t)P;
-            p.mode[b] = (int8_t)gm::kModeLean;
-            p.waves[b] = (int8_t)((c.max_n + 64 * P - 1) / (64 * P));
-        }
-        if (resident8_bucket(D, kt, fp64, b)) {
-            p.per_thread[b] = (int8_t)(c.max_n / (64 * 8));
-            p.mode[b] = (int8_t)gm::kModeStoreE;
-            p.waves[b] = 8;
-        }
+        const gm::EmDefault d = D == 1 ? gm::em_default<1>(kt, fp64, b) : gm::em_default<3>(kt, fp64, b);
+        p.per_thread[b] = (int8_t)d.per_thread;
+        p.mode[b] = (int8_t)d.mode;
+        p.waves[b] = (int8_t)d.waves;
         p.lane[b] = (int8_t)(kNumLaneOf(b));
         p.order[b] = (int8_t)(gm::kNumBuckets - 1 - b);  // largest cells first
     }
@@ -251,9 +192,100 @@ int launch_em_bucket(int D, bool fp64, int kt, int b, const EmPlan& p, gm::Compr
                 : gm::launch_compress_d3_float(kt, P, mode, W, a, grid, st);
 }
 
-// the EM phase: fork onto the lanes, launch every bucket in plan order, join
+int launch_em_big(int D, bool fp64, int kt, gm::CompressArgs& a, int64_t n_cells, hipStream_t st)
+{
+    const int g = (int)std::min<int64_t>(kBigGrid, n_cells);
+    if (D == 1)
+        return fp64 ? gm::launch_compress_big_d1_double(kt, a, g, st) : gm::launch_compress_big_d1_float(kt, a, g, st);
+    return fp64 ? gm::launch_compress_big_d3_double(kt, a, g, st) : gm::launch_compress_big_d3_float(kt, a, g, st);
+}
+
+// The built-in plan's EM phase: at most five launches that walk several
+// buckets each (k_em_span), plus those of the buckets whose densities do not
+// stay in registers and of the larger cells.  A launch of 8, 6, 4 or 1 waves
+// per workgroup takes the buckets of cells that many waves or a little fewer
+// fit (the 4-wave launch every narrower one too), so no cell waits behind
+// another bucket's slowest fit whatever hardware queues the streams share:
+// with HIP's default of four, one launch per bucket ran up to four of them
+// one after another.  Released as in launch_em_phase.
+int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArgs& a, int64_t n_cells, hipStream_t st)
+{
+    Fork* fk = fork_for_device();
+    if (!fk) return -1;
+    auto span = [&](int waves, int hi, int lo, hipStream_t s) {
+        if (D == 1)
+            return fp64 ? gm::launch_compress_span_d1_double(kt, a, waves, hi, lo, n_cells, s)
+                        : gm::launch_compress_span_d1_float(kt, a, waves, hi, lo, n_cells, s);
+        return fp64 ? gm::launch_compress_span_d3_double(kt, a, waves, hi, lo, n_cells, s)
+                    : gm::launch_compress_span_d3_float(kt, a, waves, hi, lo, n_cells, s);
+    };
+    // buckets of each launch width: W in (less, waves]; the 4-wave launch
+    // down to the narrowest
+    constexpr int kWidths = 4;
+    constexpr int kWaves[kWidths] = {8, 6, 4, 1}, kAbove[kWidths] = {6, 4, 0, 0};
+    constexpr int kLane[kWidths] = {0, 3, 2, kLanes - 1};
+    int hi[kWidths], lo[kWidths];
+    bool lane_used[kLanes] = {};
+    unsigned heavy_mask = 0;
+    int rest[gm::kNumBuckets], nrest = 0;
+    for (int w = 0; w < kWidths; ++w) {
+        hi[w] = -1;
+        lo[w] = gm::kNumBuckets;
+        for (int b = 0; b < gm::kNumBuckets; ++b)
+            if (p.mode[b] == gm::kModeStoreE && p.waves[b] <= kWaves[w] && p.waves[b] > kAbove[w]) {
+                hi[w] = std::max(hi[w], b);
+                lo[w] = std::min(lo[w], b);
+                if (kWaves[w] > 4) heavy_mask |= 1u << b;
+            }
+        if (hi[w] >= 0) lane_used[kLane[w]] = true;
+    }
+    constexpr int kRestLane[3] = {1, 3, 4};
+    for (int b = gm::kNumBuckets - 1; b >= 0; --b)
+        if (p.mode[b] != gm::kModeStoreE) {
+            if (nrest >= 3) return -1;
+            lane_used[kRestLane[nrest]] = true;
+            rest[nrest++] = b;
+            heavy_mask |= 1u << b;
+        }
+    lane_used[kRestLane[0]] = true;  // the big cells' launch
+    lane_used[kLanes - 1] = false;   // the caller's stream: no fork, no join
+    if (hipEventRecord(fk->fork, st) != hipSuccess) return -1;
+    for (int i = 0; i < kLanes - 1; ++i)
+        if (lane_used[i] && hipStreamWaitEvent(fk->aux[i], fk->fork, 0) != hipSuccess) return -1;
+    for (int i = 0; i < nrest; ++i)
+        if (launch_em_bucket(D, fp64, kt, rest[i], p, a, n_cells, fk->aux[kRestLane[i]])) return -1;
+    for (int w = 0; w < 2; ++w)
+        if (hi[w] >= 0 && span(kWaves[w], hi[w], lo[w], fk->aux[kLane[w]])) return -1;
+    if (launch_em_big(D, fp64, kt, a, n_cells, fk->aux[kRestLane[0]])) return -1;
+    k_hold<<<1, 64, 0, st>>>(fk->hold_ticks, a.plan, heavy_mask);
+    if (hipGetLastError() != hipSuccess) return -1;
+    if (hi[2] >= 0) {
+        hipStream_t s4 = fk->aux[kLane[2]];
+        if (hipEventRecord(fk->fork2, st) != hipSuccess || hipStreamWaitEvent(s4, fk->fork2, 0) != hipSuccess ||
+            span(kWaves[2], hi[2], lo[2], s4))
+            return -1;
+    }
+    if (hi[3] >= 0 && span(kWaves[3], hi[3], lo[3], st)) return -1;
+    for (int i = 0; i < kLanes - 1; ++i) {
+        if (!lane_used[i]) continue;
+        if (hipEventRecord(fk->join[i], fk->aux[i]) != hipSuccess) return -1;
+        if (hipStreamWaitEvent(st, fk->join[i], 0) != hipSuccess) return -1;
+    }
+    return 0;
+}
+
+bool same_launches(const EmPlan& p, const EmPlan& q)
+{
+    return memcmp(p.per_thread, q.per_thread, sizeof(p.per_thread)) == 0 &&
+           memcmp(p.mode, q.mode, sizeof(p.mode)) == 0 && memcmp(p.waves, q.waves, sizeof(p.waves)) == 0 &&
+           memcmp(p.lane, q.lane, sizeof(p.lane)) == 0 && memcmp(p.order, q.order, sizeof(p.order)) == 0;
+}
+
+// the EM phase of plan p: the built-in plan in its own launches; any other
+// forked onto the lanes, one launch per bucket in plan order, and joined
 int launch_em_phase(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArgs& a, int64_t n_cells, hipStream_t st)
 {
+    if (same_launches(p, default_plan(D, kt, fp64))) return launch_em_builtin(D, fp64, kt, p, a, n_cells, st);
     Fork* fk = fork_for_device();
     if (!fk) return -1;
     hipStream_t lanes[kLanes];
@@ -294,15 +326,7 @@ int launch_em_phase(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArgs&
         if (!heavy[b] && launch_em_bucket(D, fp64, kt, b, p, a, n_cells, lanes[p.lane[b]])) return -1;
     }
     // cells larger than the buckets hold, on the caller's stream
-    {
-        const int g = (int)std::min<int64_t>(kBigGrid, n_cells);
-        int rc = 0;
-        if (D == 1)
-            rc = fp64 ? gm::launch_compress_big_d1_double(kt, a, g, st) : gm::launch_compress_big_d1_float(kt, a, g, st);
-        else
-            rc = fp64 ? gm::launch_compress_big_d3_double(kt, a, g, st) : gm::launch_compress_big_d3_float(kt, a, g, st);
-        if (rc) return -1;
-    }
+    if (launch_em_big(D, fp64, kt, a, n_cells, st)) return -1;
     for (int i = 0; i < kLanes - 1; ++i) {
         if (hipEventRecord(fk->join[i], fk->aux[i]) != hipSuccess) return -1;
         if (hipStreamWaitEvent(st, fk->join[i], 0) != hipSuccess) return -1;
@@ -644,8 +668,8 @@ int gm_autotune(const double* v, const double* alpha, const int64_t* cell_off, i
             if (!gm::em_variant_built(D, kt, fp64, var.per_thread, var.store_e)) continue;
             const int waves = (max_n + 64 * var.per_thread - 1) / (64 * var.per_thread);
             if (waves < 1 || waves > gm::em_max_waves(var.lean)) continue;
-            if (chain_bucket(kt, fp64, b) && !(var.lean && waves > gm::em_max_waves(false)) &&
-                !(resident8_bucket(D, kt, fp64, b) && var.store_e && waves == 8))
+            if (gm::chain_bucket(kt, fp64, b) && !(var.lean && waves > gm::em_max_waves(false)) &&
+                !(gm::resident8_bucket(D, kt, fp64, b) && var.store_e && waves == 8))
                 continue;
             cand[b][ncand[b]][0] = vi;
             cand[b][ncand[b]][1] = waves;

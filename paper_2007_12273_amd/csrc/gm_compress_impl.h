@@ -355,6 +355,21 @@ int launch_requeue_dr(const CompressArgs& a, hipStream_t st)
 // ===========================================================================
 // k_em
 // ===========================================================================
+// A wave-uniform value held in scalar registers: every thread of a cell's
+// workgroup computes the same cell data, weights and decisions, but what
+// comes out of LDS or a cross-lane sum is divergent to the compiler, which
+// then keeps it in a vector register per value and turns every branch on it
+// into exec-mask arithmetic.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uni(float x) { return __int_as_float(uni(__float_as_int(x))); }
+__device__ __forceinline__ int64_t uni(int64_t x)
+{
+    return (int64_t)(((uint64_t)(uint32_t)uni((int)(x >> 32)) << 32) | (uint32_t)uni((int)x));
+}
+// a condition that is the same in every active lane
+__device__ __forceinline__ bool uni(bool x) { return __builtin_amdgcn_ballot_w64(x) != 0; }
+__device__ __forceinline__ double uni(double x) { return __longlong_as_double(uni((int64_t)__double_as_longlong(x))); }
+
 template <typename R, int D>
 struct CompState {
     R mu[D];
@@ -393,32 +408,32 @@ __device__ __forceinline__ R m_sqrt(R x)
 template <typename R, int D>
 __device__ __forceinline__ bool density_params(const R (&S)[ntri(D)], R u, R sdc, R (&Aout)[ntri(D)], R& c2)
 {
+#pragma clang fp contract(off)  // roundings as written, in every inlined copy
     const R k = (R)kSqrtHalfLog2e;
+    // straight-line arithmetic and one test of the pivots at the end: a bad
+    // pivot turns what follows into values nobody reads
+    auto bad = [](R x) { return !(x > R(0)) || !isfinite(x); };
     if constexpr (D == 1) {
-        if (!(S[0] > R(0)) || !isfinite(S[0])) return false;
         const R l00 = m_sqrt(S[0]);
         const R i00 = m_rcp(l00);
         Aout[0] = k * i00;
         c2 = fast_log2(u * sdc * i00);
-        return true;
+        return !bad(S[0]);
     } else {
-        if (!(S[0] > R(0)) || !isfinite(S[0])) return false;
         const R l00 = m_sqrt(S[0]);
         const R i00 = m_rcp(l00);
         const R l10 = S[1] * i00, l20 = S[2] * i00;
-        const R t11 = S[3] - l10 * l10;
-        if (!(t11 > R(0)) || !isfinite(t11)) return false;
+        const R t11 = fma(-l10, l10, S[3]);
         const R l11 = m_sqrt(t11);
         const R i11 = m_rcp(l11);
-        const R l21 = (S[4] - l20 * l10) * i11;
-        const R t22 = S[5] - l20 * l20 - l21 * l21;
-        if (!(t22 > R(0)) || !isfinite(t22)) return false;
+        const R l21 = fma(-l20, l10, S[4]) * i11;
+        const R t22 = fma(-l21, l21, fma(-l20, l20, S[5]));
         const R l22 = m_sqrt(t22);
         const R i22 = m_rcp(l22);
         // inverse of the lower factor
         const R m10 = -l10 * i00 * i11;
         const R m21 = -l21 * i11 * i22;
-        const R m20 = -(l20 * i00 + l21 * m10) * i22;
+        const R m20 = -fma(l20, i00, l21 * m10) * i22;
         Aout[0] = k * i00;
         Aout[1] = k * m10;
         Aout[2] = k * m20;
@@ -426,7 +441,7 @@ __device__ __forceinline__ bool density_params(const R (&S)[ntri(D)], R u, R sdc
         Aout[4] = k * m21;
         Aout[5] = k * i22;
         c2 = fast_log2(u * (sdc * i00) * (i11 * i22));
-        return true;
+        return !(bad(S[0]) | bad(t11) | bad(t22));
     }
 }
 
@@ -437,6 +452,7 @@ __device__ __forceinline__ bool factor_comp(CompState<R, D>& cs, double trC, R s
 {
     if (density_params<R, D>(cs.S, cs.u, sdc, cs.A, cs.c2)) return false;
     double eps = 1e-12 * trC / D;
+#pragma unroll 1
     for (int it = 0; it < 40; ++it) {
 #pragma unroll
         for (int i = 0; i < D; ++i) cs.S[tri_idx<D>(i, i)] += (R)eps;
@@ -452,7 +468,7 @@ __device__ __forceinline__ R log2_term(const CompState<R, D>& cs, const R (&x)[D
     R d[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) d[i] = x[i] - cs.mu[i];
-    return cs.c2 - tri_quad<D, R>(cs.A, d);
+    return sub_tri_quad<D, R>(cs.c2, cs.A, d);
 }
 
 // recomputed-density buckets re-sum every particle's density terms exactly
@@ -528,22 +544,11 @@ __device__ __forceinline__ void em_block_sum(T (&x)[NV], T* buf, int& parity, in
 {
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
     T* bb = buf + parity * (MAXW * NVMAX);
-    if constexpr (std::is_same<T, float>::value) {
-        constexpr int NB = (NV + 3) / 4;
-        float b[NB];
+    constexpr bool kF32 = std::is_same<T, float>::value;
+    constexpr int NB = (NV + 3) / 4;
+    [[maybe_unused]] float b[NB];
+    if constexpr (kF32) {
         wave_sums_transposed<NV>(x, b);
-        if (nwaves == 1) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) x[v] = lane_bcast(b[v / 4], 16 * tv_row(v) + 15);
-            return;
-        }
-        if ((lane & 15) == 15) {
-            const int r = lane >> 4;
-            const int off = 2 * (r & 1) + (r >> 1);  // value index within each group of four
-#pragma unroll
-            for (int j = 0; j < NB; ++j)
-                if (4 * j + off < NV) bb[wid * NVMAX + 4 * j + off] = b[j];
-        }
     } else {
 #pragma unroll
         for (int v = 0; v < NV; ++v) x[v] += dpp_get<0xB1>(x[v]);   // quad_perm [1,0,3,2]
@@ -557,29 +562,42 @@ __device__ __forceinline__ void em_block_sum(T (&x)[NV], T* buf, int& parity, in
         for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x142>(x[v]);  // row_bcast:15
 #pragma unroll
         for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x143>(x[v]);  // row_bcast:31
-        if (nwaves == 1) {
+    }
+    if (nwaves == 1) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) x[v] = lane_bcast(x[v], 63);
-            return;
+        for (int v = 0; v < NV; ++v) {
+            if constexpr (kF32)
+                x[v] = lane_bcast(b[v / 4], 16 * tv_row(v) + 15);
+            else
+                x[v] = lane_bcast(x[v], 63);
         }
-        if (lane == 63) {
+    } else {
+        if constexpr (kF32) {
+            if ((lane & 15) == 15) {
+                const int r = lane >> 4;
+                const int off = 2 * (r & 1) + (r >> 1);  // value index within each group of four
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    if (4 * j + off < NV) bb[wid * NVMAX + 4 * j + off] = b[j];
+            }
+        } else if (lane == 63) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) bb[wid * NVMAX + v] = x[v];
         }
+        __syncthreads();
+        T t = T(0);
+        if (lane < NV) {
+            T part[MAXW];
+#pragma unroll
+            for (int w = 0; w < MAXW; ++w) part[w] = bb[w * NVMAX + lane];
+            t = part[0];
+#pragma unroll
+            for (int w = 1; w < MAXW; ++w) t += part[w];
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) x[v] = lane_bcast(t, v);
+        parity ^= 1;
     }
-    __syncthreads();
-    T t = T(0);
-    if (lane < NV) {
-        T part[MAXW];
-#pragma unroll
-        for (int w = 0; w < MAXW; ++w) part[w] = bb[w * NVMAX + lane];
-        t = part[0];
-#pragma unroll
-        for (int w = 1; w < MAXW; ++w) t += part[w];
-    }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) x[v] = lane_bcast(t, v);
-    parity ^= 1;
 }
 
 // The density terms of a thread's P particles in registers, e(p, j) with p a
@@ -655,347 +673,340 @@ constexpr int em_min_waves_per_simd()
     return (!LEAN && std::is_same<R, float>::value && STORE_E && P == 1) ? 3 : 1;
 }
 
-template <int D, int KMAX, int P, bool STORE_E, typename R, bool LEAN>
-__global__ __launch_bounds__(LEAN ? kEmLeanThreads : kEmMaxThreads, (em_min_waves_per_simd<R, LEAN, P, STORE_E>()))
-void k_em(CompressArgs A_in)
+// LDS of an EM workgroup of up to MAXW waves
+template <int D, int KMAX, typename R, int MAXW>
+struct EmShared {
+    static constexpr int NS = 1 + D + ntri(D);
+    CompressArgs A;                      // arguments read where they are used, not pinned in SGPRs
+    CompState<R, D> compw[MAXW][KMAX];
+    CompState<R, D> bestc[KMAX];         // best state of the outer search over K
+    double red_d[2 * kMaxWaves * 2];
+    R red_r[2 * MAXW * NS];              // zero where no wave writes (em_block_sum)
+    int s_idx;
+    int s_flag;
+};
+
+// Fit cell c with the workgroup's first nwaves waves (all that are left of
+// it), P particles per thread, and write the converged penalised mixture into
+// the output record.  Padding particles have weight zero and add nothing to
+// any sum, so a cell's result does not depend on P, only on nwaves (which
+// fixes the particles of each lane and the order of the sums).
+template <int D, int KMAX, int P, bool STORE_E, typename R, int MAXW>
+__device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int c, int nwaves, int& par_d,
+                                            int& par_r)
 {
-    constexpr int MAXW = em_max_waves(LEAN);
+    // roundings as written: every build and inlined copy of the fit takes the
+    // same decisions
+#pragma clang fp contract(off)
     constexpr int NT = ntri(D);
     constexpr int NS = 1 + D + NT;
-    const int nthreads = blockDim.x;
+    const int nthreads = 64 * nwaves;
     const int tid = threadIdx.x;
-    const int wid = tid >> 6, lane = tid & 63;
+    const int wid = uni(tid >> 6), lane = tid & 63;
     const double T = 0.5 * D * (D + 3);
     const double halfT = 0.5 * T;
-
-    __shared__ CompressArgs A;   // arguments read where they are used, not pinned in SGPRs
-    __shared__ CompState<R, D> compw[MAXW][KMAX];
-    __shared__ CompState<R, D> bestc[KMAX];  // best state of the outer search over K
-    __shared__ double red_d[2 * kMaxWaves * 2];
-    __shared__ R red_r[2 * MAXW * NS];  // zero where no wave writes (em_block_sum)
-    __shared__ int s_idx;
-    __shared__ int s_flag;
-
-    if (tid == 0) A = A_in;
-    for (int t = tid; t < 2 * MAXW * NS; t += blockDim.x) red_r[t] = R(0);
-    __syncthreads();
-    const int nwaves = A.nwaves;
-    const int bucket = A.bucket;
-    const int count = A.plan[PLAN_COUNT + bucket];
-    const int base = A.plan[PLAN_BASE + bucket];
-    int par_d = 0, par_r = 0;
+    const CompressArgs& A = sh.A;
+    CompState<R, D>(&compw)[MAXW][KMAX] = sh.compw;
+    CompState<R, D>(&bestc)[KMAX] = sh.bestc;
+    double* red_d = sh.red_d;
+    R* red_r = sh.red_r;
+    int& s_flag = sh.s_flag;
     CompState<R, D>* comp = compw[wid];
+    const CellInfo<D>* ci = static_cast<const CellInfo<D>*>(A.cells) + c;
+    const int n = uni(ci->n);
+    // sqrt det C: densities are kept relative to the cell's own scale
+    const double sdc64 = sqrt_det<D>(ci->C);
+    const R sdc = uni((R)sdc64);
+    const double lnc0 = uni(-0.5 * D * kLnTwoPi - log(sdc64));
+    const double lnN = uni(log((double)n));
+    R inv_den = R(0);  // 1 / (N - T K / 2) of eq. omegak, set whenever K changes
+    const int64_t o0 = uni((int64_t)A.off[c]);
+    const double* vc = A.v + o0 * D;
+    const int kmax = uni(A.kmax);
+    const double N = (double)n;
+    int32_t status = 0;
 
-    // The first cell is claimed before the loop: a workgroup that finds the
-    // queue empty leaves before the loop's invariants are set up (a build
-    // that fills the register file spills them to scratch, a write per lane
-    // of every workgroup of the persistent grid).
-    if (tid == 0) s_idx = atomicAdd(&A.plan[PLAN_QUEUE + bucket], 1);
-    __syncthreads();
-    int idx = s_idx;
-    __syncthreads();
-    if (idx >= count) return;
-    for (;;) {
-        const int c = A.list[base + idx];
-        const CellInfo<D>* ci = static_cast<const CellInfo<D>*>(A.cells) + c;
-        const int n = ci->n;
-        const double trC = ci->trC;
-        // sqrt det C: densities are kept relative to the cell's own scale
-        const double sdc64 = sqrt_det<D>(ci->C);
-        const R sdc = (R)sdc64;
-        const double lnc0 = -0.5 * D * kLnTwoPi - log(sdc64);
-        const double lnN = log((double)n);
-        R inv_den = R(0);  // 1 / (N - T K / 2) of eq. omegak, set whenever K changes
-        const int64_t o0 = A.off[c];
-        const double* vc = A.v + o0 * D;
-        const int kmax = A.kmax;
-        const double N = (double)n;
-        int32_t status = 0;
-
-        // ---------------- particles into registers --------------------------
-        R x[P][D], a[P], ref[P];
-        [[maybe_unused]] DensityTerms<R, KMAX, STORE_E ? P : 1> e;
-        R Sden[P];  // sum_j e_pj, tracked incrementally and re-summed every sweep
-        {
-            const double wscale = N / ci->W;
-            double m[D];
+    // ---------------- particles into registers --------------------------
+    R x[P][D], a[P], ref[P];
+    [[maybe_unused]] DensityTerms<R, KMAX, STORE_E ? P : 1> e;
+    R Sden[P];  // sum_j e_pj, tracked incrementally and re-summed every sweep
+    {
+        const double wscale = N / ci->W;
+        double m[D];
 #pragma unroll
-            for (int d = 0; d < D; ++d) m[d] = ci->m[d];
+        for (int d = 0; d < D; ++d) m[d] = ci->m[d];
 #pragma unroll
-            for (int j = 0; j < P; ++j) {
-                const int i = tid + j * nthreads;
-                if (i < n) {
+        for (int j = 0; j < P; ++j) {
+            const int i = tid + j * nthreads;
+            if (i < n) {
 #pragma unroll
-                    for (int d = 0; d < D; ++d) x[j][d] = (R)(vc[(size_t)i * D + d] - m[d]);
-                    a[j] = (R)(A.alpha[o0 + i] * wscale);
-                } else {
-#pragma unroll
-                    for (int d = 0; d < D; ++d) x[j][d] = R(0);
-                    a[j] = R(0);
-                }
-                ref[j] = R(0);
-            }
-        }
-
-        // A warm start is kept when its converged penalised likelihood is at
-        // least that of the single Gaussian with the cell's own moments,
-        // sum_p a_p ln N(x_p; 0, C) - (T/2) ln N = N (lnc0 - D/2) - (T/2) ln N
-        // (sum_p a_p x_p x_p^T = N C), less 1e-5 of its magnitude; otherwise
-        // the cell is fitted again from the cold start.  Replay mode (fixed sweep counts) never restarts.
-        const int fixed = A.fixed ? A.fixed[c] : 0;
-        const double L_one = N * (lnc0 - 0.5 * D) - halfT * log(N);
-        bool warm = A.init.K != nullptr && A.init.K[c] > 0;
-        // A supplied start is used only if eq. (omegak) is defined for it:
-        // N - T K / 2 > 0 and N w_k > T/2 for every supplied component
-        // (weights renormalised over the K used); otherwise the cell starts
-        // cold, flagged as a rejected warm start.
-        if (warm) {
-            const int Kw = min(A.init.K[c], kmax);
-            const size_t s0 = (size_t)c * kmax;
-            double wsum = 0.0;
-            for (int j = 0; j < Kw; ++j) wsum += A.init.omega[s0 + j];
-            bool usable = N - halfT * Kw > 0.0 && wsum > 0.0 && isfinite(wsum);
-            for (int j = 0; j < Kw; ++j) usable &= N * (A.init.omega[s0 + j] / wsum) > halfT;
-            if (!usable) {
-                warm = false;
-                status = GM_ST_WARM_FALLBACK;
-            }
-        }
-        long long visits = 0;
-        double L_s = 0.0;
-        int s = 0;
-        int K = 0;
-        R G = R(0);
-        for (;;) {
-            // ---------------- initial mixture ------------------------------------
-            if (tid == 0) s_flag = 0;
-            if (warm) {
-                K = min(A.init.K[c], kmax);
+                for (int d = 0; d < D; ++d) x[j][d] = (R)(vc[(size_t)i * D + d] - m[d]);
+                a[j] = (R)(A.alpha[o0 + i] * wscale);
             } else {
-                K = min(kmax, n);
-                const int cap = max(1, (int)floor(N / T));
-                if (K > cap) {
-                    K = cap;
-                    status |= GM_ST_K0_CAPPED;
-                }
+#pragma unroll
+                for (int d = 0; d < D; ++d) x[j][d] = R(0);
+                a[j] = R(0);
             }
-            __syncthreads();
-            if (tid < K) {
-                CompState<R, D> cs;
-                if (warm) {
-                    const size_t s0 = (size_t)c * kmax;
-                    double wsum = 0.0;
-                    for (int j = 0; j < K; ++j) wsum += A.init.omega[s0 + j];
-                    const size_t sk = s0 + tid;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) cs.mu[d] = (R)(A.init.mu[sk * D + d] - ci->m[d]);
-#pragma unroll
-                    for (int q = 0; q < NT; ++q) cs.S[q] = (R)A.init.sigma[sk * NT + q];
-                    cs.u = (R)(A.init.omega[sk] / wsum);
-                } else {
-                    const int ip = A.init_idx[(size_t)c * kInitSlots + tid];
-#pragma unroll
-                    for (int d = 0; d < D; ++d) cs.mu[d] = (R)(vc[(size_t)ip * D + d] - ci->m[d]);
-#pragma unroll
-                    for (int q = 0; q < NT; ++q) cs.S[q] = (R)ci->C[q];
-                    cs.u = (R)(1.0 / K);
-                }
-                if (factor_comp<R, D>(cs, trC, sdc)) s_flag = 1;
-                for (int w = 0; w < nwaves; ++w) compw[w][tid] = cs;
-            }
-            __syncthreads();
-            if (s_flag) status |= GM_ST_COV_FLOOR;
-            G = R(0);
-            for (int j = 0; j < K; ++j) G += comp[j].u;
+            ref[j] = R(0);
+        }
+    }
 
-            // Runs of the outer search over K (a single run unless A.outer):
-            // after every converged run the state is kept if its penalised L
-            // is the best so far, the least probable component is removed
-            // and the sweeps run again, down to K = 1.
-            const bool outer = A.outer != 0 && fixed <= 0;
-            double L_best = -INFINITY;
-            int K_best = 0, s_total = 0;
-            R G_best = R(0);
-            for (;;) {
-                inv_den = m_rcp((R)(N - halfT * K));
-                // ---------------- initial density terms ------------------------------
+    // A warm start is kept when its converged penalised likelihood is at
+    // least that of the single Gaussian with the cell's own moments,
+    // sum_p a_p ln N(x_p; 0, C) - (T/2) ln N = N (lnc0 - D/2) - (T/2) ln N
+    // (sum_p a_p x_p x_p^T = N C), less 1e-5 of its magnitude; otherwise
+    // the cell is fitted again from the cold start.  Replay mode (fixed sweep counts) never restarts.
+    const int fixed = uni(A.fixed ? A.fixed[c] : 0);
+    bool warm = uni(A.init.K != nullptr && A.init.K[c] > 0);
+    // A supplied start is used only if eq. (omegak) is defined for it:
+    // N - T K / 2 > 0 and N w_k > T/2 for every supplied component
+    // (weights renormalised over the K used); otherwise the cell starts
+    // cold, flagged as a rejected warm start.
+    if (warm) {
+        const int Kw = uni(min(A.init.K[c], kmax));
+        const size_t s0 = (size_t)c * kmax;
+        double wsum = 0.0;
+        for (int j = 0; j < Kw; ++j) wsum += A.init.omega[s0 + j];
+        bool usable = N - halfT * Kw > 0.0 && wsum > 0.0 && isfinite(wsum);
+        for (int j = 0; j < Kw; ++j) usable &= N * (A.init.omega[s0 + j] / wsum) > halfT;
+        if (!uni(usable)) {
+            warm = false;
+            status = GM_ST_WARM_FALLBACK;
+        }
+    }
+    long long visits = 0;
+    double L_s = 0.0;
+    int s = 0;
+    int K = 0;
+    R G = R(0);
+    for (;;) {
+        // ---------------- initial mixture ------------------------------------
+        if (tid == 0) s_flag = 0;
+        warm = uni(warm);
+        if (warm) {
+            K = uni(min(A.init.K[c], kmax));
+        } else {
+            K = min(kmax, n);
+            const int cap = max(1, (int)floor(N / T));
+            if (K > cap) {
+                K = cap;
+                status |= GM_ST_K0_CAPPED;
+            }
+        }
+        __syncthreads();
+        K = uni(K);
+        if (tid < K) {
+            CompState<R, D> cs;
+            if (warm) {
+                const size_t s0 = (size_t)c * kmax;
+                double wsum = 0.0;
+                for (int j = 0; j < K; ++j) wsum += A.init.omega[s0 + j];
+                const size_t sk = s0 + tid;
+#pragma unroll
+                for (int d = 0; d < D; ++d) cs.mu[d] = (R)(A.init.mu[sk * D + d] - ci->m[d]);
+#pragma unroll
+                for (int q = 0; q < NT; ++q) cs.S[q] = (R)A.init.sigma[sk * NT + q];
+                cs.u = (R)(A.init.omega[sk] / wsum);
+            } else {
+                const int ip = A.init_idx[(size_t)c * kInitSlots + tid];
+#pragma unroll
+                for (int d = 0; d < D; ++d) cs.mu[d] = (R)(vc[(size_t)ip * D + d] - ci->m[d]);
+#pragma unroll
+                for (int q = 0; q < NT; ++q) cs.S[q] = (R)ci->C[q];
+                cs.u = (R)(1.0 / K);
+            }
+            if (factor_comp<R, D>(cs, ci->trC, sdc)) s_flag = 1;
+            for (int w = 0; w < nwaves; ++w) compw[w][tid] = cs;
+        }
+        __syncthreads();
+        if (uni(s_flag)) status |= GM_ST_COV_FLOOR;
+        G = R(0);
+        for (int j = 0; j < K; ++j) G += comp[j].u;
+
+        // Runs of the outer search over K (a single run unless A.outer):
+        // after every converged run the state is kept if its penalised L
+        // is the best so far, the least probable component is removed
+        // and the sweeps run again, down to K = 1.
+        const bool outer = uni(A.outer) != 0 && fixed <= 0;
+        double L_best = -INFINITY;
+        int K_best = 0, s_total = 0;
+        R G_best = R(0);
+        for (;;) {
+            K = uni(K);
+            inv_den = m_rcp((R)(N - halfT * K));
+            // ---------------- initial density terms ------------------------------
+            if constexpr (STORE_E) {
+                for (int j = 0; j < K; ++j) {
+                    const CompState<R, D> cj = comp[j];
+#pragma unroll
+                    for (int p = 0; p < P; ++p) e.set(p, j, log2_term<R, D>(cj, x[p]));
+                }
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    R mx = e.get(p, 0);
+#pragma unroll
+                    for (int j = 1; j < KMAX; ++j)
+                        if (j < K) mx = fmax(mx, e.get(p, j));
+                    ref[p] = mx;
+#pragma unroll
+                    for (int j = 0; j < KMAX; ++j) e.set(p, j, (j < K) ? fast_exp2(e.get(p, j) - mx) : R(0));
+                    Sden[p] = e.sum(p);
+                }
+            } else {
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    R mx = R(-1e30);
+                    for (int j = 0; j < K; ++j) mx = fmax(mx, log2_term<R, D>(comp[j], x[p]));
+                    R s = R(0);
+                    for (int j = 0; j < K; ++j) s += fast_exp2(log2_term<R, D>(comp[j], x[p]) - mx);
+                    ref[p] = mx;
+                    Sden[p] = s;
+                }
+            }
+
+            // ---------------- sweeps ---------------------------------------------
+            const int max_sweeps = uni(A.max_sweeps);
+            const double tol = uni(A.tol);
+            const int cap_sweeps = fixed > 0 ? fixed : max_sweeps;
+            int Kslots = K;  // slots 0..Kslots-1 hold components; some may die within a sweep
+            uint32_t alive = (1u << K) - 1u;
+            // A particle whose density sum falls far below its reference (every
+            // live component now far from it, e.g. after the one that covered
+            // it was annihilated or moved away) gets its terms recomputed in
+            // log2 space about their own maximum, as a log-sum-exp would, so
+            // that no term underflows to zero.
+            const R rebase_below = R(9.094947017729282e-13);  // 2^-40
+            auto rebase_store = [&](int p, const R (&xp)[D], R& refp) -> R {
+                R mx = R(-INFINITY);
+#pragma unroll
+                for (int j = 0; j < KMAX; ++j) {
+                    const bool live = j < Kslots && ((alive >> j) & 1u);
+                    const R t = live ? log2_term<R, D>(comp[j], xp) : R(-INFINITY);
+                    e.set(p, j, t);
+                    mx = fmax(mx, t);
+                }
+                if (!(mx > R(-INFINITY))) return R(0);
+#pragma unroll
+                for (int j = 0; j < KMAX; ++j)
+                    e.set(p, j, (j < Kslots && ((alive >> j) & 1u)) ? fast_exp2(e.get(p, j) - mx) : R(0));
+                refp = mx;
+                return e.sum(p);
+            };
+            auto rebase_sum = [&](const R (&xp)[D], R& refp) -> R {
+                R mx = R(-INFINITY);
+                for (int j = 0; j < Kslots; ++j)
+                    if ((alive >> j) & 1u) mx = fmax(mx, log2_term<R, D>(comp[j], xp));
+                if (!(mx > R(-INFINITY))) return R(0);
+                R sum = R(0);
+                for (int j = 0; j < Kslots; ++j)
+                    if ((alive >> j) & 1u) sum += fast_exp2(log2_term<R, D>(comp[j], xp) - mx);
+                refp = mx;
+                return sum;
+            };
+            // Particles flagged in `low` lost most of their density in an
+            // update (the running sum may have cancelled): re-sum their terms
+            // exactly, and rebase those whose sum is still tiny.  Particles
+            // flagged in `big` got a term more than 2^64 above their reference
+            // (a component moved onto a particle that had been rebased far
+            // down): rebase them.  The branch is wave-uniform and rarely taken.
+            // The flags are per-particle lane masks (SALU), not VGPR bit sets.
+            auto repair_store = [&](bool any, const bool (&low)[P], const bool (&big)[P]) {
                 if constexpr (STORE_E) {
-                    for (int j = 0; j < K; ++j) {
-                        const CompState<R, D> cj = comp[j];
-#pragma unroll
-                        for (int p = 0; p < P; ++p) e.set(p, j, log2_term<R, D>(cj, x[p]));
-                    }
+                    if (__builtin_amdgcn_ballot_w64(any) == 0) return;
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        R mx = e.get(p, 0);
-#pragma unroll
-                        for (int j = 1; j < KMAX; ++j)
-                            if (j < K) mx = fmax(mx, e.get(p, j));
-                        ref[p] = mx;
-#pragma unroll
-                        for (int j = 0; j < KMAX; ++j) e.set(p, j, (j < K) ? fast_exp2(e.get(p, j) - mx) : R(0));
-                        Sden[p] = e.sum(p);
-                    }
-                } else {
-#pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        R mx = R(-1e30);
-                        for (int j = 0; j < K; ++j) mx = fmax(mx, log2_term<R, D>(comp[j], x[p]));
-                        R s = R(0);
-                        for (int j = 0; j < K; ++j) s += fast_exp2(log2_term<R, D>(comp[j], x[p]) - mx);
-                        ref[p] = mx;
-                        Sden[p] = s;
+                        if (big[p]) {
+                            Sden[p] = rebase_store(p, x[p], ref[p]);
+                        } else if (low[p]) {
+                            Sden[p] = e.sum(p);
+                            if (!(Sden[p] > rebase_below)) Sden[p] = rebase_store(p, x[p], ref[p]);
+                        }
                     }
                 }
+            };
 
-                // ---------------- sweeps ---------------------------------------------
-                const int max_sweeps = A.max_sweeps;
-                const double tol = A.tol;
-                const int cap_sweeps = fixed > 0 ? fixed : max_sweeps;
-                int Kslots = K;  // slots 0..Kslots-1 hold components; some may die within a sweep
-                uint32_t alive = (1u << K) - 1u;
-                // A particle whose density sum falls far below its reference (every
-                // live component now far from it, e.g. after the one that covered
-                // it was annihilated or moved away) gets its terms recomputed in
-                // log2 space about their own maximum, as a log-sum-exp would, so
-                // that no term underflows to zero.
-                const R rebase_below = R(9.094947017729282e-13);  // 2^-40
-                auto rebase_store = [&](int p, const R (&xp)[D], R& refp) -> R {
-                    R mx = R(-INFINITY);
+            double L_prev = 0.0;
+            for (s = 1; s <= cap_sweeps; ++s) {
+                // what the sweeps carry along stays in scalar registers
+                alive = uni((int)alive);
+                Kslots = uni(Kslots);
+                K = uni(K);
+                status = uni(status);
+                par_r = uni(par_r);
+                par_d = uni(par_d);
+                L_prev = uni(L_prev);
+                bool annihilated = false;
+                // the live slots in order; the next one's mean and weight
+                // are read from LDS while the current one is updated
+                R nxmu[D], nxu;
+                auto fetch = [&](int j) {
 #pragma unroll
-                    for (int j = 0; j < KMAX; ++j) {
-                        const bool live = j < Kslots && ((alive >> j) & 1u);
-                        const R t = live ? log2_term<R, D>(comp[j], xp) : R(-INFINITY);
-                        e.set(p, j, t);
-                        mx = fmax(mx, t);
-                    }
-                    if (!(mx > R(-INFINITY))) return R(0);
+                    for (int i = 0; i < D; ++i) nxmu[i] = comp[j].mu[i];
+                    nxu = comp[j].u;
+                };
+                uint32_t todo = uni((int)alive);
+                fetch(todo != 0 ? __builtin_ctz(todo) : 0);
+                while (todo != 0) {
+                    const int k = uni(__builtin_ctz(todo));
+                    todo &= todo - 1;
+                    ++visits;
+                    R ckmu[D];
 #pragma unroll
-                    for (int j = 0; j < KMAX; ++j)
-                        e.set(p, j, (j < Kslots && ((alive >> j) & 1u)) ? fast_exp2(e.get(p, j) - mx) : R(0));
-                    refp = mx;
-                    return e.sum(p);
-                };
-                auto rebase_sum = [&](const R (&xp)[D], R& refp) -> R {
-                    R mx = R(-INFINITY);
-                    for (int j = 0; j < Kslots; ++j)
-                        if ((alive >> j) & 1u) mx = fmax(mx, log2_term<R, D>(comp[j], xp));
-                    if (!(mx > R(-INFINITY))) return R(0);
-                    R sum = R(0);
-                    for (int j = 0; j < Kslots; ++j)
-                        if ((alive >> j) & 1u) sum += fast_exp2(log2_term<R, D>(comp[j], xp) - mx);
-                    refp = mx;
-                    return sum;
-                };
-                // Particles flagged in `low` lost most of their density in an
-                // update (the running sum may have cancelled): re-sum their terms
-                // exactly, and rebase those whose sum is still tiny.  Particles
-                // flagged in `big` got a term more than 2^64 above their reference
-                // (a component moved onto a particle that had been rebased far
-                // down): rebase them.  The branch is wave-uniform and rarely taken.
-                // The flags are per-particle lane masks (SALU), not VGPR bit sets.
-                auto repair_store = [&](bool any, const bool (&low)[P], const bool (&big)[P]) {
+                    for (int i = 0; i < D; ++i) ckmu[i] = nxmu[i];
+                    const R cku = nxu;
+                    fetch(todo != 0 ? __builtin_ctz(todo) : k);
+                    // E-step of k with the current parameters of every component,
+                    // and the M-step sums about the current mean of k
+                    R sums[NS];
+#pragma unroll
+                    for (int t = 0; t < NS; ++t) sums[t] = R(0);
+                    [[maybe_unused]] R eold[STORE_E ? 1 : P];
+                    auto accumulate = [&](int p, R ek, R den) {
+                        // den > 0 for every particle of a fitted cell (the rebase keeps
+                        // it above 2^-40); the clamp keeps a zero from turning a
+                        // zero-weight padding particle's 0 * inf into NaN
+                        const R inv = fmin(fast_rcp(den), R(kBigFinite<R>));
+                        const R ae = a[p] * ek;
+                        const R g = ae * inv;
+                        R d[D];
+#pragma unroll
+                        for (int i = 0; i < D; ++i) d[i] = x[p][i] - ckmu[i];
+                        sums[0] = fma(ae, inv, sums[0]);
+#pragma unroll
+                        for (int i = 0; i < D; ++i) {
+                            const R gd = g * d[i];
+                            sums[1 + i] = fma(g, d[i], sums[1 + i]);
+#pragma unroll
+                            for (int j = i; j < D; ++j)
+                                sums[1 + D + tri_idx<D>(i, j)] = fma(gd, d[j], sums[1 + D + tri_idx<D>(i, j)]);
+                        }
+                    };
                     if constexpr (STORE_E) {
-                        if (__builtin_amdgcn_ballot_w64(any) == 0) return;
+#pragma unroll
+                        for (int p = 0; p < P; ++p) accumulate(p, e.get(p, k), Sden[p]);
+                    } else {
+                        const CompState<R, D> ck = comp[k];
 #pragma unroll
                         for (int p = 0; p < P; ++p) {
-                            if (big[p]) {
-                                Sden[p] = rebase_store(p, x[p], ref[p]);
-                            } else if (low[p]) {
-                                Sden[p] = e.sum(p);
-                                if (!(Sden[p] > rebase_below)) Sden[p] = rebase_store(p, x[p], ref[p]);
-                            }
+                            eold[p] = fast_exp2(fmin(log2_term<R, D>(ck, x[p]) - ref[p], R(64)));
+                            accumulate(p, eold[p], Sden[p]);
                         }
                     }
-                };
-
-                double L_prev = 0.0;
-                for (s = 1; s <= cap_sweeps; ++s) {
-                    bool annihilated = false;
-                    for (int k = 0; k < Kslots; ++k) {
-                        if (!((alive >> k) & 1u)) continue;
-                        ++visits;
-                        R ckmu[D];
-#pragma unroll
-                        for (int i = 0; i < D; ++i) ckmu[i] = comp[k].mu[i];
-                        const R cku = comp[k].u;
-                        // E-step of k with the current parameters of every component,
-                        // and the M-step sums about the current mean of k
-                        R sums[NS];
-#pragma unroll
-                        for (int t = 0; t < NS; ++t) sums[t] = R(0);
-                        [[maybe_unused]] R eold[STORE_E ? 1 : P];
-                        auto accumulate = [&](int p, R ek, R den) {
-                            // den > 0 for every particle of a fitted cell (the rebase keeps
-                            // it above 2^-40); the clamp keeps a zero from turning a
-                            // zero-weight padding particle's 0 * inf into NaN
-                            const R inv = fmin(fast_rcp(den), R(kBigFinite<R>));
-                            const R g = a[p] * ek * inv;
-                            R d[D];
-#pragma unroll
-                            for (int i = 0; i < D; ++i) d[i] = x[p][i] - ckmu[i];
-                            sums[0] += g;
-#pragma unroll
-                            for (int i = 0; i < D; ++i) {
-                                const R gd = g * d[i];
-                                sums[1 + i] += gd;
-#pragma unroll
-                                for (int j = i; j < D; ++j) sums[1 + D + tri_idx<D>(i, j)] += gd * d[j];
-                            }
-                        };
-                        if constexpr (STORE_E) {
-#pragma unroll
-                            for (int p = 0; p < P; ++p) accumulate(p, e.get(p, k), Sden[p]);
-                        } else {
-                            const CompState<R, D> ck = comp[k];
-#pragma unroll
-                            for (int p = 0; p < P; ++p) {
-                                eold[p] = fast_exp2(fmin(log2_term<R, D>(ck, x[p]) - ref[p], R(64)));
-                                accumulate(p, eold[p], Sden[p]);
-                            }
-                        }
-                        em_block_sum<NS, MAXW>(sums, red_r, par_r, nwaves);
-                        const R Nk = sums[0];
-                        const R NkT = Nk - (R)halfT;
-                        if (fabs(NkT) < (R)(1e-5 * halfT)) status |= GM_ST_NEAR_TIE;
-                        if (NkT <= R(0)) {
-                            // annihilate k (eq. omegak); the weights renormalise through G
-                            alive &= ~(1u << k);
-                            G -= cku;
-                            --K;
-                            inv_den = m_rcp((R)(N - halfT * K));
-                            annihilated = true;
-                            if constexpr (STORE_E) {
-                                bool low[P], big[P], any = false;
-#pragma unroll
-                                for (int p = 0; p < P; ++p) {
-                                    const R s_old = Sden[p];
-                                    const R s_new = s_old - e.get(p, k);
-                                    e.set(p, k, R(0));
-                                    Sden[p] = s_new;
-                                    low[p] = !(s_new > R(1e-3) * s_old);
-                                    big[p] = false;
-                                    any |= low[p];
-                                }
-                                repair_store(any, low, big);
-                            } else {
-#pragma unroll
-                                for (int p = 0; p < P; ++p) {
-                                    const R s_old = Sden[p];
-                                    R s_new = s_old - eold[p];
-                                    if (!(s_new > R(1e-4) * s_old)) {
-                                        s_new = R(0);
-                                        for (int j = 0; j < Kslots; ++j)
-                                            if ((alive >> j) & 1u)
-                                                s_new += fast_exp2(fmin(log2_term<R, D>(comp[j], x[p]) - ref[p], R(64)));
-                                    }
-                                    Sden[p] = (s_new > rebase_below) ? s_new : rebase_sum(x[p], ref[p]);
-                                }
-                            }
-                            continue;
-                        }
+                    em_block_sum<NS, MAXW>(sums, red_r, par_r, nwaves);
+                    const R Nk = sums[0];
+                    const R NkT = Nk - (R)halfT;
+                    if (uni(fabs(NkT) < (R)(1e-5 * halfT))) status |= GM_ST_NEAR_TIE;
+                    const bool dead = uni(NkT <= R(0));
+                    CompState<R, D> cn;
+                    if (dead) {
+                        // annihilate k (eq. omegak); the weights renormalise through G
+                        alive &= ~(1u << k);
+                        G -= cku;
+                        --K;
+                        inv_den = m_rcp((R)(N - halfT * K));
+                        annihilated = true;
+                    } else {
                         // M-step (eqs. muk, sigmak about the new mean; eq. omegak)
-                        CompState<R, D> cn;
                         const R invN = m_rcp(Nk);
                         R dl[D];
 #pragma unroll
@@ -1007,237 +1018,358 @@ void k_em(CompressArgs A_in)
                         for (int i = 0; i < D; ++i)
 #pragma unroll
                             for (int j = i; j < D; ++j)
-                                cn.S[tri_idx<D>(i, j)] = sums[1 + D + tri_idx<D>(i, j)] * invN - dl[i] * dl[j];
+                                cn.S[tri_idx<D>(i, j)] = fma(sums[1 + D + tri_idx<D>(i, j)], invN, -(dl[i] * dl[j]));
                         const R wk = NkT * inv_den;
                         const R unew = wk * G;
                         G = G - cku + unew;
                         cn.u = unew;
-                        if (factor_comp<R, D>(cn, trC, sdc)) status |= GM_ST_COV_FLOOR;
+                        if (uni(factor_comp<R, D>(cn, ci->trC, sdc))) status |= GM_ST_COV_FLOOR;
                         if (lane == 0) comp[k] = cn;  // this wave's copy; read back only by this wave
-                        if constexpr (STORE_E) {
-                            bool low[P], big[P], any = false;
-#pragma unroll
-                            for (int p = 0; p < P; ++p) {
-                                const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
-                                const R enew = fast_exp2(fmin(dt, R(64)));
-                                const R s_old = Sden[p];
-                                const R s_new = s_old - e.get(p, k) + enew;
-                                e.set(p, k, enew);
-                                Sden[p] = s_new;
-                                low[p] = !(s_new > R(1e-3) * s_old);
-                                big[p] = dt > R(64);
-                                any |= low[p] | big[p];
-                            }
-                            repair_store(any, low, big);
-                        } else {
-#pragma unroll
-                            for (int p = 0; p < P; ++p) {
-                                const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
-                                const R enew = fast_exp2(fmin(dt, R(64)));
-                                const R s_old = Sden[p];
-                                R s_new = s_old - eold[p] + enew;
-                                if (!(s_new > R(1e-4) * s_old)) {
-                                    // the particle lost most of its density: re-sum exactly
-                                    s_new = enew;
-                                    for (int j = 0; j < Kslots; ++j)
-                                        if (j != k && ((alive >> j) & 1u))
-                                            s_new += fast_exp2(fmin(log2_term<R, D>(comp[j], x[p]) - ref[p], R(64)));
-                                }
-                                Sden[p] = (s_new > rebase_below && !(dt > R(64))) ? s_new : rebase_sum(x[p], ref[p]);
-                            }
-                        }
                     }
-
-                    // ---- end of sweep: per-particle mixture density, eq. (lnL-GM) ----
-                    const R lg2G = fast_log2(G);
-                    double lsum[1] = {0.0};
-                    R dens[P];
-                    uint32_t low = 0;
                     if constexpr (STORE_E) {
-#pragma unroll
-                        for (int p = 0; p < P; ++p) dens[p] = e.sum(p);
-                    } else if (s % kResumSweeps != 0 && !annihilated) {
-                        // the running sums, kept through the sweep's updates
-                        // (each re-summed exactly where it had cancelled)
-#pragma unroll
-                        for (int p = 0; p < P; ++p) dens[p] = Sden[p];
-                    } else {
-                        // exact re-sum every kResumSweeps sweeps and after an
-                        // annihilation: component outer, particles inner, each
-                        // component's parameters read from LDS once
-#pragma unroll
-                        for (int p = 0; p < P; ++p) dens[p] = R(0);
-                        for (int j = 0; j < Kslots; ++j) {
-                            if (!((alive >> j) & 1u)) continue;
-                            const CompState<R, D> cj = comp[j];
-#pragma unroll
-                            for (int p = 0; p < P; ++p)
-                                dens[p] += fast_exp2(fmin(log2_term<R, D>(cj, x[p]) - ref[p], R(64)));
-                        }
-                    }
-#pragma unroll
-                    for (int p = 0; p < P; ++p) low |= (uint32_t)!(dens[p] > rebase_below) << p;
-                    if (__builtin_amdgcn_ballot_w64(low != 0) != 0) {
+                        // the term of k after the update: none if it died
+                        bool low[P], big[P], any = false;
+                        R s_old[P], s_new[P], enew[P];
 #pragma unroll
                         for (int p = 0; p < P; ++p) {
-                            if ((low >> p) & 1u) {
-                                if constexpr (STORE_E)
-                                    dens[p] = rebase_store(p, x[p], ref[p]);
-                                else
-                                    dens[p] = rebase_sum(x[p], ref[p]);
+                            s_old[p] = Sden[p];
+                            s_new[p] = s_old[p] - e.get(p, k);
+                            enew[p] = R(0);
+                            big[p] = false;
+                        }
+                        if (!dead) {
+#pragma unroll
+                            for (int p = 0; p < P; ++p) {
+                                const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
+                                enew[p] = fast_exp2(fmin(dt, R(64)));
+                                s_new[p] = s_new[p] + enew[p];
+                                big[p] = dt > R(64);
+                                any |= big[p];
                             }
                         }
+#pragma unroll
+                        for (int p = 0; p < P; ++p) {
+                            e.set(p, k, enew[p]);
+                            Sden[p] = s_new[p];
+                            low[p] = !(s_new[p] > R(1e-3) * s_old[p]);
+                            any |= low[p];
+                        }
+                        repair_store(any, low, big);
+                    } else if (dead) {
+#pragma unroll
+                        for (int p = 0; p < P; ++p) {
+                            const R s_old = Sden[p];
+                            R s_new = s_old - eold[p];
+                            if (!(s_new > R(1e-4) * s_old)) {
+                                s_new = R(0);
+                                for (int j = 0; j < Kslots; ++j)
+                                    if ((alive >> j) & 1u)
+                                        s_new += fast_exp2(fmin(log2_term<R, D>(comp[j], x[p]) - ref[p], R(64)));
+                            }
+                            Sden[p] = (s_new > rebase_below) ? s_new : rebase_sum(x[p], ref[p]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int p = 0; p < P; ++p) {
+                            const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
+                            const R enew = fast_exp2(fmin(dt, R(64)));
+                            const R s_old = Sden[p];
+                            R s_new = s_old - eold[p] + enew;
+                            if (!(s_new > R(1e-4) * s_old)) {
+                                // the particle lost most of its density: re-sum exactly
+                                s_new = enew;
+                                for (int j = 0; j < Kslots; ++j)
+                                    if (j != k && ((alive >> j) & 1u))
+                                        s_new += fast_exp2(fmin(log2_term<R, D>(comp[j], x[p]) - ref[p], R(64)));
+                            }
+                            Sden[p] = (s_new > rebase_below && !(dt > R(64))) ? s_new : rebase_sum(x[p], ref[p]);
+                        }
                     }
+                }
+
+                // ---- end of sweep: per-particle mixture density, eq. (lnL-GM) ----
+                annihilated = uni(annihilated);
+                const R lg2G = fast_log2(G);
+                double lsum[1] = {0.0};
+                R dens[P];
+                uint32_t low = 0;
+                if constexpr (STORE_E) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p) dens[p] = e.sum(p);
+                } else if (s % kResumSweeps != 0 && !annihilated) {
+                    // the running sums, kept through the sweep's updates
+                    // (each re-summed exactly where it had cancelled)
+#pragma unroll
+                    for (int p = 0; p < P; ++p) dens[p] = Sden[p];
+                } else {
+                    // exact re-sum every kResumSweeps sweeps and after an
+                    // annihilation: component outer, particles inner, each
+                    // component's parameters read from LDS once
+#pragma unroll
+                    for (int p = 0; p < P; ++p) dens[p] = R(0);
+                    for (int j = 0; j < Kslots; ++j) {
+                        if (!((alive >> j) & 1u)) continue;
+                        const CompState<R, D> cj = comp[j];
+#pragma unroll
+                        for (int p = 0; p < P; ++p)
+                            dens[p] += fast_exp2(fmin(log2_term<R, D>(cj, x[p]) - ref[p], R(64)));
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < P; ++p) low |= (uint32_t)!(dens[p] > rebase_below) << p;
+                if (__builtin_amdgcn_ballot_w64(low != 0) != 0) {
 #pragma unroll
                     for (int p = 0; p < P; ++p) {
-                        const R den = dens[p];
-                        const R lg = fast_log2(den);
+                        if ((low >> p) & 1u) {
+                            if constexpr (STORE_E)
+                                dens[p] = rebase_store(p, x[p], ref[p]);
+                            else
+                                dens[p] = rebase_sum(x[p], ref[p]);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    const R den = dens[p];
+                    const R lg = fast_log2(den);
+                    if constexpr (STORE_E) {
+                        // the weights are normalised below (u_j / G, c_j - log2 G):
+                        // lowering the reference by log2 G keeps every stored term
+                        ref[p] = ref[p] - lg2G;
+                        lsum[0] = fma((double)a[p], (double)(ref[p] + lg), lsum[0]);  // log2 mixture density at x_p
+                        Sden[p] = den;
+                    } else {
+                        ref[p] = ref[p] + lg - lg2G;  // log2 of the normalised mixture density at x_p
+                        lsum[0] = fma((double)a[p], (double)ref[p], lsum[0]);
+                        Sden[p] = R(1);
+                    }
+                }
+                block_sum<2, MAXW>(lsum, red_d, par_d, nwaves);
+                // normalise the weights in this wave's copy: u_j /= G, c2_j -= log2 G
+                if (lane < Kslots && ((alive >> lane) & 1u)) {
+                    comp[lane].u = comp[lane].u * m_rcp(G);
+                    comp[lane].c2 = comp[lane].c2 - lg2G;
+                }
+                // G = sum_j u_j and sum_j log2(u_j / G) over the live slots, lane j
+                // holding slot j (a 16-lane tree, then broadcast from lane 0)
+                const bool live_lane = lane < Kslots && ((alive >> lane) & 1u);
+                R uj = live_lane ? comp[lane].u : R(0);
+                R Gn = uj;
+                Gn += dpp_get<0xB1>(Gn);
+                Gn += dpp_get<0x4E>(Gn);
+                Gn += dpp_get<0x141>(Gn);
+                Gn += dpp_get<0x140>(Gn);
+                Gn = lane_bcast(Gn, 0);
+                double pl = live_lane ? (double)fast_log2(uj * m_rcp(Gn)) : 0.0;
+                pl += dpp_get<0xB1>(pl);
+                pl += dpp_get<0x4E>(pl);
+                pl += dpp_get<0x141>(pl);
+                pl += dpp_get<0x140>(pl);
+                const double pen = lane_bcast(pl, 0);
+                G = Gn;
+                const double dpar = K * T + K - 1;
+                // ref_p is log2 of the mixture density relative to (2 pi)^(-D/2) / sqrt det C
+                L_s = uni(kLn2 * (lsum[0] - 0.5 * T * pen) + N * lnc0 - 0.5 * dpar * lnN);
+
+                // ---- compaction of dead slots (rare) ----
+                if (annihilated) {
+                    for (int k = Kslots - 1; k >= 0; --k) {
+                        if ((alive >> k) & 1u) continue;
+                        if (lane == 0)
+                            for (int j = k; j + 1 < Kslots; ++j) comp[j] = comp[j + 1];
                         if constexpr (STORE_E) {
-                            // the weights are normalised below (u_j / G, c_j - log2 G):
-                            // lowering the reference by log2 G keeps every stored term
-                            ref[p] = ref[p] - lg2G;
-                            lsum[0] += (double)a[p] * (double)(ref[p] + lg);  // log2 mixture density at x_p
-                            Sden[p] = den;
-                        } else {
-                            ref[p] = ref[p] + lg - lg2G;  // log2 of the normalised mixture density at x_p
-                            lsum[0] += (double)a[p] * (double)ref[p];
-                            Sden[p] = R(1);
+#pragma unroll
+                            for (int j = 0; j + 1 < KMAX; ++j)
+                                if (j >= k) {
+#pragma unroll
+                                    for (int p = 0; p < P; ++p) e.set(p, j, e.get(p, j + 1));
+                                }
+#pragma unroll
+                            for (int p = 0; p < P; ++p) e.set(p, KMAX - 1, R(0));
                         }
+                        const uint32_t low = alive & ((1u << k) - 1u);
+                        const uint32_t high = (alive >> (k + 1)) << k;
+                        alive = low | high;
+                        --Kslots;
                     }
-                    block_sum<2, MAXW>(lsum, red_d, par_d, nwaves);
-                    // normalise the weights in this wave's copy: u_j /= G, c2_j -= log2 G
-                    if (lane < Kslots && ((alive >> lane) & 1u)) {
-                        comp[lane].u = comp[lane].u * m_rcp(G);
-                        comp[lane].c2 = comp[lane].c2 - lg2G;
-                    }
-                    // G = sum_j u_j and sum_j log2(u_j / G) over the live slots, lane j
-                    // holding slot j (a 16-lane tree, then broadcast from lane 0)
-                    const bool live_lane = lane < Kslots && ((alive >> lane) & 1u);
-                    R uj = live_lane ? comp[lane].u : R(0);
-                    R Gn = uj;
-                    Gn += dpp_get<0xB1>(Gn);
-                    Gn += dpp_get<0x4E>(Gn);
-                    Gn += dpp_get<0x141>(Gn);
-                    Gn += dpp_get<0x140>(Gn);
-                    Gn = lane_bcast(Gn, 0);
-                    double pl = live_lane ? (double)fast_log2(uj * m_rcp(Gn)) : 0.0;
-                    pl += dpp_get<0xB1>(pl);
-                    pl += dpp_get<0x4E>(pl);
-                    pl += dpp_get<0x141>(pl);
-                    pl += dpp_get<0x140>(pl);
-                    const double pen = lane_bcast(pl, 0);
-                    G = Gn;
-                    const double dpar = K * T + K - 1;
-                    // ref_p is log2 of the mixture density relative to (2 pi)^(-D/2) / sqrt det C
-                    L_s = kLn2 * (lsum[0] - 0.5 * T * pen) + N * lnc0 - 0.5 * dpar * lnN;
+                }
 
-                    // ---- compaction of dead slots (rare) ----
-                    if (annihilated) {
-                        for (int k = Kslots - 1; k >= 0; --k) {
-                            if ((alive >> k) & 1u) continue;
-                            if (lane == 0)
-                                for (int j = k; j + 1 < Kslots; ++j) comp[j] = comp[j + 1];
-                            if constexpr (STORE_E) {
-#pragma unroll
-                                for (int j = 0; j + 1 < KMAX; ++j)
-                                    if (j >= k) {
-#pragma unroll
-                                        for (int p = 0; p < P; ++p) e.set(p, j, e.get(p, j + 1));
-                                    }
-#pragma unroll
-                                for (int p = 0; p < P; ++p) e.set(p, KMAX - 1, R(0));
-                            }
-                            const uint32_t low = alive & ((1u << k) - 1u);
-                            const uint32_t high = (alive >> (k + 1)) << k;
-                            alive = low | high;
-                            --Kslots;
-                        }
-                    }
-
-                    if (fixed > 0) {
-                        if (s == fixed) break;
-                        L_prev = L_s;
-                        continue;
-                    }
-                    if (!isfinite(L_s)) break;  // the objective is undefined: no further sweep can help
-                    if (s >= 2 && !annihilated && fabs(L_s - L_prev) <= tol * fabs(L_s)) break;
-                    // FP32 resolves L only to the rounding of the per-particle
-                    // log-densities it sums, about 1e-7 of N: a change of L within
-                    // tol N, or a lower L (the iteration does not lower L between
-                    // sweeps without an annihilation), is below that, and the fit
-                    // stops as converged
-                    if constexpr (std::is_same<R, float>::value)
-                        if (s >= 2 && !annihilated && (L_s < L_prev || fabs(L_s - L_prev) <= tol * N)) break;
-                    if (s == max_sweeps) {
-                        status |= GM_ST_MAXSWEEPS;
-                        break;
-                    }
+                if (fixed > 0) {
+                    if (s == fixed) break;
                     L_prev = L_s;
+                    continue;
                 }
-                if (s > cap_sweeps) s = cap_sweeps;
-                s_total += s;
-                if (!outer) break;
-                if (K_best == 0 || L_s > L_best) {
-                    if (wid == 0 && lane < K) bestc[lane] = comp[lane];
-                    L_best = L_s;
-                    K_best = K;
-                    G_best = G;
+                if (!isfinite(L_s)) break;  // the objective is undefined: no further sweep can help
+                if (s >= 2 && !annihilated && fabs(L_s - L_prev) <= tol * fabs(L_s)) break;
+                // FP32 resolves L only to the rounding of the per-particle
+                // log-densities it sums, about 1e-7 of N: a change of L within
+                // tol N, or a lower L (the iteration does not lower L between
+                // sweeps without an annihilation), is below that, and the fit
+                // stops as converged
+                if constexpr (std::is_same<R, float>::value)
+                    if (s >= 2 && !annihilated && (L_s < L_prev || fabs(L_s - L_prev) <= tol * N)) break;
+                if (s == max_sweeps) {
+                    status |= GM_ST_MAXSWEEPS;
+                    break;
                 }
-                if (K <= 1 || !isfinite(L_s)) break;
-                // remove the least probable component (smallest weight, lowest
-                // slot on ties); the others keep their parameters and the
-                // weights renormalise through G
-                int kmin = 0;
-                R umin = comp[0].u;
-                for (int j = 1; j < K; ++j) {
-                    const R uj = comp[j].u;
-                    if (uj < umin) {
-                        umin = uj;
-                        kmin = j;
-                    }
-                }
-                if (lane == 0)
-                    for (int j = kmin; j + 1 < K; ++j) comp[j] = comp[j + 1];
-                G -= umin;
-                --K;
+                L_prev = L_s;
             }
-            if (outer && K_best > 0) {
-                __syncthreads();  // the best state, written by wave 0, into every wave's copy
-                if (lane < K_best) comp[lane] = bestc[lane];
-                K = K_best;
-                G = G_best;
-                L_s = L_best;
+            if (s > cap_sweeps) s = cap_sweeps;
+            s_total += s;
+            if (!outer) break;
+            L_best = uni(L_best);
+            K_best = uni(K_best);
+            if (K_best == 0 || L_s > L_best) {
+                if (wid == 0 && lane < K) bestc[lane] = comp[lane];
+                L_best = L_s;
+                K_best = K;
+                G_best = G;
             }
-            s = s_total;
-            if (!warm || fixed > 0 || L_s >= L_one - 1e-5 * fabs(L_one)) break;
-            // rejected warm start: cold start, flags of the cold fit only
-            warm = false;
-            status = GM_ST_WARM_FALLBACK;
-            __syncthreads();
+            if (K <= 1 || !isfinite(L_s)) break;
+            // remove the least probable component (smallest weight, lowest
+            // slot on ties); the others keep their parameters and the
+            // weights renormalise through G
+            int kmin = 0;
+            R umin = uni(comp[0].u);
+            for (int j = 1; j < K; ++j) {
+                const R uj = comp[j].u;
+                if (uni(uj) < umin) {
+                    umin = uni(uj);
+                    kmin = j;
+                }
+            }
+            if (lane == 0)
+                for (int j = kmin; j + 1 < K; ++j) comp[j] = comp[j + 1];
+            G -= umin;
+            --K;
         }
+        if (outer && K_best > 0) {
+            __syncthreads();  // the best state, written by wave 0, into every wave's copy
+            if (lane < K_best) comp[lane] = bestc[lane];
+            K = K_best;
+            G = G_best;
+            L_s = L_best;
+        }
+        s = s_total;
+        if (!warm || fixed > 0) break;
+        const double L_one = uni(N * (lnc0 - 0.5 * D) - halfT * lnN);
+        if (L_s >= L_one - 1e-5 * fabs(L_one)) break;
+        // rejected warm start: cold start, flags of the cold fit only
+        warm = false;
+        status = GM_ST_WARM_FALLBACK;
+        __syncthreads();
+    }
 
-        // ---------------- penalised state into the output record -------------
-        // (centred coordinates; k_finish turns it into the final mixture)
-        if (tid < K) {
-            const size_t sk = (size_t)c * kmax + tid;
-            const CompState<R, D> cs = compw[0][tid];
-            A.out.omega[sk] = (double)cs.u / (double)G;
-            for (int d = 0; d < D; ++d) A.out.mu[sk * D + d] = (double)cs.mu[d];
-            for (int q = 0; q < NT; ++q) A.out.sigma[sk * NT + q] = (double)cs.S[q];
-        }
-        if (tid == 0) {
-            A.out.K[c] = K;
-            A.out.L_pen[c] = L_s;
-            A.out.sweeps[c] = s;
-            A.out.visits[c] = visits;
-            A.out.status[c] = status;
-        }
+    // ---------------- penalised state into the output record -------------
+    // (centred coordinates; k_finish turns it into the final mixture)
+    if (tid < K) {
+        const size_t sk = (size_t)c * kmax + tid;
+        const CompState<R, D> cs = compw[0][tid];
+        A.out.omega[sk] = (double)cs.u / (double)G;
+        for (int d = 0; d < D; ++d) A.out.mu[sk * D + d] = (double)cs.mu[d];
+        for (int q = 0; q < NT; ++q) A.out.sigma[sk * NT + q] = (double)cs.S[q];
+    }
+    if (tid == 0) {
+        A.out.K[c] = K;
+        A.out.L_pen[c] = L_s;
+        A.out.sweeps[c] = s;
+        A.out.visits[c] = visits;
+        A.out.status[c] = status;
+    }
+}
+
+template <int D, int KMAX, typename R>
+constexpr int em_span_waves_per_simd()
+{
+    return D == 1 && KMAX == 8 && std::is_same<R, float>::value ? 3 : 1;
+}
+
+template <int D, int KMAX, int P, bool STORE_E, typename R, bool LEAN>
+__global__ __launch_bounds__(LEAN ? kEmLeanThreads : kEmMaxThreads, (em_min_waves_per_simd<R, LEAN, P, STORE_E>()))
+void k_em(CompressArgs A_in)
+{
+    constexpr int MAXW = em_max_waves(LEAN);
+    __shared__ EmShared<D, KMAX, R, MAXW> sh;
+    const int tid = threadIdx.x;
+    if (tid == 0) sh.A = A_in;
+    for (int t = tid; t < 2 * MAXW * sh.NS; t += blockDim.x) sh.red_r[t] = R(0);
+    __syncthreads();
+    const int bucket = uni(sh.A.bucket), nwaves = uni(sh.A.nwaves);
+    const int count = uni(sh.A.plan[PLAN_COUNT + bucket]);
+    const int base = uni(sh.A.plan[PLAN_BASE + bucket]);
+    int par_d = 0, par_r = 0;
+    for (;;) {
+        if (tid == 0) sh.s_idx = atomicAdd(&sh.A.plan[PLAN_QUEUE + bucket], 1);
         __syncthreads();
-        if (tid == 0) s_idx = atomicAdd(&A.plan[PLAN_QUEUE + bucket], 1);
-        __syncthreads();
-        idx = s_idx;
+        const int idx = uni(sh.s_idx);
         __syncthreads();
         if (idx >= count) break;
+        em_fit_cell<D, KMAX, P, STORE_E, R, MAXW>(sh, uni(sh.A.list[base + idx]), nwaves, par_d, par_r);
+        __syncthreads();
+    }
+}
+
+// The built-in plan's launches: persistent workgroups that walk the buckets
+// b_hi .. b_lo, widest cells first.  A bucket's cells are fitted by the
+// built-in plan's number of waves (so with its sums, bit for bit) and by the
+// fewest particles per thread that hold the cell; a workgroup that comes to
+// a narrower bucket goes on with its first waves, the others end and leave
+// their registers to the workgroups still waiting.
+template <int D, int KMAX, int PHI, typename R>
+__global__ __launch_bounds__(kEmMaxThreads, (em_span_waves_per_simd<D, KMAX, R>()))
+void k_em_span(CompressArgs A_in, int b_hi, int b_lo)
+{
+    constexpr int MAXW = em_max_waves(false);
+    __shared__ EmShared<D, KMAX, R, MAXW> sh;
+    const int tid = threadIdx.x;
+    const int wid = uni(tid >> 6);
+    if (tid == 0) sh.A = A_in;
+    for (int t = tid; t < 2 * MAXW * sh.NS; t += blockDim.x) sh.red_r[t] = R(0);
+    __syncthreads();
+    int par_d = 0, par_r = 0;
+    int nwaves = (int)(blockDim.x >> 6);
+#pragma unroll 1
+    for (int b = b_hi; b >= b_lo; --b) {
+        const int count = uni(sh.A.plan[PLAN_COUNT + b]);
+        if (count == 0) continue;
+        const int base = uni(sh.A.plan[PLAN_BASE + b]);
+        const int W = em_default<D>(KMAX, !std::is_same<R, float>::value, b).waves;
+        bool narrowed = W >= nwaves;
+#pragma unroll 1
+        for (;;) {
+            if (tid == 0) sh.s_idx = atomicAdd(&sh.A.plan[PLAN_QUEUE + b], 1);
+            __syncthreads();
+            const int idx = uni(sh.s_idx);
+            __syncthreads();
+            if (idx >= count) break;
+            if (!narrowed) {
+                // the waves beyond W end here; what they last published is
+                // cleared, as the sums run over all MAXW slots
+                if (wid >= W) return;
+                nwaves = W;
+                for (int t = tid; t < 2 * MAXW * sh.NS; t += 64 * W) sh.red_r[t] = R(0);
+                __syncthreads();
+                narrowed = true;
+            }
+            const int c = uni(sh.A.list[base + idx]);
+            const int n = uni(static_cast<const CellInfo<D>*>(sh.A.cells)[c].n);
+            const int P = (n + 64 * W - 1) / (64 * W);
+            auto fit = [&](auto p) {
+                if constexpr (decltype(p)::value <= PHI)
+                    em_fit_cell<D, KMAX, decltype(p)::value, true, R, MAXW>(sh, c, nwaves, par_d, par_r);
+            };
+            switch (P) {
+                case 1: fit(std::integral_constant<int, 1>{}); break;
+                case 2: fit(std::integral_constant<int, 2>{}); break;
+                case 3: fit(std::integral_constant<int, 3>{}); break;
+                case 4: fit(std::integral_constant<int, 4>{}); break;
+                case 5: fit(std::integral_constant<int, 5>{}); break;
+                case 6: fit(std::integral_constant<int, 6>{}); break;
+                case 7: fit(std::integral_constant<int, 7>{}); break;
+                default: fit(std::integral_constant<int, 8>{}); break;
+            }
+            __syncthreads();
+        }
     }
 }
 
@@ -2006,6 +2138,52 @@ int grid_dr(int kmax_tpl, int per_thread, int mode, int waves)
     if (nb < 1) nb = 1;
     slot = nb * ncu;
     return slot;
+}
+
+// The built-in plan's launches (k_em_span).  The most particles per thread
+// of any bucket it holds in registers bounds the builds a launch switches
+// between.
+template <int D, int KMAX, typename R>
+constexpr int em_span_max_per_thread()
+{
+    int m = 0;
+    for (int b = 0; b < kNumBuckets; ++b) {
+        const EmDefault d = em_default<D>(KMAX, !std::is_same<R, float>::value, b);
+        if (d.mode == kModeStoreE && d.per_thread > m) m = d.per_thread;
+    }
+    return m;
+}
+
+template <int D, int KMAX, typename R>
+int launch_span_k(const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t n_cells, hipStream_t st)
+{
+    constexpr int PHI = em_span_max_per_thread<D, KMAX, R>();
+    static int resident[kEmMaxWaves + 1] = {};  // workgroups the device holds at once, per waves
+    auto kern = k_em_span<D, KMAX, PHI, R>;
+    if (resident[waves] == 0) {
+        int dev = 0, ncu = 0, nb = 0;
+        if (hipGetDevice(&dev) != hipSuccess ||
+            hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+            return -1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(kern), 64 * waves, 0) !=
+                hipSuccess ||
+            nb < 1)
+            nb = 1;
+        resident[waves] = nb * ncu;
+    }
+    // twice the resident workgroups, so that some wait for the registers of
+    // waves that end where a workgroup narrows
+    int64_t grid = 2 * (int64_t)resident[waves];
+    if (grid > n_cells) grid = n_cells;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * waves), 0, st, a, b_hi, b_lo);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+template <int D, typename R>
+int launch_span_dr(int kmax_tpl, const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t n_cells, hipStream_t st)
+{
+    return kmax_tpl == 8 ? launch_span_k<D, 8, R>(a, waves, b_hi, b_lo, n_cells, st)
+                         : launch_span_k<D, 16, R>(a, waves, b_hi, b_lo, n_cells, st);
 }
 
 // the big-cell sweeps: `grid` persistent workgroups (they leave at once when

@@ -236,18 +236,21 @@ __device__ __forceinline__ void tri_inv(const R (&L)[ntri(D)], R (&M)[ntri(D)])
     }
 }
 
-// |M d|^2 for packed lower-triangular M
+// c - |M d|^2 for packed lower-triangular M.  The roundings are written out
+// (explicit fma, no contraction), so every copy the compiler inlines, in any
+// build, gives the same bits.
 template <int D, typename R>
-__device__ __forceinline__ R tri_quad(const R* M, const R (&d)[D])
+__device__ __forceinline__ R sub_tri_quad(R c, const R* M, const R (&d)[D])
 {
+#pragma clang fp contract(off)
     if constexpr (D == 1) {
         const R z = M[0] * d[0];
-        return z * z;
+        return fma(-z, z, c);
     } else {
         const R z0 = M[0] * d[0];
-        const R z1 = M[1] * d[0] + M[3] * d[1];
-        const R z2 = M[2] * d[0] + M[4] * d[1] + M[5] * d[2];
-        return z0 * z0 + z1 * z1 + z2 * z2;
+        const R z1 = fma(M[1], d[0], M[3] * d[1]);
+        const R z2 = fma(M[5], d[2], fma(M[2], d[0], M[4] * d[1]));
+        return c - fma(z2, z2, fma(z0, z0, z1 * z1));
     }
 }
 

@@ -91,6 +91,68 @@ constexpr int kEmMaxThreads = 512;
 constexpr int kEmLeanThreads = 1024;
 __host__ __device__ constexpr int em_max_waves(bool lean) { return (lean ? kEmLeanThreads : kEmMaxThreads) / 64; }
 constexpr int kEmMaxWaves = kEmLeanThreads / 64;
+// The built-in plan's variant of bucket b.
+struct EmDefault {
+    int per_thread;  // most particles per thread any cell of the bucket needs
+    int waves;
+    int mode;
+};
+
+// Buckets of cells above 2048 particles (kmax 16) hold few cells, and one
+// long fit among them can set the length of the whole EM phase: there the
+// per-update latency of a single cell matters more than the bucket's
+// throughput.  FP32 iterations run them with a lean build of more than 8
+// waves (four waves per SIMD, the cell's CU to itself; in 3V the cells of
+// 2049-4096 particles take the register-resident builds of the next rule
+// instead).  On the Weibel-like batch one
+// 2049-particle cell running 1000 sweeps made the warm phase 9.6-10.4 ms
+// with it against 13.9-14.8 ms with the 8-wave builds, while a batch without
+// such a fit cannot tell the builds apart, so the tuner keeps this choice.
+constexpr int kChainMinN = 2048;
+__host__ __device__ constexpr bool chain_bucket(int kt, bool fp64, int b)
+{
+    return !fp64 && kt == 16 && bucket_cfg(kt, b).max_n > kChainMinN;
+}
+
+// The cells of 1025-1792 particles (FP32, kmax 16) run as four waves,
+// one per SIMD, with 5, 6 or 7 register-resident particles per thread
+// instead of five to seven waves of 4: every update then waits for a SIMD
+// with one of the cell's waves, not two.  On the Weibel-like batch the warm
+// EM phase took 8.1 ms with them against 10.0-10.2 ms.
+__host__ __device__ constexpr bool four_wave_bucket(int kt, bool fp64, int b)
+{
+    return kt == 16 && !fp64 && bucket_cfg(kt, b).max_n > 1024 && bucket_cfg(kt, b).max_n <= 1792;
+}
+
+// In 3V the cells of 2049-2560 and 2561-4096 particles (FP32, kmax 16) run
+// as eight waves with 5 and up to 8 register-resident particles per thread (two
+// waves per SIMD, the CU to the cell as with the 16-wave lean build): each
+// update then evaluates one density per particle instead of recomputing the
+// old one beside the new one, and a cell near 2049 particles computes 5
+// particle slots per lane, not 8.  On the Weibel-like
+// batch, where these cells hold the longest cold fits, with built-in plans:
+// judged-fallback refit 20.7-20.9 ms against 26.7-29.3 ms with the lean
+// build, headline step 30.6-31.0 ms against 35.5-38.9 ms.  The tuner may
+// still pick a lean build there.
+__host__ __device__ constexpr bool resident8_bucket(int D, int kt, bool fp64, int b)
+{
+    return D == 3 && kt == 16 && !fp64 && bucket_cfg(kt, b).max_n > 2048 && bucket_cfg(kt, b).max_n <= 4096;
+}
+
+template <int D>
+__host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
+{
+    const Bucket& c = bucket_cfg(kt, b);
+    if (resident8_bucket(D, kt, fp64, b)) return {c.max_n / (64 * 8), 8, kModeStoreE};
+    if (chain_bucket(kt, fp64, b)) {
+        // the lean builds recompute 4 or 8 particles per thread
+        const int P = c.max_n <= kEmLeanThreads * 4 ? 4 : 8;
+        return {P, (c.max_n + 64 * P - 1) / (64 * P), kModeLean};
+    }
+    if (four_wave_bucket(kt, fp64, b)) return {c.max_n / 256, 4, kModeStoreE};
+    return {c.per_thread, c.waves, c.store_e ? kModeStoreE : 0};
+}
+
 // launch-plan code of a variant: per_thread * 1000 + waves * 10 + mode
 __host__ __device__ constexpr int em_variant_code(int per_thread, int waves, int mode)
 {
