@@ -219,6 +219,9 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
         return fp64 ? gm::launch_compress_span_d3_double(kt, a, waves, hi, lo, n_cells, s)
                     : gm::launch_compress_span_d3_float(kt, a, waves, hi, lo, n_cells, s);
     };
+    auto spanned = [&](int b) {
+        return D == 1 ? gm::em_default<1>(kt, fp64, b).span : gm::em_default<3>(kt, fp64, b).span;
+    };
     // buckets of each launch width: W in (less, waves]; the 4-wave launch
     // down to the narrowest
     constexpr int kWidths = 4;
@@ -232,17 +235,18 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
         hi[w] = -1;
         lo[w] = gm::kNumBuckets;
         for (int b = 0; b < gm::kNumBuckets; ++b)
-            if (p.mode[b] == gm::kModeStoreE && p.waves[b] <= kWaves[w] && p.waves[b] > kAbove[w]) {
+            if (spanned(b) && p.waves[b] <= kWaves[w] && p.waves[b] > kAbove[w]) {
                 hi[w] = std::max(hi[w], b);
                 lo[w] = std::min(lo[w], b);
                 if (kWaves[w] > 4) heavy_mask |= 1u << b;
             }
         if (hi[w] >= 0) lane_used[kLane[w]] = true;
     }
-    constexpr int kRestLane[3] = {1, 3, 4};
+    constexpr int kMaxRest = 5;
+    constexpr int kRestLane[kMaxRest] = {1, 3, 4, 5, 6};
     for (int b = gm::kNumBuckets - 1; b >= 0; --b)
-        if (p.mode[b] != gm::kModeStoreE) {
-            if (nrest >= 3) return -1;
+        if (!spanned(b)) {
+            if (nrest >= kMaxRest) return -1;
             lane_used[kRestLane[nrest]] = true;
             rest[nrest++] = b;
             heavy_mask |= 1u << b;

@@ -379,24 +379,21 @@ struct CompState {
     R u;            // unnormalised mixing weight
 };
 
-// Reciprocal and square root for the FP32 M-step: the hardware instructions
-// (about 1 ulp); FP64 keeps the correctly rounded operations.
+// Reciprocal and reciprocal square root of the M-step: in FP32 the hardware
+// instructions (about 1 ulp).
 template <typename R>
 __device__ __forceinline__ R m_rcp(R x)
 {
-    if constexpr (std::is_same<R, float>::value)
-        return __builtin_amdgcn_rcpf(x);
-    else
-        return R(1) / x;
+    return fast_rcp(x);
 }
 
 template <typename R>
-__device__ __forceinline__ R m_sqrt(R x)
+__device__ __forceinline__ R m_rsq(R x)
 {
     if constexpr (std::is_same<R, float>::value)
-        return __builtin_amdgcn_sqrtf(x);
+        return __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(x));  // one v_rsq_f32
     else
-        return sqrt(x);
+        return rsq64(x);
 }
 
 // Cholesky factor of a packed 1x1 / 3x3 covariance and the parameters of the
@@ -414,22 +411,18 @@ __device__ __forceinline__ bool density_params(const R (&S)[ntri(D)], R u, R sdc
     // pivot turns what follows into values nobody reads
     auto bad = [](R x) { return !(x > R(0)) || !isfinite(x); };
     if constexpr (D == 1) {
-        const R l00 = m_sqrt(S[0]);
-        const R i00 = m_rcp(l00);
+        const R i00 = m_rsq(S[0]);
         Aout[0] = k * i00;
         c2 = fast_log2(u * sdc * i00);
         return !bad(S[0]);
     } else {
-        const R l00 = m_sqrt(S[0]);
-        const R i00 = m_rcp(l00);
+        const R i00 = m_rsq(S[0]);
         const R l10 = S[1] * i00, l20 = S[2] * i00;
         const R t11 = fma(-l10, l10, S[3]);
-        const R l11 = m_sqrt(t11);
-        const R i11 = m_rcp(l11);
+        const R i11 = m_rsq(t11);
         const R l21 = fma(-l20, l10, S[4]) * i11;
         const R t22 = fma(-l21, l21, fma(-l20, l20, S[5]));
-        const R l22 = m_sqrt(t22);
-        const R i22 = m_rcp(l22);
+        const R i22 = m_rsq(t22);
         // inverse of the lower factor
         const R m10 = -l10 * i00 * i11;
         const R m21 = -l21 * i11 * i22;
@@ -488,7 +481,7 @@ __device__ __forceinline__ T dpp_get(T x)
         return dpp_d<CTRL, ROW_MASK>(x);
 }
 
-// Wave sums of NV FP32 values, transposed: values are paired so that each
+// Wave sums of NV values, transposed: values are paired so that each
 // step halves the registers still to be reduced.  A lane-half swap
 // (v_permlane32_swap) of x[2i] and x[2i+1] plus one add leaves x[2i]'s sums
 // over lane pairs (l, l + 32) in lanes 0-31 and x[2i+1]'s in lanes 32-63; a
@@ -501,25 +494,38 @@ __device__ __forceinline__ T dpp_get(T x)
 // then hold it).
 constexpr int tv_row(int v) { return 2 * (v & 1) + ((v >> 1) & 1); }
 
-template <int NV>
-__device__ __forceinline__ void wave_sums_transposed(const float (&x)[NV], float (&b)[(NV + 3) / 4])
+// lane-half (32) or row (16) swap of a and b, then their sum
+template <int W>
+__device__ __forceinline__ float swap_add(float a, float b)
+{
+    const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    const auto r = W == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                           : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+template <int W>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
+    const auto l = W == 32 ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false)
+                           : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = W == 32 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
+                           : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    return __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[0] << 32) | (unsigned)l[0])) +
+           __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[1] << 32) | (unsigned)l[1]));
+}
+
+template <int NV, typename T>
+__device__ __forceinline__ void wave_sums_transposed(const T (&x)[NV], T (&b)[(NV + 3) / 4])
 {
     constexpr int NA = (NV + 1) / 2, NB = (NV + 3) / 4;
-    float a[NA];
+    T a[NA];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        const unsigned lo = __float_as_uint(x[2 * i]);
-        const unsigned hi = __float_as_uint(x[2 * i + 1 < NV ? 2 * i + 1 : 2 * i]);
-        const auto r = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
-        a[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
+    for (int i = 0; i < NA; ++i) a[i] = swap_add<32>(x[2 * i], x[2 * i + 1 < NV ? 2 * i + 1 : 2 * i]);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-        const unsigned f = __float_as_uint(a[2 * j]);
-        const unsigned g = __float_as_uint(a[2 * j + 1 < NA ? 2 * j + 1 : 2 * j]);
-        const auto r = __builtin_amdgcn_permlane16_swap(f, g, false, false);
-        b[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
+    for (int j = 0; j < NB; ++j) b[j] = swap_add<16>(a[2 * j], a[2 * j + 1 < NA ? 2 * j + 1 : 2 * j]);
 #pragma unroll
     for (int j = 0; j < NB; ++j) b[j] += dpp_get<0xB1>(b[j]);   // quad_perm [1,0,3,2]
 #pragma unroll
@@ -531,58 +537,29 @@ __device__ __forceinline__ void wave_sums_transposed(const float (&x)[NV], float
 }
 
 // Workgroup sum of the NV M-step sums of one component update, delivered to
-// every thread.  FP32: the transposed wave sums above; lane 15 of each row
-// publishes the values its row holds.  FP64: the 64-lane tree of wave_sum
-// applied to all NV values one level at a time (the independent DPP
-// operations fill each other's wait states); lane 63, where the tree ends,
-// publishes.  After one barrier lane v < NV adds value v over all MAXW
-// slots in wave order: slots of absent waves hold zeros (the buffer is
-// cleared when the kernel starts and only present waves write), so no
+// every thread: the transposed wave sums above; lane 15 of each row publishes
+// the values its row holds.  After one barrier lane v < NV adds value v over
+// all MAXW slots in wave order: slots of absent waves hold zeros (the buffer
+// is cleared when the kernel starts and only present waves write), so no
 // per-wave test is needed.
 template <int NVMAX, int MAXW, typename T, int NV>
 __device__ __forceinline__ void em_block_sum(T (&x)[NV], T* buf, int& parity, int nwaves)
 {
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
     T* bb = buf + parity * (MAXW * NVMAX);
-    constexpr bool kF32 = std::is_same<T, float>::value;
     constexpr int NB = (NV + 3) / 4;
-    [[maybe_unused]] float b[NB];
-    if constexpr (kF32) {
-        wave_sums_transposed<NV>(x, b);
-    } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] += dpp_get<0xB1>(x[v]);   // quad_perm [1,0,3,2]
-#pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x4E>(x[v]);   // quad_perm [2,3,0,1]
-#pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x141>(x[v]);  // row_half_mirror
-#pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x140>(x[v]);  // row_mirror
-#pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x142>(x[v]);  // row_bcast:15
-#pragma unroll
-        for (int v = 0; v < NV; ++v) x[v] += dpp_get<0x143>(x[v]);  // row_bcast:31
-    }
+    T b[NB];
+    wave_sums_transposed<NV>(x, b);
     if (nwaves == 1) {
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            if constexpr (kF32)
-                x[v] = lane_bcast(b[v / 4], 16 * tv_row(v) + 15);
-            else
-                x[v] = lane_bcast(x[v], 63);
-        }
+        for (int v = 0; v < NV; ++v) x[v] = lane_bcast(b[v / 4], 16 * tv_row(v) + 15);
     } else {
-        if constexpr (kF32) {
-            if ((lane & 15) == 15) {
-                const int r = lane >> 4;
-                const int off = 2 * (r & 1) + (r >> 1);  // value index within each group of four
+        if ((lane & 15) == 15) {
+            const int r = lane >> 4;
+            const int off = 2 * (r & 1) + (r >> 1);  // value index within each group of four
 #pragma unroll
-                for (int j = 0; j < NB; ++j)
-                    if (4 * j + off < NV) bb[wid * NVMAX + 4 * j + off] = b[j];
-            }
-        } else if (lane == 63) {
-#pragma unroll
-            for (int v = 0; v < NV; ++v) bb[wid * NVMAX + v] = x[v];
+            for (int j = 0; j < NB; ++j)
+                if (4 * j + off < NV) bb[wid * NVMAX + 4 * j + off] = b[j];
         }
         __syncthreads();
         T t = T(0);
@@ -2149,7 +2126,7 @@ constexpr int em_span_max_per_thread()
     int m = 0;
     for (int b = 0; b < kNumBuckets; ++b) {
         const EmDefault d = em_default<D>(KMAX, !std::is_same<R, float>::value, b);
-        if (d.mode == kModeStoreE && d.per_thread > m) m = d.per_thread;
+        if (d.span && d.per_thread > m) m = d.per_thread;
     }
     return m;
 }

@@ -265,6 +265,51 @@ __device__ __forceinline__ R tri_log2diag(const R (&L)[ntri(D)])
     }
 }
 
+// FP64 reciprocal, reciprocal square root and log2 of the EM iterations, to
+// about one unit in the last place: Newton steps on the hardware's estimates
+// (5 and 9 instructions against 12 of the correctly rounded division and 27
+// of the square root and division), and for log2 the series of atanh,
+// log2(m) = (2 / ln 2) (s + s^3/3 + s^5/5 + ...) with s = (m - 1) / (m + 1),
+// m in [sqrt(1/2), sqrt 2): |s| <= 0.172, so the eleven terms kept leave
+// 2e-18.  For finite positive arguments; log2 hands others to the library.
+__device__ __forceinline__ double rcp64(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
+__device__ __forceinline__ double rsq64(double x)
+{
+    double y = __builtin_amdgcn_rsq(x);
+    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
+__device__ __forceinline__ double log2_64(double x)
+{
+    if (!(x > 0.0 && x <= 1.7976931348623157e308)) return log2(x);
+    double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double s = (m - 1.0) * rcp64(m + 1.0);
+    const double z = s * s;
+    double q = 1.0 / 21.0;
+    q = fma(q, z, 1.0 / 19.0);
+    q = fma(q, z, 1.0 / 17.0);
+    q = fma(q, z, 1.0 / 15.0);
+    q = fma(q, z, 1.0 / 13.0);
+    q = fma(q, z, 1.0 / 11.0);
+    q = fma(q, z, 1.0 / 9.0);
+    q = fma(q, z, 1.0 / 7.0);
+    q = fma(q, z, 1.0 / 5.0);
+    q = fma(q, z, 1.0 / 3.0);
+    const double t = 2.88539008177792681472 * s;  // 2 / ln 2
+    return (double)e + fma(t * z, q, t);
+}
+
 template <typename R>
 __device__ __forceinline__ R fast_exp2(R x)
 {
@@ -281,7 +326,7 @@ __device__ __forceinline__ R fast_log2(R x)
     if constexpr (std::is_same<R, float>::value) {
         return __builtin_amdgcn_logf(x);
     } else {
-        return log2(x);
+        return log2_64(x);
     }
 }
 
@@ -291,7 +336,7 @@ __device__ __forceinline__ R fast_rcp(R x)
     if constexpr (std::is_same<R, float>::value) {
         return __builtin_amdgcn_rcpf(x);
     } else {
-        return R(1) / x;
+        return rcp64(x);
     }
 }
 

@@ -96,6 +96,7 @@ struct EmDefault {
     int per_thread;  // most particles per thread any cell of the bucket needs
     int waves;
     int mode;
+    bool span;       // in the launches that walk several buckets (k_em_span)
 };
 
 // Buckets of cells above 2048 particles (kmax 16) hold few cells, and one
@@ -143,14 +144,21 @@ template <int D>
 __host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
 {
     const Bucket& c = bucket_cfg(kt, b);
-    if (resident8_bucket(D, kt, fp64, b)) return {c.max_n / (64 * 8), 8, kModeStoreE};
+    // FP64 iterations spend most of an update on what every wave computes
+    // alike, and a particle's terms take twice the registers: two particles
+    // per thread up to 1024, four up to 2048 (more spill)
+    if (fp64 && c.max_n <= 64) return {1, 1, kModeStoreE, true};
+    if (fp64 && c.max_n <= 128) return {1, 2, kModeStoreE, true};
+    if (fp64 && c.max_n <= 1024) return {2, c.max_n / 128, kModeStoreE, true};
+    if (fp64 && c.max_n <= 2048) return {4, 8, kModeStoreE, true};
+    if (resident8_bucket(D, kt, fp64, b)) return {c.max_n / (64 * 8), 8, kModeStoreE, true};
     if (chain_bucket(kt, fp64, b)) {
         // the lean builds recompute 4 or 8 particles per thread
         const int P = c.max_n <= kEmLeanThreads * 4 ? 4 : 8;
-        return {P, (c.max_n + 64 * P - 1) / (64 * P), kModeLean};
+        return {P, (c.max_n + 64 * P - 1) / (64 * P), kModeLean, false};
     }
-    if (four_wave_bucket(kt, fp64, b)) return {c.max_n / 256, 4, kModeStoreE};
-    return {c.per_thread, c.waves, c.store_e ? kModeStoreE : 0};
+    if (four_wave_bucket(kt, fp64, b)) return {c.max_n / 256, 4, kModeStoreE, true};
+    return {c.per_thread, c.waves, c.store_e ? kModeStoreE : 0, c.store_e && !fp64};
 }
 
 // launch-plan code of a variant: per_thread * 1000 + waves * 10 + mode
