@@ -144,13 +144,16 @@ template <int D>
 __host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
 {
     const Bucket& c = bucket_cfg(kt, b);
-    // FP64 iterations spend most of an update on what every wave computes
-    // alike, and a particle's terms take twice the registers: two particles
-    // per thread up to 1024, four up to 2048 (more spill)
-    if (fp64 && c.max_n <= 64) return {1, 1, kModeStoreE, true};
-    if (fp64 && c.max_n <= 128) return {1, 2, kModeStoreE, true};
-    if (fp64 && c.max_n <= 1024) return {2, c.max_n / 128, kModeStoreE, true};
-    if (fp64 && c.max_n <= 2048) return {4, 8, kModeStoreE, true};
+    // FP64 iterations: four particles per thread in 1V (two, on twice the
+    // waves: 8.2 against 7.7 ms for 32 cells of 1000, most of an update being
+    // what every wave computes alike); two up to 1024 particles in 3V, whose
+    // four-particle build spills 196 B per lane (7.7-9.3 against 6.1-8.0 ms
+    // for 512 cells of 256 on average).  Eight spill inside the update.
+    if (fp64 && c.max_n <= 2048) {
+        const int most = D == 3 && c.max_n <= 1024 ? 2 : 4;
+        const int P = c.max_n <= 64 * most ? c.max_n / 64 : most;
+        return {P, D == 3 && c.max_n > 1024 ? 8 : (c.max_n + 64 * P - 1) / (64 * P), kModeStoreE, true};
+    }
     if (resident8_bucket(D, kt, fp64, b)) return {c.max_n / (64 * 8), 8, kModeStoreE, true};
     if (chain_bucket(kt, fp64, b)) {
         // the lean builds recompute 4 or 8 particles per thread
@@ -160,6 +163,24 @@ __host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
     if (four_wave_bucket(kt, fp64, b)) return {c.max_n / 256, 4, kModeStoreE, true};
     return {c.per_thread, c.waves, c.store_e ? kModeStoreE : 0, c.store_e && !fp64};
 }
+
+// k_em_span's workgroups only narrow on their way down the buckets
+template <int D>
+constexpr bool em_spans_narrow(int kt, bool fp64)
+{
+    int w = 0;
+    for (int b = 0; b < kNumBuckets; ++b) {
+        const EmDefault d = em_default<D>(kt, fp64, b);
+        if (!d.span) continue;
+        if (d.waves < w || d.waves > em_max_waves(false)) return false;
+        w = d.waves;
+    }
+    return true;
+}
+static_assert(em_spans_narrow<1>(8, false) && em_spans_narrow<1>(16, false) && em_spans_narrow<1>(8, true) &&
+                  em_spans_narrow<1>(16, true) && em_spans_narrow<3>(8, false) && em_spans_narrow<3>(16, false) &&
+                  em_spans_narrow<3>(8, true) && em_spans_narrow<3>(16, true),
+              "a bucket of larger cells runs on fewer waves");
 
 // launch-plan code of a variant: per_thread * 1000 + waves * 10 + mode
 __host__ __device__ constexpr int em_variant_code(int per_thread, int waves, int mode)
