@@ -472,70 +472,6 @@ constexpr int kResumSweeps = 4;
 template <typename R>
 constexpr double kBigFinite = std::is_same<R, float>::value ? 3.4028234663852886e38 : 1.7976931348623157e308;
 
-template <int CTRL, int ROW_MASK = 0xf, typename T>
-__device__ __forceinline__ T dpp_get(T x)
-{
-    if constexpr (std::is_same<T, float>::value)
-        return __int_as_float(dpp_i<CTRL, ROW_MASK>(__float_as_int(x)));
-    else
-        return dpp_d<CTRL, ROW_MASK>(x);
-}
-
-// Wave sums of NV values, transposed: values are paired so that each
-// step halves the registers still to be reduced.  A lane-half swap
-// (v_permlane32_swap) of x[2i] and x[2i+1] plus one add leaves x[2i]'s sums
-// over lane pairs (l, l + 32) in lanes 0-31 and x[2i+1]'s in lanes 32-63; a
-// row swap (v_permlane16_swap) of two such registers plus one add leaves
-// four values' 4-lane partial sums, one per 16-lane row; four in-row DPP
-// levels then give every lane its row's total.  Value v ends in register
-// v / 4, in row tv_row(v): about 28 VALU instructions for ten values
-// against 60 for ten separate 64-lane trees.
-// An unpaired last value is swapped with itself (both halves, or both rows,
-// then hold it).
-constexpr int tv_row(int v) { return 2 * (v & 1) + ((v >> 1) & 1); }
-
-// lane-half (32) or row (16) swap of a and b, then their sum
-template <int W>
-__device__ __forceinline__ float swap_add(float a, float b)
-{
-    const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
-    const auto r = W == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
-                           : __builtin_amdgcn_permlane16_swap(x, y, false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-template <int W>
-__device__ __forceinline__ double swap_add(double a, double b)
-{
-    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
-    const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
-    const auto l = W == 32 ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false)
-                           : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
-    const auto h = W == 32 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
-                           : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
-    return __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[0] << 32) | (unsigned)l[0])) +
-           __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[1] << 32) | (unsigned)l[1]));
-}
-
-template <int NV, typename T>
-__device__ __forceinline__ void wave_sums_transposed(const T (&x)[NV], T (&b)[(NV + 3) / 4])
-{
-    constexpr int NA = (NV + 1) / 2, NB = (NV + 3) / 4;
-    T a[NA];
-#pragma unroll
-    for (int i = 0; i < NA; ++i) a[i] = swap_add<32>(x[2 * i], x[2 * i + 1 < NV ? 2 * i + 1 : 2 * i]);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] = swap_add<16>(a[2 * j], a[2 * j + 1 < NA ? 2 * j + 1 : 2 * j]);
-#pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0xB1>(b[j]);   // quad_perm [1,0,3,2]
-#pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x4E>(b[j]);   // quad_perm [2,3,0,1]
-#pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x141>(b[j]);  // row_half_mirror
-#pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x140>(b[j]);  // row_mirror
-}
-
 // Workgroup sum of the NV M-step sums of one component update, delivered to
 // every thread: the transposed wave sums above; lane 15 of each row publishes
 // the values its row holds.  After one barrier lane v < NV adds value v over

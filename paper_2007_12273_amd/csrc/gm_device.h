@@ -117,6 +117,70 @@ __device__ __forceinline__ double wave_sum(double x)
     return __longlong_as_double((int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
 }
 
+template <int CTRL, int ROW_MASK = 0xf, typename T>
+__device__ __forceinline__ T dpp_get(T x)
+{
+    if constexpr (std::is_same<T, float>::value)
+        return __int_as_float(dpp_i<CTRL, ROW_MASK>(__float_as_int(x)));
+    else
+        return dpp_d<CTRL, ROW_MASK>(x);
+}
+
+// Wave sums of NV values, transposed: values are paired so that each
+// step halves the registers still to be reduced.  A lane-half swap
+// (v_permlane32_swap) of x[2i] and x[2i+1] plus one add leaves x[2i]'s sums
+// over lane pairs (l, l + 32) in lanes 0-31 and x[2i+1]'s in lanes 32-63; a
+// row swap (v_permlane16_swap) of two such registers plus one add leaves
+// four values' 4-lane partial sums, one per 16-lane row; four in-row DPP
+// levels then give every lane its row's total.  Value v ends in register
+// v / 4, in row tv_row(v): about 28 VALU instructions for ten values
+// against 60 for ten separate 64-lane trees.
+// An unpaired last value is swapped with itself (both halves, or both rows,
+// then hold it).
+constexpr int tv_row(int v) { return 2 * (v & 1) + ((v >> 1) & 1); }
+
+// lane-half (32) or row (16) swap of a and b, then their sum
+template <int W>
+__device__ __forceinline__ float swap_add(float a, float b)
+{
+    const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    const auto r = W == 32 ? __builtin_amdgcn_permlane32_swap(x, y, false, false)
+                           : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+template <int W>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
+    const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
+    const auto l = W == 32 ? __builtin_amdgcn_permlane32_swap(xl, yl, false, false)
+                           : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
+    const auto h = W == 32 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
+                           : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
+    return __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[0] << 32) | (unsigned)l[0])) +
+           __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[1] << 32) | (unsigned)l[1]));
+}
+
+template <int NV, typename T>
+__device__ __forceinline__ void wave_sums_transposed(const T (&x)[NV], T (&b)[(NV + 3) / 4])
+{
+    constexpr int NA = (NV + 1) / 2, NB = (NV + 3) / 4;
+    T a[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] = swap_add<32>(x[2 * i], x[2 * i + 1 < NV ? 2 * i + 1 : 2 * i]);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] = swap_add<16>(a[2 * j], a[2 * j + 1 < NA ? 2 * j + 1 : 2 * j]);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0xB1>(b[j]);   // quad_perm [1,0,3,2]
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x4E>(b[j]);   // quad_perm [2,3,0,1]
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x141>(b[j]);  // row_half_mirror
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x140>(b[j]);  // row_mirror
+}
+
 // Workgroup-wide sum of NV values; every thread receives the totals.  Lane
 // 0 of every wave publishes its wave's sums; after one barrier lane v < NV
 // adds the per-wave partials of value v in wave order (MAXW bounds the wave
@@ -138,6 +202,16 @@ __device__ __forceinline__ double lane_bcast(double x, int lane)
     const int lo = __builtin_amdgcn_readlane((int)(uint32_t)b, lane);
     const int hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
     return __longlong_as_double((int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo));
+}
+
+// the wave's NV sums in every lane, by the transposed reduction
+template <int NV, typename T>
+__device__ __forceinline__ void wave_sums(T (&x)[NV])
+{
+    T b[(NV + 3) / 4];
+    wave_sums_transposed<NV>(x, b);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) x[v] = lane_bcast(b[v / 4], 16 * tv_row(v) + 15);
 }
 
 template <int NVMAX, int MAXW = kMaxWaves, typename T, int NV>
@@ -308,6 +382,78 @@ __device__ __forceinline__ double log2_64(double x)
     q = fma(q, z, 1.0 / 3.0);
     const double t = 2.88539008177792681472 * s;  // 2 / ln 2
     return (double)e + fma(t * z, q, t);
+}
+
+// The Box-Muller functions of the sampling, each to within one unit in the
+// last place, without the library's argument cases:
+//   log_64       x in (0, 1]: the same series in natural units, the quotient
+//                s corrected by its own remainder, ln 2 in two parts
+//   sqrt_64      x >= 0: rsq64 and one correction by the remainder
+//   sincospi_64  sin and cos of pi a, a in [0, 2): a = q/2 + f exactly, |f| <=
+//                1/4, and the Taylor series of both about 0 (nine terms leave
+//                1e-19 and 2e-18), pi in two parts
+__device__ __forceinline__ double log_64(double x)
+{
+    double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
+    int e = __builtin_amdgcn_frexp_exp(x);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    e = low ? e - 1 : e;
+    const double n = m - 1.0, d = m + 1.0, r = rcp64(d);
+    double s = n * r;
+    s = fma(r, fma(-s, d, n), s);
+    const double z = s * s;
+    double q = 1.0 / 21.0;
+    q = fma(q, z, 1.0 / 19.0);
+    q = fma(q, z, 1.0 / 17.0);
+    q = fma(q, z, 1.0 / 15.0);
+    q = fma(q, z, 1.0 / 13.0);
+    q = fma(q, z, 1.0 / 11.0);
+    q = fma(q, z, 1.0 / 9.0);
+    q = fma(q, z, 1.0 / 7.0);
+    q = fma(q, z, 1.0 / 5.0);
+    q = fma(q, z, 1.0 / 3.0);
+    const double t = s + s;
+    const double small = fma(t * z, q, (double)e * 2.31904681384629955842e-17);
+    return fma((double)e, 0.693147180559945286227, t + small);
+}
+
+__device__ __forceinline__ double sqrt_64(double x)
+{
+    const double y = rsq64(x);
+    const double g = x * y;
+    return x > 0.0 ? fma(0.5 * y, fma(-g, g, x), g) : 0.0;
+}
+
+__device__ __forceinline__ void sincospi_64(double a, double& sn, double& cs)
+{
+    const double h = __builtin_rint(a + a);
+    const int q = (int)h;
+    const double f = fma(-0.5, h, a);
+    const double z = f * f;
+    double p = 7.95205400147551261113e-07;
+    p = fma(p, z, -2.19153534478302172922e-05);
+    p = fma(p, z, 4.66302805767612553716e-04);
+    p = fma(p, z, -7.37043094571435044443e-03);
+    p = fma(p, z, 8.21458866111282326461e-02);
+    p = fma(p, z, -5.99264529320792105338e-01);
+    p = fma(p, z, 2.55016403987734552317e+00);
+    p = fma(p, z, -5.16771278004997025590e+00);
+    p = fma(p, z, 1.22464679914735320717e-16);
+    const double s0 = fma(f, p, f * 3.14159265358979311600);
+    double c = 4.30306958703294729370e-06;
+    c = fma(c, z, -1.04638104924845704697e-04);
+    c = fma(c, z, 1.92957430940392314460e-03);
+    c = fma(c, z, -2.58068913900140611828e-02);
+    c = fma(c, z, 2.35330630358893205800e-01);
+    c = fma(c, z, -1.33526276885458949906e+00);
+    c = fma(c, z, 4.05871212641676848421e+00);
+    c = fma(c, z, -4.93480220054467899615e+00);
+    const double c0 = fma(c, z, 1.0);
+    const bool odd = (q & 1) != 0;
+    const double u = odd ? c0 : s0, w = odd ? s0 : c0;
+    sn = (q & 2) ? -u : u;
+    cs = ((q + 1) & 2) ? -w : w;
 }
 
 template <typename R>

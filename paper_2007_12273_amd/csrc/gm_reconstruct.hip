@@ -24,12 +24,12 @@ constexpr int kReconThreads = 256;
 // counter (i, c, j / 4, 0) and key (seed, "RECO").  Uniform 0 picks the
 // component, the next ceil(D/2) pairs feed Box-Muller, the rest are positions.
 template <int D>
-__device__ __forceinline__ void draw_particle(uint64_t seed, int c, int64_t i, int K, const double* cum,
+__device__ __forceinline__ void draw_particle(uint64_t seed, int c, uint64_t i, int K, const double* cum,
                                               const double (*mu)[D], const double (*L)[ntri(D)], int dx,
                                               double (&v)[D], double (&xpos)[3])
 {
     constexpr int NPAIR = (D + 1) / 2;
-    const u64x4 b0 = philox4x64_10((uint64_t)i, (uint64_t)c, 0, 0, seed, kTagRecon);
+    const u64x4 b0 = philox4x64_10(i, (uint64_t)c, 0, 0, seed, kTagRecon);
     double u[8];
     u[0] = unit53(b0.x);
     u[1] = unit53(b0.y);
@@ -37,24 +37,28 @@ __device__ __forceinline__ void draw_particle(uint64_t seed, int c, int64_t i, i
     u[3] = unit53(b0.w);
     const int nu = 1 + 2 * NPAIR + dx;
     if (nu > 4) {
-        const u64x4 b1 = philox4x64_10((uint64_t)i, (uint64_t)c, 1, 0, seed, kTagRecon);
+        const u64x4 b1 = philox4x64_10(i, (uint64_t)c, 1, 0, seed, kTagRecon);
         u[4] = unit53(b1.x);
         u[5] = unit53(b1.y);
         u[6] = unit53(b1.z);
         u[7] = unit53(b1.w);
     }
-    // component by inverse CDF over the cumulative weights
+    // component by inverse CDF over the cumulative weights: the first k < K - 1
+    // with u0 < cum[k], else K - 1
     int k = 0;
-    while (k < K - 1 && !(u[0] < cum[k])) ++k;
+    bool past = true;
+    for (int j = 0; j < K - 1; ++j) {
+        past = past && !(u[0] < cum[j]);
+        k += past ? 1 : 0;
+    }
     // Box-Muller pairs
     double z[2 * NPAIR];
 #pragma unroll
     for (int pr = 0; pr < NPAIR; ++pr) {
-        const double r = sqrt(-2.0 * log(1.0 - u[1 + 2 * pr]));
-        // angle 2 pi u: sincospi(2u) takes the exact argument 2u (no
-        // reduction by a rounded pi)
+        const double r = sqrt_64(-2.0 * log_64(1.0 - u[1 + 2 * pr]));
+        // angle 2 pi u: the exact argument 2u (no reduction by a rounded pi)
         double sn, cs;
-        sincospi(2.0 * u[2 + 2 * pr], &sn, &cs);
+        sincospi_64(2.0 * u[2 + 2 * pr], sn, cs);
         z[2 * pr] = r * cs;
         z[2 * pr + 1] = r * sn;
     }
@@ -257,7 +261,7 @@ __device__ __forceinline__ void recon_cell(const ReconArgs& A, int c, int64_t o0
         }
     };
     const int kmax = A.kmax;
-    const int K = A.K[c];
+    const int K = __builtin_amdgcn_readfirstlane(A.K[c]);
     const int dx = A.dx;
     if (K < 1 || K > kmax) {
         for (int64_t i = t; i < n; i += G) {
@@ -301,7 +305,7 @@ __device__ __forceinline__ void recon_cell(const ReconArgs& A, int c, int64_t o0
     // sample's sums
     for (int64_t i = t; i < n; i += G) {
         double v[D], xp[3];
-        draw_particle<D>(A.seed, c, i, K, s_cum, s_mu, s_L, dx, v, xp);
+        draw_particle<D>(A.seed, c, WAVE ? (uint64_t)(uint32_t)i : (uint64_t)i, K, s_cum, s_mu, s_L, dx, v, xp);
 #pragma unroll
         for (int d = 0; d < D; ++d) A.v_out[(o0 + i) * D + d] = v[d];
         A.w_out[o0 + i] = wp;
@@ -311,8 +315,7 @@ __device__ __forceinline__ void recon_cell(const ReconArgs& A, int c, int64_t o0
         sums.add(v, wp);
     }
     if constexpr (WAVE) {
-#pragma unroll
-        for (int q = 0; q < Sums::NA; ++q) sums.acc[q] = wave_sum(sums.acc[q]);
+        wave_sums(sums.acc);
     } else {
         block_sum<Sums::NA>(sums.acc, red, par, G >> 6);
     }
@@ -343,7 +346,7 @@ __global__ __launch_bounds__(kReconThreads) void k_reconstruct(ReconArgs A, int6
     __shared__ double red[2 * kMaxWaves * Sums::NA];
     __shared__ int s_bad[NW];
     const int tid = threadIdx.x;
-    const int wid = tid >> 6, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     int par = 0;
     const int64_t cb = (int64_t)blockIdx.x * NW;
     {
