@@ -573,10 +573,11 @@ int gm_deposit(const double* x, const double* w, const int64_t* cell_off, int64_
  * (each particle puts at least half its spline on its own cell, more unless
  * it sits on the cell's edge) and nonsingular; in 2D it is not dominant but
  * nonsingular for generic positions.  The iteration's scalars stay on the
- * device; the call reads them back once per 8 iterations and per restart,
- * so it synchronises `stream` and cannot be captured in a graph; the empty
- * cell check and GM_ENOCONV come from those reads, after kernels on the
- * workspace were enqueued.  iters_out (iterations) and resid_out (final
+ * device; the call reads them back once (meshes of up to about 131072 cells,
+ * with nx <= 512 in 2D, solved in one launch) or, on other meshes, once per
+ * 8 iterations and per restart, so it synchronises `stream` and cannot be
+ * captured in a graph; the empty cell check and GM_ENOCONV come from those
+ * reads, after kernels on the workspace were enqueued.  iters_out (iterations) and resid_out (final
  * true relative residual) are host pointers, may be NULL.  Returns
  * GM_ENOCONV, with the weights corrected by the last iterate, when the
  * tolerance was not reached. */

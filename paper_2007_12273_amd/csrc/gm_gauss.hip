@@ -21,7 +21,9 @@
 //               vector kernel returns at once when the flag is set, so the
 //               host enqueues iterations in chunks and reads the state once
 //               per chunk.  A restart recomputes the true residual b - M dA,
-//               which alone decides convergence (below tol |b|).
+//               which alone decides convergence (below tol |b|).  Meshes
+//               of up to 131072 cells run the whole solve in one launch
+//               (k_solve).
 //   k_apply_dA  w_p += dA_{cell(p)} (eq. new-p-weight)
 #include <cmath>
 
@@ -48,12 +50,14 @@ template <int DX>
 constexpr int kCentre = DX == 1 ? 1 : 4;
 
 // one wave per cell (kStencilThreads / 64 cells per workgroup): lanes stride
-// over the cell's particles, then a wave-wide DPP sum per slot (fixed order)
+// over the cell's particles, then wave-wide sums of the slots (fixed order)
 template <int DX>
 __global__ __launch_bounds__(kStencilThreads) void k_stencil(const double* x, const double* w, const int64_t* off,
-                                                             int64_t n_cells, double* colM, double* colW)
+                                                             int64_t n_cells, double* colM, double* colW,
+                                                             unsigned long long* tag, int ntag)
 {
     constexpr int NS = kSlots<DX>;
+    if (blockIdx.x == 0 && (int)threadIdx.x < ntag) tag[threadIdx.x] = 0;  // k_solve's tags
     const int lane = threadIdx.x & 63;
     const int64_t c = (int64_t)blockIdx.x * (kStencilThreads / 64) + (threadIdx.x >> 6);
     if (c >= n_cells) return;  // whole waves leave; no workgroup barrier follows
@@ -81,16 +85,23 @@ __global__ __launch_bounds__(kStencilThreads) void k_stencil(const double* x, co
                 acc[NS + oy * 3 + ox] += wp * s;
             }
     }
+    // value v of the transposed sums ends in register v / 4 of every lane of
+    // its row; the row's last lane stores it
+    constexpr int NB = (2 * NS + 3) / 4;
+    double b[NB];
+    wave_sums_transposed<2 * NS>(acc, b);
+    if ((lane & 15) == 15) {
+        const int r = lane >> 4, first = 2 * (r & 1) + (r >> 1);
 #pragma unroll
-    for (int t = 0; t < 2 * NS; ++t) acc[t] = wave_sum(acc[t]);
-    // every lane holds the totals; lane t stores slot t (static indices keep
-    // acc in registers)
-#pragma unroll
-    for (int t = 0; t < NS; ++t)
-        if (lane == t) {
-            if (colM) colM[c * NS + t] = acc[t];
-            colW[c * NS + t] = acc[NS + t];
+        for (int j = 0; j < NB; ++j) {
+            const int v = 4 * j + first;
+            if (v < NS) {
+                if (colM) colM[c * NS + v] = b[j];
+            } else if (v < 2 * NS) {
+                colW[c * NS + v - NS] = b[j];
+            }
         }
+    }
 }
 
 // sum over the stencil slots o of col[j(i, o)][o] * f(j), j = the cell whose
@@ -324,8 +335,347 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(const double* st, con
     store_partials(q0, q1, partial);
 }
 
-__global__ void k_apply_dA(double* w, const int64_t* off, const double* dA)
+// ---------------------------------------------------------------------------
+// The whole solve in one launch, for meshes whose rows fit a workgroup.
+//
+// Workgroup g owns a block of whole rows (dx = 2) or of cells (dx = 1), up to
+// kSolveOwn cells, two per thread; a thread keeps its cells' mass-matrix rows
+// and vectors in registers and the workgroup the scaled vector it multiplies
+// in LDS, with one row (one cell) of halo on either side.  An iteration needs
+// two exchanges: after v = M dinv p the workgroups publish v and their part
+// of rh.v, after t = M dinv s they publish t and their parts of t.s, t.t,
+// rh.s, rh.t and s.s; omega, the new rho = rh.s - omega rh.t and the new |r|^2
+// = s.s - 2 omega t.s + omega^2 t.t follow from those, and every workgroup
+// updates p, r and s of its halo itself from the neighbours' v and t.  The
+// restarts from the true residual b - M dA, which alone decides convergence,
+// run inside as well.  Launched one kernel per step the solve was bound by
+// its eight launches and a host round trip per eight iterations: 23 us an
+// iteration.  Solve on the 65536-cell grid (64 workgroups, 27 iterations)
+// 0.26 ms against 0.74 ms and four host round trips, on 4096 cells in 1D (4
+// workgroups) 0.09 ms against 0.36 ms; what is left is the two exchanges.
+//
+// An exchange: each workgroup stores its halo-visible values and partial
+// sums, then, once they are out, a tag with the exchange's number; every
+// workgroup waits for all tags and adds the partials in workgroup order, so
+// all take the same decisions.  Buffers alternate by the parity of the
+// exchange: a workgroup two exchanges ahead would need every tag of the one
+// between.  The grid (at most kSolveMaxGroups workgroups, one per CU) is
+// resident as a whole; should it ever not be, the waits are bounded and every
+// workgroup leaves.  A solve that did not converge here, for that or for
+// numerical reasons, leaves the weights alone, and the host then takes the
+// launch-per-step path, whose recurrences cancel less.
+// ---------------------------------------------------------------------------
+constexpr int kSolveThreads = 512;
+constexpr int kSolveOwn = 2 * kSolveThreads;   // cells a workgroup owns
+constexpr int kSolveHalo = kSolveThreads;      // cells of one halo row
+constexpr int kSolveMaxGroups = 128;
+constexpr int kSolvePart = 8;                  // doubles per workgroup and exchange
+constexpr int kSolveSpin = 1 << 20;            // polls (each with a sleep) before a wait gives up
+
+struct SolveArgs {
+    const double* colM;
+    const double* colW;
+    const double* target;
+    const int64_t* off;
+    int64_t n;
+    int nx, ny;
+    int per;              // rows (dx = 2) or cells (dx = 1) per workgroup
+    double tol;
+    int max_iter, max_restarts;
+    double* x;            // [n] the corrections dA
+    double* halo[2];      // [n] v or t (or dA, r at a restart), alternating
+    double* part;         // [2][groups][kSolvePart]
+    unsigned long long* tag;  // [2][groups], zero at the start
+    double* st;
+};
+
+__device__ __forceinline__ void agent_store(double* p, double v)
 {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double agent_load(const double* p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits until this wave's stores have reached the point of coherence.  All
+// that the workgroups share goes through agent-scope atomics, which pass the
+// XCD's L2 by; a release fence would write the L2's other lines back as well,
+// in every wave and exchange (18 us per exchange of 64 workgroups against 4.5).
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+template <int DX>
+__global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
+{
+    constexpr int NS = kSlots<DX>;
+    constexpr int NC = 2;                       // own cells per thread, and halo cells per thread
+    __shared__ double vec[kSolveOwn + 2 * kSolveHalo];
+    __shared__ double red[kSolveThreads / 64][kSolvePart];
+    __shared__ double tot[kSolvePart];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int G = gridDim.x, g = blockIdx.x;
+    const int H = DX == 1 ? 1 : A.nx;           // cells of one halo row
+    const int64_t c0 = (int64_t)g * A.per * (DX == 1 ? 1 : A.nx);
+    const int64_t c1 = c0 + (int64_t)A.per * (DX == 1 ? 1 : A.nx) < A.n ? c0 + (int64_t)A.per * (DX == 1 ? 1 : A.nx) : A.n;
+    const int own = (int)(c1 - c0);
+
+    // local layout of `vec`: [0, H) the row before, [H, H + own) own, then the row after
+    int64_t gi[NC], hi[NC];                     // global indices of own and halo cells
+    int li[NC], lh[NC], nb[NC][NS];             // their places in vec; the stencil's places
+    double m[NC][NS], dinv[NC], hdinv[NC], b[NC];
+    double x[NC], p[NC], r[NC], rh[NC], v[NC], sv[NC], t[NC];
+    double hp[NC], hr[NC], hv[NC], hs[NC];
+    auto column = [&](int64_t j, int o) { return A.colM[j * NS + o]; };
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        const int q = tid + k * kSolveThreads;
+        const bool in = q < own;
+        gi[k] = in ? c0 + q : -1;
+        li[k] = H + q;
+        dinv[k] = b[k] = x[k] = p[k] = r[k] = rh[k] = v[k] = sv[k] = t[k] = 0.0;
+#pragma unroll
+        for (int o = 0; o < NS; ++o) {
+            m[k][o] = 0.0;
+            nb[k][o] = 0;
+        }
+        if (in) {
+            const int64_t i = gi[k];
+            const bool empty = A.off[i + 1] <= A.off[i];
+            dinv[k] = empty ? 0.0 : 1.0 / column(i, kCentre<DX>);
+            b[k] = A.target[i] - gather<DX>(A.colW, i, A.n, A.nx, A.ny, [](int64_t) { return 1.0; });
+            if constexpr (DX == 1) {
+#pragma unroll
+                for (int o = 0; o < 3; ++o) {
+                    int64_t j = i - (o - 1);
+                    j = j < 0 ? j + A.n : (j >= A.n ? j - A.n : j);
+                    m[k][o] = column(j, o);
+                    nb[k][o] = li[k] - (o - 1);
+                }
+            } else {
+                const int ix = (int)(i % A.nx), iy = (int)(i / A.nx);
+#pragma unroll
+                for (int oy = 0; oy < 3; ++oy) {
+                    int jy = iy - (oy - 1);
+                    jy = jy < 0 ? jy + A.ny : (jy >= A.ny ? jy - A.ny : jy);
+#pragma unroll
+                    for (int ox = 0; ox < 3; ++ox) {
+                        int jx = ix - (ox - 1);
+                        jx = jx < 0 ? jx + A.nx : (jx >= A.nx ? jx - A.nx : jx);
+                        m[k][oy * 3 + ox] = column((int64_t)jy * A.nx + jx, oy * 3 + ox);
+                        nb[k][oy * 3 + ox] = li[k] - ix - (oy - 1) * A.nx + jx;
+                    }
+                }
+            }
+        }
+        // halo cell q of 2 H: the row before the first own one, then the row after the last
+        const bool hin = q < 2 * H;
+        const int64_t j = q < H ? c0 - H + q : c1 + (q - H);
+        hi[k] = hin ? (j < 0 ? j + A.n : (j >= A.n ? j - A.n : j)) : -1;
+        lh[k] = q < H ? q : own + q;            // own + H + (q - H)
+        hdinv[k] = hp[k] = hr[k] = hv[k] = hs[k] = 0.0;
+        if (hin) hdinv[k] = A.off[hi[k] + 1] <= A.off[hi[k]] ? 0.0 : 1.0 / column(hi[k], kCentre<DX>);
+    }
+
+    unsigned long long epoch = 0;
+    // publish val of the own cells, add up q over the grid (into tot), and
+    // return the neighbours' val on the halo; false when a wait gave up
+    auto exchange = [&](const double (&val)[NC], const double (&q)[5], double (&hval)[NC]) -> bool {
+        ++epoch;
+        const int par = (int)(epoch & 1);
+        double* halo = A.halo[par];
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            if (gi[k] >= 0) agent_store(halo + gi[k], val[k]);
+        double w[5];
+#pragma unroll
+        for (int u = 0; u < 5; ++u) w[u] = q[u];
+        wave_sums(w);
+        if (lane == 0)
+#pragma unroll
+            for (int u = 0; u < 5; ++u) red[wid][u] = w[u];
+        stores_done();  // this wave's part is out before the tag below
+        __syncthreads();
+        double* part = A.part + (size_t)par * G * kSolvePart;
+        if (tid < 5) {
+            double a = 0.0;
+#pragma unroll
+            for (int u = 0; u < kSolveThreads / 64; ++u) a += red[u][tid];
+            agent_store(part + (size_t)g * kSolvePart + tid, a);
+        }
+        if (wid == 0) {
+            stores_done();
+            if (lane == 0)
+                __hip_atomic_store(A.tag + (size_t)par * G + g, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        // lane l of wave w waits for workgroup 64 w + l
+        bool ok = true;
+        if (tid < G) {
+            ok = false;
+            for (int spin = 0; spin < kSolveSpin; ++spin) {
+                if (__hip_atomic_load(A.tag + (size_t)par * G + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                    epoch) {
+                    ok = true;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        const bool all = __syncthreads_and(ok);
+        if (!all) return false;
+        if (wid < 5) {
+            // value wid over the workgroups: a lane adds its two, then the wave
+            double a = 0.0;
+            if (lane < G) a = agent_load(part + (size_t)lane * kSolvePart + wid);
+            if (lane + 64 < G) a += agent_load(part + (size_t)(lane + 64) * kSolvePart + wid);
+            a = wave_sum(a);
+            if (lane == 0) tot[wid] = a;
+        }
+#pragma unroll
+        for (int k = 0; k < NC; ++k) hval[k] = hi[k] >= 0 ? agent_load(halo + hi[k]) : 0.0;
+        __syncthreads();
+        return true;
+    };
+    // y = M a over the own cells, a given on own and halo cells
+    auto product = [&](const double (&a)[NC], const double (&ha)[NC], double (&y)[NC]) {
+        __syncthreads();  // the last product's reads are done
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            if (gi[k] >= 0) vec[li[k]] = a[k];
+            if (hi[k] >= 0) vec[lh[k]] = ha[k];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            double acc = 0.0;
+#pragma unroll
+            for (int o = 0; o < NS; ++o) acc += m[k][o] * vec[nb[k][o]];
+            y[k] = gi[k] >= 0 ? acc : 0.0;
+        }
+    };
+
+    double hx[NC], q[5], a_[NC], ha_[NC];
+    auto zero5 = [&]() {
+#pragma unroll
+        for (int u = 0; u < 5; ++u) q[u] = 0.0;
+    };
+    int done = 0, iters = 0;
+    double b2 = 0.0, r2 = 0.0, true_r2 = 0.0, empty = 0.0;
+    // b.b and the number of empty cells
+    zero5();
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        q[0] += b[k] * b[k];
+        if (gi[k] >= 0 && A.off[gi[k] + 1] <= A.off[gi[k]]) q[1] += 1.0;
+    }
+    bool ok = exchange(x, q, hx);
+    if (ok) {
+        b2 = true_r2 = tot[0];
+        empty = tot[1];
+    }
+    const double tol2b2 = A.tol * A.tol * b2;
+    if (empty != 0.0 || b2 == 0.0) done = 1;
+    for (int rs = 0; ok && done == 0 && rs <= A.max_restarts; ++rs) {
+        // the true residual of the current dA (zero at first), and r on the halo
+        product(x, hx, a_);
+        double rho = 0.0, alpha = 1.0, omega = 1.0, beta = 0.0;
+        zero5();
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+            r[k] = rh[k] = b[k] - a_[k];
+            p[k] = v[k] = 0.0;
+            hp[k] = hv[k] = 0.0;
+            q[0] += r[k] * r[k];
+        }
+        ok = exchange(r, q, hr);
+        if (!ok) break;
+        r2 = true_r2 = rho = tot[0];
+        if (r2 <= tol2b2) {
+            done = 1;
+            break;
+        }
+        if (!isfinite(r2) || iters >= A.max_iter) {
+            done = 2;
+            break;
+        }
+        bool stop = false;
+        while (!stop && iters < A.max_iter) {
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                p[k] = r[k] + beta * (p[k] - omega * v[k]);
+                hp[k] = hr[k] + beta * (hp[k] - omega * hv[k]);
+                a_[k] = dinv[k] * p[k];
+                ha_[k] = hdinv[k] * hp[k];
+            }
+            product(a_, ha_, v);
+            zero5();
+#pragma unroll
+            for (int k = 0; k < NC; ++k) q[0] += rh[k] * v[k];
+            ok = exchange(v, q, hv);
+            if (!ok) break;
+            const double rv = tot[0];
+            if (rv == 0.0 || !isfinite(rv)) break;  // breakdown: restart
+            alpha = rho / rv;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                sv[k] = r[k] - alpha * v[k];
+                hs[k] = hr[k] - alpha * hv[k];
+                a_[k] = dinv[k] * sv[k];
+                ha_[k] = hdinv[k] * hs[k];
+            }
+            product(a_, ha_, t);
+            zero5();
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                q[0] += t[k] * sv[k];
+                q[1] += t[k] * t[k];
+                q[2] += rh[k] * sv[k];
+                q[3] += rh[k] * t[k];
+                q[4] += sv[k] * sv[k];
+            }
+            double ht[NC];
+            ok = exchange(t, q, ht);
+            if (!ok) break;
+            const double ts = tot[0], tt = tot[1], rhs = tot[2], rht = tot[3], ss = tot[4];
+            omega = tt > 0.0 ? ts / tt : 0.0;
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                x[k] += dinv[k] * (alpha * p[k] + omega * sv[k]);
+                r[k] = sv[k] - omega * t[k];
+                hr[k] = hs[k] - omega * ht[k];
+            }
+            ++iters;
+            r2 = ss - omega * (2.0 * ts - omega * tt);
+            const double rho1 = rhs - omega * rht;
+            // converged by the recurrence (or below its rounding): checked
+            // against the true residual
+            if (r2 <= tol2b2) stop = true;
+            else if (omega == 0.0 || rho1 == 0.0 || !isfinite(r2) || !isfinite(rho1)) stop = true;
+            else {
+                beta = (rho1 / rho) * (alpha / omega);
+                rho = rho1;
+            }
+        }
+        if (!ok) break;
+        // dA on the halo for the next true residual
+        zero5();
+        ok = exchange(x, q, hx);
+    }
+#pragma unroll
+    for (int k = 0; k < NC; ++k)
+        if (gi[k] >= 0) A.x[gi[k]] = x[k];
+    if (g == 0 && tid == 0) {
+        A.st[S_TOL2B2] = b2;  // the host divides by b.b
+        A.st[S_R2] = true_r2;
+        A.st[S_EMPTY] = empty;
+        A.st[S_ITERS] = (double)iters;
+        A.st[S_DONE] = ok && done == 1 ? 1.0 : 2.0;
+    }
+}
+
+// w_p += dA of its cell; nothing when st says that the solve did not converge
+__global__ void k_apply_dA(double* w, const int64_t* off, const double* dA, const double* st)
+{
+    if (st && (st[S_EMPTY] != 0.0 || st[S_DONE] != 1.0)) return;
     const int c = blockIdx.x;
     const int64_t o0 = off[c], n = off[c + 1] - o0;
     const double d = dA[c];
@@ -408,8 +758,46 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
     auto fold = [&](int mode) {
         hipLaunchKernelGGL(k_fold, dim3(1), vb, 0, st, g.partial, (int)nb, g.st, mode, tol);
     };
+    // The one-launch solve: rows that fit a workgroup with their halo, and a
+    // mesh that a resident grid covers (131072 cells; at 65536, half of that,
+    // it takes a third of the other path's time, and at one workgroup a quarter).
+    // Longer rows and larger meshes are launched step by step.
+    const int per = DX == 1 ? kSolveOwn : (nx <= kSolveHalo ? kSolveOwn / nx : 0);
+    const int64_t ngroups = per > 0 ? ((DX == 1 ? n : (int64_t)ny) + per - 1) / per : 0;
+    const bool one_launch = per > 0 && ngroups <= kSolveMaxGroups;
+    const int groups = one_launch ? (int)ngroups : 0;
     hipLaunchKernelGGL(k_stencil<DX>, dim3(stencil_blocks(n)), dim3(kStencilThreads), 0, st, x, w, off, n, g.colM,
-                       g.colW);
+                       g.colW, (unsigned long long*)g.t, one_launch ? 2 * groups : 0);
+    if (one_launch) {
+        SolveArgs a;
+        a.colM = g.colM;
+        a.colW = g.colW;
+        a.target = target;
+        a.off = off;
+        a.n = n;
+        a.nx = nx;
+        a.ny = ny;
+        a.per = per;
+        a.tol = tol;
+        a.max_iter = max_iter;
+        a.max_restarts = kMaxRestarts;
+        a.x = g.x;
+        a.halo[0] = g.p;
+        a.halo[1] = g.v;
+        a.part = g.s;  // 128 B per group: the vector holds 8 B per cell, at least 256
+        a.tag = (unsigned long long*)g.t;
+        a.st = g.st;
+        hipLaunchKernelGGL(k_solve<DX>, dim3(groups), dim3(kSolveThreads), 0, st, a);
+        hipLaunchKernelGGL(k_apply_dA, dim3((unsigned)n), dim3(256), 0, st, w, off, g.x, g.st);
+        if (!read_state()) return GM_EHIP;
+        if (hs[S_EMPTY] != 0.0) return GM_EINVAL;  // a cell without particles: M is singular
+        const double rel = hs[S_TOL2B2] > 0.0 ? std::sqrt(hs[S_R2] / hs[S_TOL2B2]) : 0.0;
+        if (hs[S_DONE] == 1.0 && std::isfinite(rel)) {
+            if (iters_out) *iters_out = (int)hs[S_ITERS];
+            if (resid_out) *resid_out = rel;
+            return GM_OK;
+        }
+    }
     hipLaunchKernelGGL(k_setup<DX>, dim3(nb), vb, 0, st, g.colM, g.colW, target, off, n, nx, ny, g.dinv, g.b, g.x,
                        g.partial);
     fold(E_INIT);
@@ -451,7 +839,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
             if (hs[S_DONE] != 0.0) break;
         }
     }
-    hipLaunchKernelGGL(k_apply_dA, dim3((unsigned)n), dim3(256), 0, st, w, off, g.x);
+    hipLaunchKernelGGL(k_apply_dA, dim3((unsigned)n), dim3(256), 0, st, w, off, g.x, (const double*)nullptr);
     if (hipGetLastError() != hipSuccess) return GM_EHIP;
     const double rel = b2 > 0.0 ? std::sqrt(r2 / b2) : 0.0;
     if (iters_out) *iters_out = iters;
@@ -482,11 +870,11 @@ int gm_deposit(const double* x, const double* w, const int64_t* cell_off, int64_
     const unsigned nb = (unsigned)vec_blocks(n_cells);
     if (dx == 1) {
         hipLaunchKernelGGL(k_stencil<1>, dim3(stencil_blocks(n_cells)), dim3(kStencilThreads), 0, st, x, w,
-                           cell_off, n_cells, nullptr, g.colW);
+                           cell_off, n_cells, nullptr, g.colW, (unsigned long long*)nullptr, 0);
         hipLaunchKernelGGL(k_deposit<1>, dim3(nb), dim3(kVecThreads), 0, st, g.colW, n_cells, NX, NY, dep);
     } else {
         hipLaunchKernelGGL(k_stencil<2>, dim3(stencil_blocks(n_cells)), dim3(kStencilThreads), 0, st, x, w,
-                           cell_off, n_cells, nullptr, g.colW);
+                           cell_off, n_cells, nullptr, g.colW, (unsigned long long*)nullptr, 0);
         hipLaunchKernelGGL(k_deposit<2>, dim3(nb), dim3(kVecThreads), 0, st, g.colW, n_cells, NX, NY, dep);
     }
     return hipGetLastError() == hipSuccess ? GM_OK : GM_EHIP;
