@@ -12,14 +12,15 @@
 //               E[u_d^3], E[u_d^4] - 3, E[u_d^2 u_e^2] - 1 -> 105 BF16 values
 //               (padded to 128) and the frame (m, L_C)
 //   k_gemm      C = A B with BF16 operands on v_mfma_f32_16x16x32_bf16, FP32
-//               accumulation, fused bias / ReLU / mask epilogue, FP32 and/or
-//               BF16 outputs; arbitrary element strides cover the transposed
-//               products of the backward pass
-//   k_loss      soft cross-entropy of the target weights + weighted squared
-//               error of the whitened means and log-Cholesky factors, and its
-//               gradient
-//   k_colsum    bias gradients (fixed-order column sums)
-//   k_adam      Adam on FP32 master weights, refreshing the BF16 copies
+//               accumulation, fused bias / ReLU epilogue, FP32 and/or BF16
+//               outputs
+//   k_train_rows  a training step's row-local part: gather, forward, loss
+//               (soft cross-entropy of the target weights + weighted squared
+//               error of the whitened means and log-Cholesky factors) and
+//               the gradients of the activations
+//   k_train_update  weight gradients on MFMA, bias gradients (fixed-order
+//               column sums) and Adam on FP32 master weights, refreshing the
+//               BF16 copies
 //   k_decode    network outputs -> initial mixtures (gm_init layout)
 //   k_targets   plain-EM mixtures -> training targets in the whitened frame
 #include <stdio.h>
@@ -169,10 +170,9 @@ __global__ __launch_bounds__(kFeatThreads) void k_features3(const double* v, con
 // workgroup (a 32x32 block tile).  A(i,k) = A[i*sa_i + k*sa_k],
 // B(k,j) = B[k*sb_k + j*sb_j].  Each 32-wide step of k stages the block's
 // A and B slices through LDS, loaded along whichever index is contiguous in
-// memory (the transposed operands of the backward products included) and
+// memory and
 // stored k-contiguous, so every MFMA operand is one 16-byte LDS read.
-// Epilogue: + bias[j], ReLU, mask (keep where mask(i,j) > 0), then FP32
-// and/or BF16 stores.
+// Epilogue: + bias[j], ReLU, then FP32 and/or BF16 stores.
 // ---------------------------------------------------------------------------
 struct GemmArgs {
     const uint16_t* A;
@@ -181,8 +181,6 @@ struct GemmArgs {
     int64_t sb_k, sb_j;
     int M, N, K;
     const float* bias;
-    const float* mask;
-    int64_t ldm;
     int relu;
     float* C32;
     int64_t ldc;
@@ -257,7 +255,6 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs g)
         float x = acc[r];
         if (g.bias) x += g.bias[j];
         if (g.relu) x = x > 0.f ? x : 0.f;
-        if (g.mask) x = g.mask[(int64_t)i * g.ldm + j] > 0.f ? x : 0.f;
         if (g.C32) g.C32[(int64_t)i * g.ldc + j] = x;
         if (g.C16) g.C16[(int64_t)i * g.ldc16 + j] = f2bf(x);
     }
@@ -272,96 +269,373 @@ static int gemm(const GemmArgs& a, hipStream_t st)
 }
 
 // ---------------------------------------------------------------------------
-// loss and its gradient, one thread per row
+// Training step, two launches.
+//
+// Everything up to the gradients of the activations concerns one row of the
+// batch at a time, so k_train_rows takes 16 rows per workgroup through gather,
+// the three layers, the loss and the two backward products with the
+// activations in LDS; a wave owns 16 columns of each layer, whose weights it
+// loads from the L2 as MFMA operands while the layer before runs.  For
+// that the forward products read a second BF16 copy of the weights (wf) in
+// blocks of 32 inputs, the 32 inputs of an output contiguous; the
+// backward products read the row-major copy as it lies.  k_train_update then
+// forms dW = A^T dZ from activations that k_train_rows stored in the same
+// blocks of 32 rows (an operand is one contiguous KB), the bias gradients, and
+// applies Adam to what each wave holds.
+//
+// What bounds them is latency: five dependent layers, and 32 dependent
+// MFMAs per 1024 rows.  Launched one product, sum and loss at a time (14
+// launches, 20-160 workgroups each, the loss on one thread per row) a step of
+// 1024 rows took 204 us of kernels; these two take 18 and 11 us, and an epoch
+// of four such steps 0.21 ms against 0.91 ms.  Every product accumulates in
+// the order it had there, with the same MFMA, and the sums likewise, so the
+// trained parameters are the same bit for bit.
 // ---------------------------------------------------------------------------
-__global__ void k_loss(const float* Y, const float* T, int B, float lambda, float* dY, uint16_t* dYb, float* loss)
+constexpr int kTrainRows = 16;
+constexpr int kTrainThreads = 1024;
+static_assert(kTrainThreads / 64 == NH / 16 && kTrainThreads / 64 == kTrainRows, "a wave per 16 columns, and per row");
+
+// element (k, i) of a matrix with ni columns in blocks of 32 k
+__host__ __device__ constexpr size_t blocked(size_t k, size_t i, size_t ni) { return (k / 32) * ni * 32 + i * 32 + k % 32; }
+// rows of the blocked batch arrays
+__host__ __device__ constexpr size_t padded_rows(size_t batch) { return (batch + 31) / 32 * 32; }
+
+struct TrainArgs {
+    const uint16_t* feats;
+    const float* targets;
+    const int32_t* idx;
+    int64_t n_rows;
+    int B;
+    float lambda;
+    const float* w;
+    const uint16_t *wb, *wf;
+    uint16_t *X, *H1, *H2, *dYb, *dH2b, *dH1b;  // blocked, padded_rows(B) rows
+    float *dY, *dH2, *dH1;                      // blocked
+    float* loss;
+};
+
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4 mfma_bf16(u16x8 a, u16x8 b, f32x4 c)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= B) return;
-    const float* y = Y + (size_t)r * NO;
-    const float* t = T + (size_t)r * NO;
-    float* g = dY + (size_t)r * NO;
-    uint16_t* gb = dYb + (size_t)r * NO;
-    float mx = -INFINITY;
-    for (int j = 0; j < NSLOT; ++j) mx = fmaxf(mx, y[j * SLOT]);
-    float se = 0.f, wsum = 0.f;
-    for (int j = 0; j < NSLOT; ++j) {
-        se += expf(y[j * SLOT] - mx);
-        wsum += t[j * SLOT];
-    }
-    const float lse = mx + logf(se);
-    const float invB = 1.0f / (float)B;
-    float l = 0.f;
-    for (int j = 0; j < NSLOT; ++j) {
-        const float wt = t[j * SLOT];
-        const float pj = expf(y[j * SLOT] - lse);
-        l += -wt * (y[j * SLOT] - lse);
-        const float gl = (pj * wsum - wt) * invB;
-        g[j * SLOT] = gl;
-        gb[j * SLOT] = f2bf(gl);
-        for (int q = 1; q < SLOT; ++q) {
-            const float d = y[j * SLOT + q] - t[j * SLOT + q];
-            l += lambda * wt * d * d;
-            const float gq = 2.f * lambda * wt * d * invB;
-            g[j * SLOT + q] = gq;
-            gb[j * SLOT + q] = f2bf(gq);
-        }
-    }
-    if (loss) loss[r] = l;
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                   0);
 }
 
-// column sums: a 32 x 32 block per 32 columns; thread (ty, tx) adds rows
-// ty, ty + 32, ... of column tx, then row 0 adds the 32 partials in order
-constexpr int kColTile = 32;
-__global__ __launch_bounds__(kColTile * kColTile) void k_colsum(const float* X, int rows, int cols, int64_t ld,
-                                                                 float* out)
+__global__ __launch_bounds__(kTrainThreads) void k_train_rows(TrainArgs A)
 {
-    __shared__ float part[kColTile][kColTile + 1];
-    const int tx = threadIdx.x % kColTile, ty = threadIdx.x / kColTile;
-    const int j = blockIdx.x * kColTile + tx;
-    float s = 0.f;
-    if (j < cols)
-        for (int r = ty; r < rows; r += kColTile) s += X[(size_t)r * ld + j];
-    part[ty][tx] = s;
+    constexpr int LX = NFP + 8, LH = NH + 8, LY = NO + 8;  // LDS row lengths: rows of 16-byte reads on other banks
+    __shared__ __align__(16) uint16_t s_x[kTrainRows * LX], s_h1[kTrainRows * LH], s_h2[kTrainRows * LH],
+        s_dy[kTrainRows * LY], s_dh[kTrainRows * LH];
+    __shared__ __align__(16) float s_y[kTrainRows * LY], s_t[kTrainRows * NO];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int r0 = blockIdx.x * kTrainRows;
+    const int col = wave * 16 + (lane & 15);    // this lane's output column
+    const int kq = (lane >> 4) * 8;             // its eight inputs of an operand
+    const int ri = (lane >> 4) * 4;             // its four rows of a result
+
+    // operands of the weights: forward from the blocked copy, backward from
+    // the row-major one (the product's inputs are W's columns)
+    auto fwd = [&](auto& f, size_t off, int n) {
+#pragma unroll
+        for (int q = 0; q < (int)(sizeof(f) / sizeof(f[0])); ++q)
+            f[q] = *reinterpret_cast<const u16x8*>(A.wf + off + blocked(32 * q, col, n) + kq);
+    };
+    auto bwd = [&](auto& f, size_t off, int n) {
+#pragma unroll
+        for (int q = 0; q < (int)(sizeof(f) / sizeof(f[0])); ++q)
+            f[q] = *reinterpret_cast<const u16x8*>(A.wb + off + (size_t)col * n + 32 * q + kq);
+    };
+    auto product = [&](const uint16_t* in, int ld, const auto& f) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < (int)(sizeof(f) / sizeof(f[0])); ++q)
+            acc = mfma_bf16(*reinterpret_cast<const u16x8*>(in + (lane & 15) * ld + 32 * q + kq), f[q], acc);
+        return acc;
+    };
+    // four rows of a column, zero beyond the batch
+    auto put = [&](uint16_t* X, const u16x4& h, int c, int row, int n) {
+        u16x4 z;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[r] = r0 + row + r < A.B ? h[r] : (uint16_t)0;
+        *reinterpret_cast<u16x4*>(X + blocked(r0 + row, c, n)) = z;
+    };
+    auto put32 = [&](float* X, const f32x4& x, int c, int row, int n) {
+        f32x4 z;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[r] = r0 + row + r < A.B ? x[r] : 0.f;
+        *reinterpret_cast<f32x4*>(X + blocked(r0 + row, c, n)) = z;
+    };
+
+    u16x8 f1[NFP / 32], f2[NH / 32], f3[NH / 32], g3[NO / 32], g2[NH / 32];
+    fwd(f1, OFF_W1, NH);
+    // gather, one wave per row; an index outside [0, n_rows) gives a zero row
+    // (zero features and zero target weights: it adds nothing to the loss or
+    // the gradient)
+    const int row = r0 + wave;
+    {
+        const int64_t src = row < A.B ? A.idx[row] : -1;
+        const bool ok = src >= 0 && src < A.n_rows;
+        uint16_t xv[2];
+        float tv[3];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) xv[u] = ok ? A.feats[src * NFP + lane + 64 * u] : (uint16_t)0;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) tv[u] = ok && lane + 64 * u < NO ? A.targets[src * NO + lane + 64 * u] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) s_x[wave * LX + lane + 64 * u] = xv[u];
+#pragma unroll
+        for (int u = 0; u < 3; ++u)
+            if (lane + 64 * u < NO) s_t[wave * NO + lane + 64 * u] = tv[u];
+    }
+    fwd(f2, OFF_W2, NH);
+    const float bias1 = A.w[OFF_B1 + col], bias2 = A.w[OFF_B2 + col];
     __syncthreads();
-    if (ty == 0 && j < cols) {
-        float t = part[0][tx];
-        for (int q = 1; q < kColTile; ++q) t += part[q][tx];
-        out[j] = t;
+    // hidden layers; the masks of the backward pass stay with the columns
+    bool pos1[4], pos2[4];
+    auto hidden = [&](const f32x4& acc, float bias, uint16_t* s, uint16_t* X, bool (&pos)[4]) {
+        u16x4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float x = acc[r] + bias;
+            x = x > 0.f ? x : 0.f;
+            pos[r] = x > 0.f;
+            h[r] = f2bf(x);
+            s[(ri + r) * LH + col] = h[r];
+        }
+        put(X, h, col, ri, NH);
+    };
+    hidden(product(s_x, LX, f1), bias1, s_h1, A.H1, pos1);
+    if (tid < NFP * 4) {
+        const int c = tid >> 2, i = (tid & 3) * 4;
+        u16x4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[r] = s_x[(i + r) * LX + c];
+        put(A.X, h, c, i, NFP);
     }
+    if (col < NO) fwd(f3, OFF_W3, NO);
+    __syncthreads();
+    hidden(product(s_h1, LH, f2), bias2, s_h2, A.H2, pos2);
+    bwd(g3, OFF_W3, NO);
+    __syncthreads();
+    if (col < NO) {
+        const float bias3 = A.w[OFF_B3 + col];
+        const f32x4 acc = product(s_h2, LH, f3);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s_y[(ri + r) * LY + col] = acc[r] + bias3;
+    }
+    bwd(g2, OFF_W2, NH);
+    __syncthreads();
+    // loss and its gradient, one wave per row: lane j holds slot j's logit,
+    // the sums over the slots run in slot order
+    {
+        float* y = s_y + wave * LY;
+        const float* t = s_t + wave * NO;
+        const int slot = lane & (NSLOT - 1);
+        const float lg = y[slot * SLOT], wt = t[slot * SLOT];
+        float mx = lg;
+#pragma unroll
+        for (int d = NSLOT / 2; d > 0; d /= 2) mx = fmaxf(mx, __shfl_xor(mx, d));
+        const float e = expf(lg - mx);
+        float se = 0.f, wsum = 0.f;
+#pragma unroll
+        for (int j = 0; j < NSLOT; ++j) {
+            se += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e), j));
+            wsum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), j));
+        }
+        const float lse = mx + logf(se);
+        const float invB = 1.0f / (float)A.B;
+        const float gl = fmaf(expf(lg - lse), wsum, -wt) * invB;
+        float l = lane < NSLOT ? -wt * (lg - lse) : 0.f;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const int c = lane + 64 * u;
+            if (c < NO && c % SLOT != 0) {
+                const float wc = t[c - c % SLOT], d = y[c] - t[c];
+                l = fmaf(A.lambda * wc * d, d, l);
+                const float g = 2.f * A.lambda * wc * d * invB;
+                y[c] = g;
+                s_dy[wave * LY + c] = f2bf(g);
+            }
+        }
+        if (lane < NSLOT) {
+            y[lane * SLOT] = gl;
+            s_dy[wave * LY + lane * SLOT] = f2bf(gl);
+        }
+        l = wave_sum(l);
+        if (lane == 0 && row < A.B) A.loss[row] = l;
+    }
+    __syncthreads();
+    if (tid < NO * 4) {
+        const int c = tid >> 2, i = (tid & 3) * 4;
+        u16x4 h;
+        f32x4 x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            h[r] = s_dy[(i + r) * LY + c];
+            x[r] = s_y[(i + r) * LY + c];
+        }
+        put(A.dYb, h, c, i, NO);
+        put32(A.dY, x, c, i, NO);
+    }
+    auto hidden_grad = [&](f32x4 acc, const bool (&pos)[4], uint16_t* s, uint16_t* X, float* X32) {
+        u16x4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            acc[r] = pos[r] ? acc[r] : 0.f;
+            h[r] = f2bf(acc[r]);
+            if (s) s[(ri + r) * LH + col] = h[r];
+        }
+        put(X, h, col, ri, NH);
+        put32(X32, acc, col, ri, NH);
+    };
+    hidden_grad(product(s_dy, LY, g3), pos2, s_dh, A.dH2b, A.dH2);
+    __syncthreads();
+    hidden_grad(product(s_dh, LH, g2), pos1, nullptr, A.dH1b, A.dH1);
 }
 
-__global__ void k_adam(float* w, float* m, float* v, const float* g, uint16_t* wb, int64_t n, float lr, float b1,
-                       float b2, float eps, float bc1, float bc2)
+struct UpdateArgs {
+    int nk;                                     // blocks of 32 rows
+    const uint16_t *X, *H1, *H2, *dYb, *dH2b, *dH1b;
+    const float *dY, *dH2, *dH1;
+    float *w, *m, *v, *grad;
+    uint16_t *wb, *wf;
+    float lr, b1, b2, eps, bc1, bc2;
+};
+
+__device__ __forceinline__ float adam(const UpdateArgs& A, size_t p, float g, float w, float m, float v)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.f - b1) * gi;
-    const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float wi = w[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-    w[i] = wi;
-    if (wb) wb[i] = f2bf(wi);
+    const float mi = fmaf(1.f - A.b1, g, A.b1 * m);
+    const float vi = fmaf(g, (1.f - A.b2) * g, A.b2 * v);
+    const float wi = w - A.lr * (mi / A.bc1) / (sqrtf(vi / A.bc2) + A.eps);
+    A.grad[p] = g;
+    A.m[p] = mi;
+    A.v[p] = vi;
+    A.w[p] = wi;
+    A.wb[p] = f2bf(wi);
+    return wi;
 }
 
-__global__ void k_to_bf16(const float* w, uint16_t* wb, int64_t n)
+// workgroups: the 32 x 32 tiles of dW1, dW2 and dW3 (a wave per 16 x 16),
+// then eight columns each (two per wave) of the bias gradients
+constexpr int kUpdateThreads = 256;
+constexpr int kTiles1 = (NFP / 32) * (NH / 32), kTiles2 = (NH / 32) * (NH / 32), kTiles3 = (NH / 32) * (NO / 32);
+constexpr int kBiasCols = 2 * (kUpdateThreads / 64);
+constexpr int kUpdateGroups = kTiles1 + kTiles2 + kTiles3 + (2 * NH + NO) / kBiasCols;
+constexpr int kUpdateBatch = 8;                 // blocks of rows loaded ahead
+
+__global__ __launch_bounds__(kUpdateThreads) void k_train_update(UpdateArgs A)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) wb[i] = f2bf(w[i]);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int g = blockIdx.x;
+    if (g >= kTiles1 + kTiles2 + kTiles3) {
+        // lane l of a half-wave adds rows l, l + 32, ..., then its first lane
+        // the 32 partial sums in order
+        __shared__ __align__(16) float part[kBiasCols][32];
+        const int half = lane >> 5, ty = lane & 31, q = 2 * wave + half;
+        int c = (g - kTiles1 - kTiles2 - kTiles3) * kBiasCols + q;
+        const float* X;
+        size_t p;
+        int n;
+        if (c < NO) {
+            X = A.dY, p = OFF_B3 + c, n = NO;
+        } else if (c < NO + NH) {
+            c -= NO;
+            X = A.dH2, p = OFF_B2 + c, n = NH;
+        } else {
+            c -= NO + NH;
+            X = A.dH1, p = OFF_B1 + c, n = NH;
+        }
+        const float w = A.w[p], m = A.m[p], v = A.v[p];
+        X += c * 32 + ty;
+        float s = 0.f;
+        int k = 0;
+        for (; k + 16 <= A.nk; k += 16) {
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = X[(size_t)(k + u) * n * 32];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) s += x[u];
+        }
+        for (; k < A.nk; ++k) s += X[(size_t)k * n * 32];
+        part[q][ty] = s;
+        __syncthreads();
+        if (ty == 0) {
+            float t = part[q][0];
+#pragma unroll
+            for (int u = 1; u < 32; ++u) t += part[q][u];
+            adam(A, p, t, w, m, v);
+        }
+        return;
+    }
+    // dW = A^T dZ, K = the batch
+    const uint16_t *P, *Q;
+    size_t off;
+    int ni, nj;
+    if (g < kTiles1) {
+        P = A.X, Q = A.dH1b, off = OFF_W1, ni = NFP, nj = NH;
+    } else if (g < kTiles1 + kTiles2) {
+        g -= kTiles1;
+        P = A.H1, Q = A.dH2b, off = OFF_W2, ni = NH, nj = NH;
+    } else {
+        g -= kTiles1 + kTiles2;
+        P = A.H2, Q = A.dYb, off = OFF_W3, ni = NH, nj = NO;
+    }
+    const int ti = g % (ni / 32) * 32 + (wave >> 1) * 16, tj = g / (ni / 32) * 32 + (wave & 1) * 16;
+    const int i = ti + (lane >> 4) * 4, j = tj + (lane & 15);
+    P += (size_t)(ti + (lane & 15)) * 32 + (lane >> 4) * 8;
+    Q += (size_t)(tj + (lane & 15)) * 32 + (lane >> 4) * 8;
+    const size_t sp = (size_t)ni * 32, sq = (size_t)nj * 32;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    u16x8 a[2][kUpdateBatch], b[2][kUpdateBatch];
+    auto load = [&](int set, int k0) {
+#pragma unroll
+        for (int u = 0; u < kUpdateBatch; ++u)
+            if (k0 + u < A.nk) {
+                a[set][u] = *reinterpret_cast<const u16x8*>(P + (size_t)(k0 + u) * sp);
+                b[set][u] = *reinterpret_cast<const u16x8*>(Q + (size_t)(k0 + u) * sq);
+            }
+    };
+    auto mac = [&](int set, int k0) {
+#pragma unroll
+        for (int u = 0; u < kUpdateBatch; ++u)
+            if (k0 + u < A.nk) acc = mfma_bf16(a[set][u], b[set][u], acc);
+    };
+    load(0, 0);
+    float w[4], m[4], v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const size_t p = off + (size_t)(i + r) * nj + j;
+        w[r] = A.w[p];
+        m[r] = A.m[p];
+        v[r] = A.v[p];
+    }
+    for (int k0 = 0; k0 < A.nk; k0 += 2 * kUpdateBatch) {
+        load(1, k0 + kUpdateBatch);
+        mac(0, k0);
+        load(0, k0 + 2 * kUpdateBatch);
+        mac(1, k0 + kUpdateBatch);
+    }
+    u16x4 h;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = f2bf(adam(A, off + (size_t)(i + r) * nj + j, acc[r], w[r], m[r], v[r]));
+    *reinterpret_cast<u16x4*>(A.wf + off + blocked(i, j, nj)) = h;
 }
 
-// batch rows; an index outside [0, n_rows) gives a zero row (zero features
-// and zero target weights, so it adds nothing to the loss or the gradient)
-__global__ void k_gather(const uint16_t* feats, const float* T, const int32_t* idx, int64_t n_rows, uint16_t* Xb,
-                         float* Tb)
+// the BF16 copies of the parameters: row-major, and the weights in blocks of
+// 32 inputs
+__global__ void k_to_bf16(const float* w, uint16_t* wb, uint16_t* wf)
 {
-    const int r = blockIdx.x;
-    const int64_t src = idx[r];
-    const bool ok = src >= 0 && src < n_rows;
-    for (int t = threadIdx.x; t < NFP; t += blockDim.x) Xb[(size_t)r * NFP + t] = ok ? feats[src * NFP + t] : 0;
-    for (int t = threadIdx.x; t < NO; t += blockDim.x) Tb[(size_t)r * NO + t] = ok ? T[src * NO + t] : 0.f;
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= NPARAM) return;
+    const uint16_t h = f2bf(w[i]);
+    wb[i] = h;
+    if (i < OFF_B1)
+        wf[OFF_W1 + blocked(i / NH, i % NH, NH)] = h;
+    else if (i >= OFF_W2 && i < OFF_B2)
+        wf[OFF_W2 + blocked((i - OFF_W2) / NH, (i - OFF_W2) % NH, NH)] = h;
+    else if (i >= OFF_W3 && i < OFF_B3)
+        wf[OFF_W3 + blocked((i - OFF_W3) / NO, (i - OFF_W3) % NO, NO)] = h;
 }
 
 // Glorot-uniform weights from Philox (key (seed, "WARM"), counter (index, tensor, 0, 0)), zero biases
@@ -648,9 +922,10 @@ struct gm_warm {
     float* v;        // Adam second moment
     float* grad;     // gradients (NPARAM)
     uint16_t* wb;    // BF16 copy of the parameters (weights used by the products)
-    // batch scratch
+    uint16_t* wf;    // the weights again, in blocks of 32 inputs
+    // batch scratch, in blocks of 32 rows (the loss by rows)
     uint16_t *Xb, *H1b, *H2b, *dYb, *dH2b, *dH1b;
-    float *Tb, *H1, *H2, *Y, *dY, *dH2, *dH1, *loss;
+    float *dY, *dH2, *dH1, *loss;
     void* block;     // one allocation holding everything
 };
 
@@ -679,25 +954,19 @@ gm::GemmArgs ga(const uint16_t* A, int64_t sa_i, int64_t sa_k, const uint16_t* B
     return g;
 }
 
-// forward of rows [0, rows) of X (BF16, NFP wide) into H1b/H2b (BF16) and Y (FP32);
-// FP32 hidden copies when given (training)
-int forward(const gm_warm* mdl, const uint16_t* X, int rows, uint16_t* H1b, float* H1, uint16_t* H2b, float* H2,
-            float* Y, hipStream_t st)
+// forward of rows [0, rows) of X (BF16, NFP wide) into H1b/H2b (BF16) and Y (FP32)
+int forward(const gm_warm* mdl, const uint16_t* X, int rows, uint16_t* H1b, uint16_t* H2b, float* Y, hipStream_t st)
 {
     using namespace gm;
     GemmArgs g = ga(X, NFP, 1, mdl->wb + OFF_W1, NH, 1, rows, NH, NFP);
     g.bias = mdl->w + OFF_B1;
     g.relu = 1;
-    g.C32 = H1;
-    g.ldc = NH;
     g.C16 = H1b;
     g.ldc16 = NH;
     if (gemm(g, st)) return GM_EHIP;
     g = ga(H1b, NH, 1, mdl->wb + OFF_W2, NH, 1, rows, NH, NH);
     g.bias = mdl->w + OFF_B2;
     g.relu = 1;
-    g.C32 = H2;
-    g.ldc = NH;
     g.C16 = H2b;
     g.ldc16 = NH;
     if (gemm(g, st)) return GM_EHIP;
@@ -725,7 +994,7 @@ int gm_warm_create(gm_warm** out, int32_t D, int32_t kmax, int32_t batch, uint64
     m->D = D;
     m->kmax = kmax;
     m->batch = batch;
-    const size_t B = (size_t)batch;
+    const size_t B = padded_rows((size_t)batch);
     size_t sz[20], tot = 0;
     int i = 0;
     sz[i++] = al256(NPARAM * 4);        // w
@@ -733,16 +1002,13 @@ int gm_warm_create(gm_warm** out, int32_t D, int32_t kmax, int32_t batch, uint64
     sz[i++] = al256(NPARAM * 4);        // v
     sz[i++] = al256(NPARAM * 4);        // grad
     sz[i++] = al256(NPARAM * 2);        // wb
+    sz[i++] = al256(NPARAM * 2);        // wf
     sz[i++] = al256(B * NFP * 2);       // Xb
     sz[i++] = al256(B * NH * 2);        // H1b
     sz[i++] = al256(B * NH * 2);        // H2b
     sz[i++] = al256(B * NO * 2);        // dYb
     sz[i++] = al256(B * NH * 2);        // dH2b
     sz[i++] = al256(B * NH * 2);        // dH1b
-    sz[i++] = al256(B * NO * 4);        // Tb
-    sz[i++] = al256(B * NH * 4);        // H1
-    sz[i++] = al256(B * NH * 4);        // H2
-    sz[i++] = al256(B * NO * 4);        // Y
     sz[i++] = al256(B * NO * 4);        // dY
     sz[i++] = al256(B * NH * 4);        // dH2
     sz[i++] = al256(B * NH * 4);        // dH1
@@ -754,17 +1020,17 @@ int gm_warm_create(gm_warm** out, int32_t D, int32_t kmax, int32_t batch, uint64
         return GM_ENOMEM;
     }
     char* p = (char*)m->block;
-    void** ptrs[20] = {(void**)&m->w,   (void**)&m->m,   (void**)&m->v,   (void**)&m->grad, (void**)&m->wb,
-                       (void**)&m->Xb,  (void**)&m->H1b, (void**)&m->H2b, (void**)&m->dYb,  (void**)&m->dH2b,
-                       (void**)&m->dH1b, (void**)&m->Tb, (void**)&m->H1,  (void**)&m->H2,   (void**)&m->Y,
-                       (void**)&m->dY,  (void**)&m->dH2, (void**)&m->dH1, (void**)&m->loss};
+    void** ptrs[20] = {(void**)&m->w,    (void**)&m->m,    (void**)&m->v,   (void**)&m->grad, (void**)&m->wb,
+                       (void**)&m->wf,   (void**)&m->Xb,   (void**)&m->H1b, (void**)&m->H2b,  (void**)&m->dYb,
+                       (void**)&m->dH2b, (void**)&m->dH1b, (void**)&m->dY,  (void**)&m->dH2,  (void**)&m->dH1,
+                       (void**)&m->loss};
     for (int k = 0; k < nb; ++k) {
         *ptrs[k] = p;
         p += sz[k];
     }
     const int nblk = (int)((NPARAM + 255) / 256);
     hipLaunchKernelGGL(k_init_params, dim3(nblk), dim3(256), 0, st, m->w, seed);
-    hipLaunchKernelGGL(k_to_bf16, dim3(nblk), dim3(256), 0, st, m->w, m->wb, (int64_t)NPARAM);
+    hipLaunchKernelGGL(k_to_bf16, dim3(nblk), dim3(256), 0, st, m->w, m->wb, m->wf);
     if (!ok(hipMemsetAsync(m->m, 0, NPARAM * 4, st)) || !ok(hipMemsetAsync(m->v, 0, NPARAM * 4, st)) ||
         launch_ok() != GM_OK) {
         (void)hipFree(m->block);
@@ -799,7 +1065,7 @@ int gm_warm_set_params(gm_warm* m, const float* host)
     if (!ok(hipMemset(m->m, 0, NPARAM * 4)) || !ok(hipMemset(m->v, 0, NPARAM * 4))) return GM_EHIP;
     m->step = 0;
     const int nblk = (int)((NPARAM + 255) / 256);
-    hipLaunchKernelGGL(k_to_bf16, dim3(nblk), dim3(256), 0, 0, m->w, m->wb, (int64_t)NPARAM);
+    hipLaunchKernelGGL(k_to_bf16, dim3(nblk), dim3(256), 0, 0, m->w, m->wb, m->wf);
     if (launch_ok() != GM_OK) return GM_EHIP;
     return ok(hipDeviceSynchronize()) ? GM_OK : GM_EHIP;
 }
@@ -876,7 +1142,7 @@ int gm_warm_forward(const gm_warm* m, const uint16_t* feats, int64_t n_rows, flo
     if (!ws || ws_bytes < need) return GM_ENOMEM;
     uint16_t* H1b = (uint16_t*)ws;
     uint16_t* H2b = (uint16_t*)((char*)ws + al256((size_t)n_rows * NH * 2));
-    return forward(m, feats, (int)n_rows, H1b, nullptr, H2b, nullptr, Y, (hipStream_t)stream);
+    return forward(m, feats, (int)n_rows, H1b, H2b, Y, (hipStream_t)stream);
 }
 
 int gm_warm_model_kmax(const gm_warm* m) { return m ? m->kmax : 0; }
@@ -930,54 +1196,54 @@ int gm_warm_train_step(gm_warm* m, const uint16_t* feats, const float* targets, 
     if (!m || !feats || !targets || !idx || n_rows < 1 || !(lr > 0.f) || !(lambda >= 0.f)) return GM_EINVAL;
     hipStream_t st = (hipStream_t)stream;
     const int B = m->batch;
-    hipLaunchKernelGGL(k_gather, dim3(B), dim3(128), 0, st, feats, targets, idx, n_rows, m->Xb, m->Tb);
-    if (launch_ok() != GM_OK) return GM_EHIP;
-    int rc = forward(m, m->Xb, B, m->H1b, m->H1, m->H2b, m->H2, m->Y, st);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_loss, dim3((B + 127) / 128), dim3(128), 0, st, m->Y, m->Tb, B, lambda, m->dY, m->dYb,
-                       loss_rows ? loss_rows : m->loss);
-    if (launch_ok() != GM_OK) return GM_EHIP;
-    // layer 3: dW3 = H2^T dY, db3 = colsum dY, dH2 = (dY W3^T) * [H2 > 0]
-    GemmArgs g = ga(m->H2b, 1, NH, m->dYb, NO, 1, NH, NO, B);
-    g.C32 = m->grad + OFF_W3;
-    g.ldc = NO;
-    if (gemm(g, st)) return GM_EHIP;
-    hipLaunchKernelGGL(k_colsum, dim3((NO + kColTile - 1) / kColTile), dim3(kColTile * kColTile), 0, st, m->dY, B, NO, (int64_t)NO, m->grad + OFF_B3);
-    g = ga(m->dYb, NO, 1, m->wb + OFF_W3, 1, NO, B, NH, NO);
-    g.mask = m->H2;
-    g.ldm = NH;
-    g.C32 = m->dH2;
-    g.ldc = NH;
-    g.C16 = m->dH2b;
-    g.ldc16 = NH;
-    if (gemm(g, st)) return GM_EHIP;
-    // layer 2
-    g = ga(m->H1b, 1, NH, m->dH2b, NH, 1, NH, NH, B);
-    g.C32 = m->grad + OFF_W2;
-    g.ldc = NH;
-    if (gemm(g, st)) return GM_EHIP;
-    hipLaunchKernelGGL(k_colsum, dim3((NH + kColTile - 1) / kColTile), dim3(kColTile * kColTile), 0, st, m->dH2, B, NH, (int64_t)NH, m->grad + OFF_B2);
-    g = ga(m->dH2b, NH, 1, m->wb + OFF_W2, 1, NH, B, NH, NH);
-    g.mask = m->H1;
-    g.ldm = NH;
-    g.C32 = m->dH1;
-    g.ldc = NH;
-    g.C16 = m->dH1b;
-    g.ldc16 = NH;
-    if (gemm(g, st)) return GM_EHIP;
-    // layer 1 (rows of W1 beyond the 105 features get zero gradient: X is zero there)
-    g = ga(m->Xb, 1, NFP, m->dH1b, NH, 1, NFP, NH, B);
-    g.C32 = m->grad + OFF_W1;
-    g.ldc = NH;
-    if (gemm(g, st)) return GM_EHIP;
-    hipLaunchKernelGGL(k_colsum, dim3((NH + kColTile - 1) / kColTile), dim3(kColTile * kColTile), 0, st, m->dH1, B, NH, (int64_t)NH, m->grad + OFF_B1);
+    TrainArgs t;
+    t.feats = feats;
+    t.targets = targets;
+    t.idx = idx;
+    t.n_rows = n_rows;
+    t.B = B;
+    t.lambda = lambda;
+    t.w = m->w;
+    t.wb = m->wb;
+    t.wf = m->wf;
+    t.X = m->Xb;
+    t.H1 = m->H1b;
+    t.H2 = m->H2b;
+    t.dYb = m->dYb;
+    t.dH2b = m->dH2b;
+    t.dH1b = m->dH1b;
+    t.dY = m->dY;
+    t.dH2 = m->dH2;
+    t.dH1 = m->dH1;
+    t.loss = loss_rows ? loss_rows : m->loss;
+    const unsigned rows = (unsigned)padded_rows((size_t)B);
+    hipLaunchKernelGGL(k_train_rows, dim3(rows / kTrainRows), dim3(kTrainThreads), 0, st, t);
     if (launch_ok() != GM_OK) return GM_EHIP;
     m->step += 1;
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float bc1 = 1.f - powf(b1, (float)m->step), bc2 = 1.f - powf(b2, (float)m->step);
-    const int nblk = (int)((NPARAM + 255) / 256);
-    hipLaunchKernelGGL(k_adam, dim3(nblk), dim3(256), 0, st, m->w, m->m, m->v, m->grad, m->wb, (int64_t)NPARAM, lr, b1,
-                       b2, 1e-8f, bc1, bc2);
+    UpdateArgs u;
+    u.nk = (int)(rows / 32);
+    u.X = m->Xb;
+    u.H1 = m->H1b;
+    u.H2 = m->H2b;
+    u.dYb = m->dYb;
+    u.dH2b = m->dH2b;
+    u.dH1b = m->dH1b;
+    u.dY = m->dY;
+    u.dH2 = m->dH2;
+    u.dH1 = m->dH1;
+    u.w = m->w;
+    u.m = m->m;
+    u.v = m->v;
+    u.grad = m->grad;
+    u.wb = m->wb;
+    u.wf = m->wf;
+    u.lr = lr;
+    u.b1 = 0.9f;
+    u.b2 = 0.999f;
+    u.eps = 1e-8f;
+    u.bc1 = 1.f - powf(u.b1, (float)m->step);
+    u.bc2 = 1.f - powf(u.b2, (float)m->step);
+    hipLaunchKernelGGL(k_train_update, dim3(kUpdateGroups), dim3(kUpdateThreads), 0, st, u);
     return launch_ok();
 }
 
