@@ -170,8 +170,8 @@ __global__ __launch_bounds__(kFeatThreads) void k_features3(const double* v, con
 // workgroup (a 32x32 block tile).  A(i,k) = A[i*sa_i + k*sa_k],
 // B(k,j) = B[k*sb_k + j*sb_j].  Each 32-wide step of k stages the block's
 // A and B slices through LDS, loaded along whichever index is contiguous in
-// memory and
-// stored k-contiguous, so every MFMA operand is one 16-byte LDS read.
+// memory and stored k-contiguous, so every MFMA operand is one 16-byte LDS
+// read.
 // Epilogue: + bias[j], ReLU, then FP32 and/or BF16 stores.
 // ---------------------------------------------------------------------------
 struct GemmArgs {
