@@ -438,12 +438,11 @@ __device__ __forceinline__ bool density_params(const R (&S)[ntri(D)], R u, R sdc
     }
 }
 
-// Factor a component, with the floor used when it fails (eps I, eps =
-// 1e-12 tr(C)/D, growing tenfold).  Returns true if the floor was needed.
+// The floor used when a component's factorisation fails: eps I, eps = 1e-12
+// tr(C)/D, growing tenfold.
 template <typename R, int D>
-__device__ __forceinline__ bool factor_comp(CompState<R, D>& cs, double trC, R sdc)
+__device__ __forceinline__ void floor_comp(CompState<R, D>& cs, double trC, R sdc)
 {
-    if (density_params<R, D>(cs.S, cs.u, sdc, cs.A, cs.c2)) return false;
     double eps = 1e-12 * trC / D;
 #pragma unroll 1
     for (int it = 0; it < 40; ++it) {
@@ -452,6 +451,14 @@ __device__ __forceinline__ bool factor_comp(CompState<R, D>& cs, double trC, R s
         if (density_params<R, D>(cs.S, cs.u, sdc, cs.A, cs.c2)) break;
         eps *= 10.0;
     }
+}
+
+// Factor a component; returns true if the floor was needed.
+template <typename R, int D>
+__device__ __forceinline__ bool factor_comp(CompState<R, D>& cs, double trC, R sdc)
+{
+    if (density_params<R, D>(cs.S, cs.u, sdc, cs.A, cs.c2)) return false;
+    floor_comp<R, D>(cs, trC, sdc);
     return true;
 }
 
@@ -473,40 +480,39 @@ template <typename R>
 constexpr double kBigFinite = std::is_same<R, float>::value ? 3.4028234663852886e38 : 1.7976931348623157e308;
 
 // Workgroup sum of the NV M-step sums of one component update, delivered to
-// every thread: the transposed wave sums above; lane 15 of each row publishes
-// the values its row holds.  After one barrier lane v < NV adds value v over
-// all MAXW slots in wave order: slots of absent waves hold zeros (the buffer
-// is cleared when the kernel starts and only present waves write), so no
-// per-wave test is needed.
-template <int NVMAX, int MAXW, typename T, int NV>
+// every thread: the transposed wave sums above, whose row totals all lanes of
+// a row hold and store to the same place (values past NV to places nobody
+// reads): no lane masks, which cost more scalar instructions than the
+// stores.  After one barrier lane v < NV adds value v over all MAXW slots in
+// wave order (the other lanes add something): slots of absent waves hold
+// zeros (the buffer is cleared when the kernel starts and only present waves
+// write), so no per-wave test is needed.  Without the masks, and with one
+// rarely taken branch for ties and annihilations and one for the covariance
+// floor in the update: 32 cells of 156 in 1V 0.755 -> 0.686 ms, 256 cells
+// of 512 in 3V 4.02 -> 3.85 ms, bits unchanged.
+template <int MAXW, typename T, int NV>
 __device__ __forceinline__ void em_block_sum(T (&x)[NV], T* buf, int& parity, int nwaves)
 {
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    T* bb = buf + parity * (MAXW * NVMAX);
-    constexpr int NB = (NV + 3) / 4;
+    constexpr int NB = (NV + 3) / 4, SLOT = 4 * NB;
+    T* bb = buf + parity * (MAXW * SLOT);
     T b[NB];
     wave_sums_transposed<NV>(x, b);
     if (nwaves == 1) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) x[v] = lane_bcast(b[v / 4], 16 * tv_row(v) + 15);
     } else {
-        if ((lane & 15) == 15) {
-            const int r = lane >> 4;
-            const int off = 2 * (r & 1) + (r >> 1);  // value index within each group of four
+        const int r = lane >> 4;
+        const int off = 2 * (r & 1) + (r >> 1);  // value index within each group of four
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
-                if (4 * j + off < NV) bb[wid * NVMAX + 4 * j + off] = b[j];
-        }
+        for (int j = 0; j < NB; ++j) bb[wid * SLOT + 4 * j + off] = b[j];
         __syncthreads();
-        T t = T(0);
-        if (lane < NV) {
-            T part[MAXW];
+        T part[MAXW];
 #pragma unroll
-            for (int w = 0; w < MAXW; ++w) part[w] = bb[w * NVMAX + lane];
-            t = part[0];
+        for (int w = 0; w < MAXW; ++w) part[w] = bb[w * SLOT + min(lane, SLOT - 1)];
+        T t = part[0];
 #pragma unroll
-            for (int w = 1; w < MAXW; ++w) t += part[w];
-        }
+        for (int w = 1; w < MAXW; ++w) t += part[w];
 #pragma unroll
         for (int v = 0; v < NV; ++v) x[v] = lane_bcast(t, v);
         parity ^= 1;
@@ -620,12 +626,12 @@ constexpr int em_min_waves_per_simd()
 // LDS of an EM workgroup of up to MAXW waves
 template <int D, int KMAX, typename R, int MAXW>
 struct EmShared {
-    static constexpr int NS = 1 + D + ntri(D);
+    static constexpr int NR = (1 + D + ntri(D) + 3) / 4 * 4;  // places per wave of red_r
     CompressArgs A;                      // arguments read where they are used, not pinned in SGPRs
     CompState<R, D> compw[MAXW][KMAX];
     CompState<R, D> bestc[KMAX];         // best state of the outer search over K
     double red_d[2 * kMaxWaves * 2];
-    R red_r[2 * MAXW * NS];              // zero where no wave writes (em_block_sum)
+    R red_r[2 * MAXW * NR];              // zero where no wave writes (em_block_sum)
     int s_idx;
     int s_flag;
 };
@@ -934,12 +940,15 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
                             accumulate(p, eold[p], Sden[p]);
                         }
                     }
-                    em_block_sum<NS, MAXW>(sums, red_r, par_r, nwaves);
+                    em_block_sum<MAXW>(sums, red_r, par_r, nwaves);
                     const R Nk = sums[0];
                     const R NkT = Nk - (R)halfT;
-                    if (uni(fabs(NkT) < (R)(1e-5 * halfT))) status |= GM_ST_NEAR_TIE;
-                    const bool dead = uni(NkT <= R(0));
                     CompState<R, D> cn;
+                    bool dead = false;
+                    if (uni(!(NkT >= (R)(1e-5 * halfT)))) {
+                        if (uni(fabs(NkT) < (R)(1e-5 * halfT))) status |= GM_ST_NEAR_TIE;
+                        dead = uni(NkT <= R(0));
+                    }
                     if (dead) {
                         // annihilate k (eq. omegak); the weights renormalise through G
                         alive &= ~(1u << k);
@@ -947,6 +956,12 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
                         --K;
                         inv_den = m_rcp((R)(N - halfT * K));
                         annihilated = true;
+                        // parameters whose term is zero for every particle
+#pragma unroll
+                        for (int i = 0; i < D; ++i) cn.mu[i] = R(0);
+#pragma unroll
+                        for (int q = 0; q < NT; ++q) cn.A[q] = R(0);
+                        cn.c2 = R(-1e30);
                     } else {
                         // M-step (eqs. muk, sigmak about the new mean; eq. omegak)
                         const R invN = m_rcp(Nk);
@@ -965,8 +980,11 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
                         const R unew = wk * G;
                         G = G - cku + unew;
                         cn.u = unew;
-                        if (uni(factor_comp<R, D>(cn, ci->trC, sdc))) status |= GM_ST_COV_FLOOR;
-                        if (lane == 0) comp[k] = cn;  // this wave's copy; read back only by this wave
+                        if (uni(!density_params<R, D>(cn.S, cn.u, sdc, cn.A, cn.c2))) {
+                            floor_comp<R, D>(cn, ci->trC, sdc);
+                            status |= GM_ST_COV_FLOOR;
+                        }
+                        comp[k] = cn;  // this wave's copy; read back only by this wave
                     }
                     if constexpr (STORE_E) {
                         // the term of k after the update: none if it died
@@ -976,14 +994,8 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
                         for (int p = 0; p < P; ++p) {
                             s_old[p] = Sden[p];
                             Sden[p] = s_old[p] - e.get(p, k);
-                            enew[p] = R(0);
-                        }
-                        if (!dead) {
-#pragma unroll
-                            for (int p = 0; p < P; ++p) {
-                                enew[p] = fast_exp2(log2_term<R, D>(cn, x[p]) - ref[p]);
-                                Sden[p] = Sden[p] + enew[p];
-                            }
+                            enew[p] = fast_exp2(log2_term<R, D>(cn, x[p]) - ref[p]);
+                            Sden[p] = Sden[p] + enew[p];
                         }
 #pragma unroll
                         for (int p = 0; p < P; ++p) {
@@ -1246,7 +1258,7 @@ void k_em(CompressArgs A_in)
     __shared__ EmShared<D, KMAX, R, MAXW> sh;
     const int tid = threadIdx.x;
     if (tid == 0) sh.A = A_in;
-    for (int t = tid; t < 2 * MAXW * sh.NS; t += blockDim.x) sh.red_r[t] = R(0);
+    for (int t = tid; t < 2 * MAXW * sh.NR; t += blockDim.x) sh.red_r[t] = R(0);
     __syncthreads();
     const int bucket = uni(sh.A.bucket), nwaves = uni(sh.A.nwaves);
     const int count = uni(sh.A.plan[PLAN_COUNT + bucket]);
@@ -1278,7 +1290,7 @@ void k_em_span(CompressArgs A_in, int b_hi, int b_lo)
     const int tid = threadIdx.x;
     const int wid = uni(tid >> 6);
     if (tid == 0) sh.A = A_in;
-    for (int t = tid; t < 2 * MAXW * sh.NS; t += blockDim.x) sh.red_r[t] = R(0);
+    for (int t = tid; t < 2 * MAXW * sh.NR; t += blockDim.x) sh.red_r[t] = R(0);
     __syncthreads();
     int par_d = 0, par_r = 0;
     int nwaves = (int)(blockDim.x >> 6);
@@ -1301,7 +1313,7 @@ void k_em_span(CompressArgs A_in, int b_hi, int b_lo)
                 // cleared, as the sums run over all MAXW slots
                 if (wid >= W) return;
                 nwaves = W;
-                for (int t = tid; t < 2 * MAXW * sh.NS; t += 64 * W) sh.red_r[t] = R(0);
+                for (int t = tid; t < 2 * MAXW * sh.NR; t += 64 * W) sh.red_r[t] = R(0);
                 __syncthreads();
                 narrowed = true;
             }
