@@ -562,21 +562,24 @@ struct DensityTerms {
 };
 
 // One test over a thread's particles of what an update rarely does to a
-// density sum: see(t, s) for each, then hit() says whether some t is not above
-// kTinyDen or some s not below 2^64 (NaN is neither).  In FP32 positive values
-// order like their bit patterns and negative ones lie below them; two running
-// extremes (one three-operand instruction per two particles) replace a
-// comparison and a mask operation for each.
+// density sum: see(t, s) for each, then hit(least) says whether some t is not
+// above least (positive) or some s not below 2^63 (NaN is neither).  In FP32
+// positive values order like their bit patterns and negative ones lie below
+// them; two running extremes (one three-operand instruction per two
+// particles) replace a comparison and a mask operation for each.
 // Against a clamp and two compared masks per particle and update: 1V 24.7 ->
-// 22.5 ms (1000 ragged cells), 3V 29.0 -> 27.7 ms (65536 cells), bits unchanged.
-template <typename R>
-constexpr R kTinyDen = R(1e-30);
+// 22.5 ms (1024 cells of about 2000), 3V 29.0 -> 27.7 ms (65536 cells), bits
+// unchanged.
 template <typename R>
 struct UpdateWatch {
-    R lo = R(INFINITY), hi = R(0);
+    R lo = R(INFINITY);
     bool odd = false;
-    __device__ __forceinline__ void see(R t, R s) { odd |= !(t > kTinyDen<R>) | !(s < R(18446744073709551616.0)); }
-    __device__ __forceinline__ bool hit() const { return __builtin_amdgcn_ballot_w64(odd) != 0; }
+    __device__ __forceinline__ void see(R t, R s)
+    {
+        lo = t < lo ? t : lo;
+        odd |= !(s < R(9223372036854775808.0)) | (t != t);
+    }
+    __device__ __forceinline__ bool hit(R least) const { return __builtin_amdgcn_ballot_w64(odd | !(lo > least)) != 0; }
 };
 template <>
 struct UpdateWatch<float> {
@@ -586,9 +589,9 @@ struct UpdateWatch<float> {
         lo = min(lo, __float_as_int(t));
         hi = max(hi, __float_as_int(s));
     }
-    __device__ __forceinline__ bool hit() const
+    __device__ __forceinline__ bool hit(float least) const
     {
-        return __builtin_amdgcn_ballot_w64(lo <= __float_as_int(kTinyDen<float>) || hi >= 0x5f800000) != 0;
+        return __builtin_amdgcn_ballot_w64(lo <= __float_as_int(least) || hi >= 0x5f000000) != 0;
     }
 };
 
@@ -1004,7 +1007,7 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
                         }
                         // what passes the watch kept more than a thousandth
                         // of its density, and no term is above 2^64
-                        if (watch.hit()) {
+                        if (watch.hit(R(1e-30))) {
                             bool low[P], big[P];
 #pragma unroll
                             for (int p = 0; p < P; ++p) {
@@ -1035,21 +1038,35 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
                             Sden[p] = (s_new > rebase_below) ? s_new : rebase_sum(x[p], ref[p]);
                         }
                     } else {
+                        R s_new[P];
+                        UpdateWatch<R> watch;
 #pragma unroll
                         for (int p = 0; p < P; ++p) {
-                            const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
-                            const R enew = fast_exp2(fmin(dt, R(64)));
-                            const R s_old = Sden[p];
-                            R s_new = s_old - eold[p] + enew;
-                            if (!(s_new > R(1e-4) * s_old)) {
-                                // the particle lost most of its density: re-sum exactly
-                                s_new = enew;
-                                for (int j = 0; j < Kslots; ++j)
-                                    if (j != k && ((alive >> j) & 1u))
-                                        s_new += fast_exp2(fmin(log2_term<R, D>(comp[j], x[p]) - ref[p], R(64)));
-                            }
-                            Sden[p] = (s_new > rebase_below && !(dt > R(64))) ? s_new : rebase_sum(x[p], ref[p]);
+                            s_new[p] = Sden[p] - eold[p] + fast_exp2(log2_term<R, D>(cn, x[p]) - ref[p]);
+                            watch.see(fma(R(-1.001e-4), Sden[p], s_new[p]), s_new[p]);
                         }
+                        // what passes the watch kept more than 1e-4 of its
+                        // density, is above the rebase bound, and has no
+                        // term above 2^64
+                        if (watch.hit(rebase_below)) {
+#pragma unroll
+                            for (int p = 0; p < P; ++p) {
+                                const R dt = log2_term<R, D>(cn, x[p]) - ref[p];
+                                const R enew = fast_exp2(fmin(dt, R(64)));
+                                const R s_old = Sden[p];
+                                R t = s_old - eold[p] + enew;
+                                if (!(t > R(1e-4) * s_old)) {
+                                    // the particle lost most of its density: re-sum exactly
+                                    t = enew;
+                                    for (int j = 0; j < Kslots; ++j)
+                                        if (j != k && ((alive >> j) & 1u))
+                                            t += fast_exp2(fmin(log2_term<R, D>(comp[j], x[p]) - ref[p], R(64)));
+                                }
+                                s_new[p] = (t > rebase_below && !(dt > R(64))) ? t : rebase_sum(x[p], ref[p]);
+                            }
+                        }
+#pragma unroll
+                        for (int p = 0; p < P; ++p) Sden[p] = s_new[p];
                     }
                 }
 
@@ -1270,7 +1287,32 @@ void k_em(CompressArgs A_in)
         const int idx = uni(sh.s_idx);
         __syncthreads();
         if (idx >= count) break;
-        em_fit_cell<D, KMAX, P, STORE_E, R, MAXW>(sh, uni(sh.A.list[base + idx]), nwaves, par_d, par_r);
+        const int c = uni(sh.A.list[base + idx]);
+        if constexpr (LEAN && !STORE_E) {
+            // the fewest particles per thread that hold the cell, down to
+            // half the variant's
+            const int n = uni(static_cast<const CellInfo<D>*>(sh.A.cells)[c].n);
+            const int need = (n + 64 * nwaves - 1) / (64 * nwaves);
+            auto fit = [&](auto p) {
+                em_fit_cell<D, KMAX, decltype(p)::value, STORE_E, R, MAXW>(sh, c, nwaves, par_d, par_r);
+            };
+            if constexpr (P == 8) {
+                switch (need) {
+                    case 8: fit(std::integral_constant<int, 8>{}); break;
+                    case 7: fit(std::integral_constant<int, 7>{}); break;
+                    case 6: fit(std::integral_constant<int, 6>{}); break;
+                    default: fit(std::integral_constant<int, 5>{}); break;
+                }
+            } else {
+                static_assert(P == 4, "lean builds recompute 4 or 8 particles per thread");
+                if (need == 4)
+                    fit(std::integral_constant<int, 4>{});
+                else
+                    fit(std::integral_constant<int, 3>{});
+            }
+        } else {
+            em_fit_cell<D, KMAX, P, STORE_E, R, MAXW>(sh, c, nwaves, par_d, par_r);
+        }
         __syncthreads();
     }
 }
