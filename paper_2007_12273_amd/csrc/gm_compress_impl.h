@@ -936,7 +936,9 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
 #pragma unroll
                         for (int p = 0; p < P; ++p) accumulate(p, e.get(p, k), Sden[p]);
                     } else {
-                        const CompState<R, D> ck = comp[k];
+                        CompState<R, D> ck = comp[k];
+#pragma unroll
+                        for (int i = 0; i < D; ++i) ck.mu[i] = ckmu[i];  // the same value: one difference per particle
 #pragma unroll
                         for (int p = 0; p < P; ++p) {
                             eold[p] = fast_exp2(fmin(log2_term<R, D>(ck, x[p]) - ref[p], R(64)));
