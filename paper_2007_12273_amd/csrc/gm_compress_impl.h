@@ -45,6 +45,8 @@
 // log-sum-exp).
 #pragma once
 
+#include <atomic>
+
 #include "gm_device.h"
 #include "gm_launch.h"
 
@@ -1263,12 +1265,6 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
     }
 }
 
-template <int D, int KMAX, typename R>
-constexpr int em_span_waves_per_simd()
-{
-    return D == 1 && KMAX == 8 && std::is_same<R, float>::value ? 3 : 1;
-}
-
 template <int D, int KMAX, int P, bool STORE_E, typename R, bool LEAN>
 __global__ __launch_bounds__(LEAN ? kEmLeanThreads : kEmMaxThreads, (em_min_waves_per_simd<R, LEAN, P, STORE_E>()))
 void k_em(CompressArgs A_in)
@@ -1325,8 +1321,9 @@ void k_em(CompressArgs A_in)
 // fewest particles per thread that hold the cell; a workgroup that comes to
 // a narrower bucket goes on with its first waves, the others end and leave
 // their registers to the workgroups still waiting.
-template <int D, int KMAX, int PHI, typename R>
-__global__ __launch_bounds__(kEmMaxThreads, (em_span_waves_per_simd<D, KMAX, R>()))
+// WPS: waves per SIMD the build leaves registers for.
+template <int D, int KMAX, int PHI, typename R, int WPS>
+__global__ __launch_bounds__(kEmMaxThreads, WPS)
 void k_em_span(CompressArgs A_in, int b_hi, int b_lo)
 {
     constexpr int MAXW = em_max_waves(false);
@@ -2164,13 +2161,14 @@ constexpr int em_span_max_per_thread()
     return m;
 }
 
-template <int D, int KMAX, typename R>
-int launch_span_k(const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t n_cells, hipStream_t st)
+// workgroups of `waves` waves of a k_em_span build the device holds at once
+template <int D, int KMAX, int PHI, typename R, int WPS>
+int64_t resident_spans(int waves)
 {
-    constexpr int PHI = em_span_max_per_thread<D, KMAX, R>();
-    static int resident[kEmMaxWaves + 1] = {};  // workgroups the device holds at once, per waves
-    auto kern = k_em_span<D, KMAX, PHI, R>;
-    if (resident[waves] == 0) {
+    auto kern = k_em_span<D, KMAX, PHI, R, WPS>;
+    static std::atomic<int> known[kEmMaxWaves + 1];
+    int r = known[waves].load(std::memory_order_relaxed);
+    if (r == 0) {
         int dev = 0, ncu = 0, nb = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -2179,14 +2177,39 @@ int launch_span_k(const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t 
                 hipSuccess ||
             nb < 1)
             nb = 1;
-        resident[waves] = nb * ncu;
+        r = nb * ncu;
+        known[waves].store(r, std::memory_order_relaxed);
     }
-    // twice the resident workgroups, so that some wait for the registers of
-    // waves that end where a workgroup narrows
-    int64_t grid = 2 * (int64_t)resident[waves];
-    if (grid > n_cells) grid = n_cells;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * waves), 0, st, a, b_hi, b_lo);
-    return hipGetLastError() == hipSuccess ? 0 : -1;
+    return r;
+}
+
+// Builds of k_em_span.  With eight slots an FP32 wave fits in 168 registers
+// (a few values of cells with seven and eight particles per thread spill), so three
+// waves share a SIMD: 65536 3V cells 23.1 ms against 27.1 ms with two, 1024 1V
+// cells of about 2000 24.5 against 27.1 ms.  In 3V a batch that two waves per
+// SIMD hold as a whole gains nothing from that, and the build for two spills
+// less (256 cells of 512: 3.55 against 3.61 ms).  With sixteen slots and up to
+// four particles per thread three waves would fit as well, but those batches
+// wait for the slowest fits of larger cells (4096 cells of about 1000: no
+// difference on four batches).
+template <int D, int KMAX, typename R>
+int launch_span_k(const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t n_cells, hipStream_t st)
+{
+    constexpr int PHI = em_span_max_per_thread<D, KMAX, R>();
+    constexpr bool kThree = KMAX == 8 && std::is_same<R, float>::value;
+    auto launch = [&](auto kern, int64_t resident) {
+        if (resident < 0) return -1;
+        // twice the resident workgroups, so that some wait for the registers of
+        // waves that end where a workgroup narrows
+        const int64_t grid = 2 * resident < n_cells ? 2 * resident : n_cells;
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * waves), 0, st, a, b_hi, b_lo);
+        return hipGetLastError() == hipSuccess ? 0 : -1;
+    };
+    if constexpr (kThree)
+        if (D == 1 || n_cells > resident_spans<D, KMAX, PHI, R, 1>(waves))
+            return launch(k_em_span<D, KMAX, PHI, R, 3>, resident_spans<D, KMAX, PHI, R, 3>(waves));
+    if constexpr (!kThree || D == 3)
+        return launch(k_em_span<D, KMAX, PHI, R, 1>, resident_spans<D, KMAX, PHI, R, 1>(waves));
 }
 
 template <int D, typename R>
