@@ -51,3 +51,28 @@ def test_three_wave_build_equals_one_launch_per_bucket():
     for k in built_in:
         assert np.array_equal(built_in[k], per_bucket[k], equal_nan=True), k
     assert (built_in["K"] > 0).all()
+
+
+@pytest.mark.parametrize("D,n_cells", [(3, 4097), (1, 5121)])
+def test_plan_of_one_workgroup_and_of_many_fit_the_same_cells(D, n_cells):
+    """4096 cells are planned by one workgroup, more by several: the common
+    cells' records are equal bit for bit (cells of every bucket, empty ones
+    and some too small to fit among them)."""
+    from paper_2007_12273_amd import api
+    rng = np.random.default_rng(4)
+    counts = rng.integers(11, 80, size=n_cells)
+    counts[::97] = 0
+    counts[1::97] = 3
+    for i, n in enumerate((300, 700, 1100, 1700, 2100, 2700, 3500, 4000, 5000, 9000)):
+        counts[2 + 300 * i] = n
+    off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    v = rng.normal(size=(off[-1], D))
+    a = rng.uniform(0.5, 1.5, size=off[-1])
+    kw = dict(seed=5, max_sweeps=6)
+    vt, at, ot = to_gpu(dict(v=v, alpha=a, cell_off=off))
+    many = host(api.compress(vt, at, ot, 8, **kw))
+    vt, at, ot = to_gpu(dict(v=v[:off[4096]], alpha=a[:off[4096]], cell_off=off[:4097]))
+    one = host(api.compress(vt, at, ot, 8, **kw))
+    for k in one:
+        assert np.array_equal(one[k], many[k][:4096], equal_nan=True), k
+    assert (one["K"] > 0).sum() > 3900
