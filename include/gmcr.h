@@ -184,18 +184,22 @@ int gm_compress_noalloc(const double* v, const double* alpha, const int64_t* cel
  * gm_compress runs the EM iterations in twelve length buckets (largest
  * cells: 64, 128, 256, 512, 1024, 1536, 2048, 2560, 3072, 3584, 4096, 8192
  * particles at kmax <= 8; 128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048,
- * 2560, 4096, 8192 at kmax > 8), each a
- * persistent launch whose workgroups take cells from a queue, each on a
- * library stream of its own (cells of more than 8192 particles run on the
- * caller's stream), so that all thirteen launches run concurrently.  The
- * launches of buckets whose workgroups fill a compute unit's register file
+ * 2560, 4096, 8192 at kmax > 8), whose
+ * persistent workgroups take cells from a queue.  The built-in plan runs in
+ * a few launches that walk several buckets each (four or five streams; with
+ * FP64 iterations a cell of up to 2048 particles runs on more waves than
+ * the plan's codes, the variants of a plan installed by hand, say).  A plan
+ * tuned or installed by hand runs one launch per bucket, each on a library
+ * stream of its own (cells of more than 8192 particles run on the caller's
+ * stream), so that all thirteen launches run concurrently.  The launches of
+ * buckets whose workgroups fill a compute unit's register file
  * (eight or more waves of a standard build, sixteen of a lean one) are
  * released first and the others about 40 us later, after a one-wave wait
  * kernel on the caller's stream that ends at once when those buckets hold
  * no cell.  HIP
  * maps streams onto GPU_MAX_HW_QUEUES hardware queues per process (default
- * 4): run with GPU_MAX_HW_QUEUES >= 13 (set before the HIP runtime starts)
- * for them to overlap; with fewer, launches sharing a queue run one after
+ * 4): run such a plan with GPU_MAX_HW_QUEUES >= 13 (set before the HIP
+ * runtime starts) for them to overlap; with fewer, launches sharing a queue run one after
  * another (same results, longer EM phase).  The same holds for a captured
  * compress: a HIP graph replay runs the graph's parallel launches on the
  * few streams of the runtime's graph executor (three or four hardware

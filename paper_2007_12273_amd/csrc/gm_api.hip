@@ -66,12 +66,14 @@ struct WsLayout {
     size_t plan, cells, list, init, total;
 };
 
-// Streams of the EM phase, one set per device: every length bucket runs on
-// a library stream of its own and the big-cell launch on the caller's
-// stream, so the thirteen launches can run concurrently.  HIP maps streams
-// onto GPU_MAX_HW_QUEUES hardware queues (default 4); they only all run at
-// once with at least thirteen.  With fewer, streams share queues
-// round-robin and the launches sharing a queue run one after another.
+// Streams of the EM phase, one set per device.  The built-in plan's launches
+// use three of them and the caller's (a few more in FP64 and 1V with sixteen
+// slots), so they run concurrently on HIP's default of four hardware queues.
+// A plan tuned or installed by hand runs every length bucket on a library
+// stream of its own and the big-cell launch on the caller's: those thirteen
+// launches only all run at once with GPU_MAX_HW_QUEUES of at least thirteen;
+// with fewer, streams share queues round-robin and the launches sharing a
+// queue run one after another.
 constexpr int kLanes = gm::kNumBuckets + 1;
 struct Fork {
     hipStream_t aux[kLanes - 1];
@@ -147,7 +149,7 @@ EmPlan default_plan(int D, int kt, bool fp64)
 {
     EmPlan p;
     for (int b = 0; b < gm::kNumBuckets; ++b) {
-        const gm::EmDefault d = D == 1 ? gm::em_default<1>(kt, fp64, b) : gm::em_default<3>(kt, fp64, b);
+        const gm::EmDefault d = D == 1 ? gm::em_reported<1>(kt, fp64, b) : gm::em_reported<3>(kt, fp64, b);
         p.per_thread[b] = (int8_t)d.per_thread;
         p.mode[b] = (int8_t)d.mode;
         p.waves[b] = (int8_t)d.waves;
@@ -204,7 +206,8 @@ int launch_em_big(int D, bool fp64, int kt, gm::CompressArgs& a, int64_t n_cells
 // buckets each (k_em_span), plus those of the buckets whose densities do not
 // stay in registers and of the larger cells.  A launch of 8, 6, 4 or 1 waves
 // per workgroup takes the buckets of cells that many waves or a little fewer
-// fit (the 4-wave launch every narrower one too), so no cell waits behind
+// fit (the 4-wave launch every narrower one too), with FP64 iterations on
+// more waves than the plan's codes say (em_default), so no cell waits behind
 // another bucket's slowest fit whatever hardware queues the streams share:
 // with HIP's default of four, one launch per bucket ran up to four of them
 // one after another.  Released as in launch_em_phase.
@@ -219,9 +222,8 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
         return fp64 ? gm::launch_compress_span_d3_double(kt, a, waves, hi, lo, n_cells, s)
                     : gm::launch_compress_span_d3_float(kt, a, waves, hi, lo, n_cells, s);
     };
-    auto spanned = [&](int b) {
-        return D == 1 ? gm::em_default<1>(kt, fp64, b).span : gm::em_default<3>(kt, fp64, b).span;
-    };
+    auto run_as = [&](int b) { return D == 1 ? gm::em_default<1>(kt, fp64, b) : gm::em_default<3>(kt, fp64, b); };
+    auto spanned = [&](int b) { return run_as(b).span; };
     // buckets of each launch width: W in (less, waves]; the 4-wave launch
     // down to the narrowest
     constexpr int kWidths = 4;
@@ -239,7 +241,7 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
         hi[w] = -1;
         lo[w] = gm::kNumBuckets;
         for (int b = 0; b < gm::kNumBuckets; ++b)
-            if (spanned(b) && p.waves[b] <= kWaves[w] && p.waves[b] > kAbove[w]) {
+            if (spanned(b) && run_as(b).waves <= kWaves[w] && run_as(b).waves > kAbove[w]) {
                 hi[w] = std::max(hi[w], b);
                 lo[w] = std::min(lo[w], b);
                 if (kWaves[w] > 4) heavy_mask |= 1u << b;
@@ -413,9 +415,9 @@ int compress_run(const double* v, const double* alpha, const int64_t* cell_off, 
     int rc = D == 1 ? gm::launch_compress_pre_d1(a, st) : gm::launch_compress_pre_d3(a, st);
     if (rc) return GM_EHIP;
     prof_mark(EV_EM, st);
-    // Length buckets run concurrently on the caller's stream and three
-    // auxiliary streams (fork/join through events, so the sequence can be
-    // captured into a graph), in the order and lanes of the launch plan.
+    // Length buckets run concurrently on the caller's and library streams
+    // (fork/join through events, so the sequence can be captured into a
+    // graph), as the launch plan says.
     {
         const EmPlan* tuned = plan_slot(D, kt, fp64, init && init->K, false);
         const EmPlan p = tuned ? *tuned : default_plan(D, kt, fp64);

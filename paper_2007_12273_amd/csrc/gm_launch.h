@@ -91,7 +91,8 @@ constexpr int kEmMaxThreads = 512;
 constexpr int kEmLeanThreads = 1024;
 __host__ __device__ constexpr int em_max_waves(bool lean) { return (lean ? kEmLeanThreads : kEmMaxThreads) / 64; }
 constexpr int kEmMaxWaves = kEmLeanThreads / 64;
-// The built-in plan's variant of bucket b.
+// The built-in plan's variant of bucket b, as the plan reports it
+// (em_reported) and as its launches run it (em_default).
 struct EmDefault {
     int per_thread;  // most particles per thread any cell of the bucket needs
     int waves;
@@ -141,6 +142,20 @@ __host__ __device__ constexpr bool resident8_bucket(int D, int kt, bool fp64, in
 }
 
 template <int D>
+__host__ __device__ constexpr EmDefault em_reported(int kt, bool fp64, int b)
+{
+    const Bucket& c = bucket_cfg(kt, b);
+    if (resident8_bucket(D, kt, fp64, b)) return {c.max_n / (64 * 8), 8, kModeStoreE, true};
+    if (chain_bucket(kt, fp64, b)) {
+        // the lean builds recompute 4 or 8 particles per thread
+        const int P = c.max_n <= kEmLeanThreads * 4 ? 4 : 8;
+        return {P, (c.max_n + 64 * P - 1) / (64 * P), kModeLean, false};
+    }
+    if (four_wave_bucket(kt, fp64, b)) return {c.max_n / 256, 4, kModeStoreE, true};
+    return {c.per_thread, c.waves, c.store_e ? kModeStoreE : 0, c.store_e && !fp64};
+}
+
+template <int D>
 __host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
 {
     const Bucket& c = bucket_cfg(kt, b);
@@ -154,14 +169,7 @@ __host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
         const int P = c.max_n <= 64 * most ? c.max_n / 64 : most;
         return {P, D == 3 && c.max_n > 1024 ? 8 : (c.max_n + 64 * P - 1) / (64 * P), kModeStoreE, true};
     }
-    if (resident8_bucket(D, kt, fp64, b)) return {c.max_n / (64 * 8), 8, kModeStoreE, true};
-    if (chain_bucket(kt, fp64, b)) {
-        // the lean builds recompute 4 or 8 particles per thread
-        const int P = c.max_n <= kEmLeanThreads * 4 ? 4 : 8;
-        return {P, (c.max_n + 64 * P - 1) / (64 * P), kModeLean, false};
-    }
-    if (four_wave_bucket(kt, fp64, b)) return {c.max_n / 256, 4, kModeStoreE, true};
-    return {c.per_thread, c.waves, c.store_e ? kModeStoreE : 0, c.store_e && !fp64};
+    return em_reported<D>(kt, fp64, b);
 }
 
 // k_em_span's workgroups only narrow on their way down the buckets
