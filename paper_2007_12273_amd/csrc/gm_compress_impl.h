@@ -693,9 +693,10 @@ __device__ __forceinline__ void em_fit_cell(EmShared<D, KMAX, R, MAXW>& sh, int 
 #pragma clang fp contract(off)
     constexpr int NT = ntri(D);
     constexpr int NS = 1 + D + NT;
+    if constexpr (MAXW == 1) nwaves = 1;
     const int nthreads = 64 * nwaves;
     const int tid = threadIdx.x;
-    const int wid = uni(tid >> 6), lane = tid & 63;
+    const int wid = MAXW == 1 ? 0 : uni(tid >> 6), lane = tid & 63;
     const double T = 0.5 * D * (D + 3);
     const double halfT = 0.5 * T;
     const CompressArgs& A = sh.A;
@@ -1360,11 +1361,12 @@ void k_em(CompressArgs A_in)
 // a narrower bucket goes on with its first waves, the others end and leave
 // their registers to the workgroups still waiting.
 // WPS: waves per SIMD the build leaves registers for.
-template <int D, int KMAX, int PHI, typename R, int WPS>
-__global__ __launch_bounds__(kEmMaxThreads, WPS)
+// MAXW: waves of a workgroup at most; one for the launch of the narrowest
+// cells, whose build then has no barriers and one copy of the parameters.
+template <int D, int KMAX, int PHI, typename R, int WPS, int MAXW>
+__global__ __launch_bounds__(64 * MAXW, WPS)
 void k_em_span(CompressArgs A_in, int b_hi, int b_lo)
 {
-    constexpr int MAXW = em_max_waves(false);
     __shared__ EmShared<D, KMAX, R, MAXW> sh;
     const int tid = threadIdx.x;
     const int wid = uni(tid >> 6);
@@ -2200,10 +2202,10 @@ constexpr int em_span_max_per_thread()
 }
 
 // workgroups of `waves` waves of a k_em_span build the device holds at once
-template <int D, int KMAX, int PHI, typename R, int WPS>
+template <int D, int KMAX, int PHI, typename R, int WPS, int MAXW>
 int64_t resident_spans(int waves)
 {
-    auto kern = k_em_span<D, KMAX, PHI, R, WPS>;
+    auto kern = k_em_span<D, KMAX, PHI, R, WPS, MAXW>;
     static std::atomic<int> known[kEmMaxWaves + 1];
     int r = known[waves].load(std::memory_order_relaxed);
     if (r == 0) {
@@ -2230,11 +2232,14 @@ int64_t resident_spans(int waves)
 // four particles per thread three waves would fit as well, but those batches
 // wait for the slowest fits of larger cells (4096 cells of about 1000: no
 // difference on four batches).
+//
+// The one-wave build of the narrowest launch: 32 1V cells of 156 0.691 ->
+// 0.661 ms, 256 3V cells of 512 3.48 -> 3.40 ms; no gain where three waves
+// share a SIMD, with sixteen slots or with FP64 iterations.
 template <int D, int KMAX, typename R>
 int launch_span_k(const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t n_cells, hipStream_t st)
 {
-    constexpr int PHI = em_span_max_per_thread<D, KMAX, R>();
-    constexpr bool kThree = KMAX == 8 && std::is_same<R, float>::value;
+    constexpr int PHI = em_span_max_per_thread<D, KMAX, R>(), MAXW = em_max_waves(false);
     auto launch = [&](auto kern, int64_t resident) {
         if (resident < 0) return -1;
         // twice the resident workgroups, so that some wait for the registers of
@@ -2243,13 +2248,20 @@ int launch_span_k(const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t 
         hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * waves), 0, st, a, b_hi, b_lo);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     };
-    bool three = kThree;
-    if constexpr (kThree && D == 3) three = n_cells > resident_spans<D, KMAX, PHI, R, 1>(waves);
-    if constexpr (kThree)
-        if (three) return launch(k_em_span<D, KMAX, PHI, R, 3>, resident_spans<D, KMAX, PHI, R, 3>(waves));
-    if constexpr (!kThree || D == 3)
-        return launch(k_em_span<D, KMAX, PHI, R, 1>, resident_spans<D, KMAX, PHI, R, 1>(waves));
-    return -1;
+    if constexpr (KMAX == 8 && std::is_same<R, float>::value) {
+        if constexpr (D == 1) {
+            if (waves == 1) return launch(k_em_span<D, KMAX, PHI, R, 3, 1>, resident_spans<D, KMAX, PHI, R, 3, 1>(1));
+            return launch(k_em_span<D, KMAX, PHI, R, 3, MAXW>, resident_spans<D, KMAX, PHI, R, 3, MAXW>(waves));
+        } else {
+            const int64_t two = resident_spans<D, KMAX, PHI, R, 1, MAXW>(waves);
+            if (n_cells > two)
+                return launch(k_em_span<D, KMAX, PHI, R, 3, MAXW>, resident_spans<D, KMAX, PHI, R, 3, MAXW>(waves));
+            if (waves == 1) return launch(k_em_span<D, KMAX, PHI, R, 1, 1>, resident_spans<D, KMAX, PHI, R, 1, 1>(1));
+            return launch(k_em_span<D, KMAX, PHI, R, 1, MAXW>, two);
+        }
+    } else {
+        return launch(k_em_span<D, KMAX, PHI, R, 1, MAXW>, resident_spans<D, KMAX, PHI, R, 1, MAXW>(waves));
+    }
 }
 
 template <int D, typename R>
