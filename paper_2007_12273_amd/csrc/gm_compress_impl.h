@@ -1,12 +1,14 @@
 // gm_compress_impl.h -- per-cell adaptive EM-GM for gfx950.
 //
-// Three kernels per compress call (plus the length-bucket plan):
+// Three steps per compress call (plus the length-bucket plan):
 //   k_moments  one wave per cell, FP64: W = sum alpha, P = sum alpha v,
 //              S = sum alpha v v^T, mean m = P / W, covariance C about m (two
 //              passes); classifies the cell (invalid / empty / small or
-//              singular -> closed form / EM) and bins EM cells by length.
+//              singular -> closed form / EM); the k_plan_* kernels then list
+//              the EM cells by length.
 //   k_em       the hot loop.  Persistent workgroups pull cells of one length
-//              bucket from a queue.  Centred FP32 velocities, normalised
+//              bucket from a queue (k_em_span: of several buckets, from the
+//              largest down).  Centred FP32 velocities, normalised
 //              weights and every (particle, component) density term stay in
 //              VGPRs for the whole fit; LDS carries only the component
 //              parameters and the cross-wave partial sums.  Writes the
