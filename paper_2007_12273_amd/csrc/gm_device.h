@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "../../include/gmcr.h"
+#include "gm_math.h"
 
 namespace gm {
 
@@ -337,123 +338,6 @@ __device__ __forceinline__ R tri_log2diag(const R (&L)[ntri(D)])
     } else {
         return log2(L[0] * L[3] * L[5]);
     }
-}
-
-// FP64 reciprocal, reciprocal square root and log2 of the EM iterations, to
-// about one unit in the last place: Newton steps on the hardware's estimates
-// (5 and 9 instructions against 12 of the correctly rounded division and 27
-// of the square root and division), and for log2 the series of atanh,
-// log2(m) = (2 / ln 2) (s + s^3/3 + s^5/5 + ...) with s = (m - 1) / (m + 1),
-// m in [sqrt(1/2), sqrt 2): |s| <= 0.172, so the eleven terms kept leave
-// 2e-18.  For finite positive arguments; log2 hands others to the library.
-__device__ __forceinline__ double rcp64(double x)
-{
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return fma(r, fma(-x, r, 1.0), r);
-}
-
-__device__ __forceinline__ double rsq64(double x)
-{
-    double y = __builtin_amdgcn_rsq(x);
-    y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-    return fma(0.5 * y, fma(-x * y, y, 1.0), y);
-}
-
-__device__ __forceinline__ double log2_64(double x)
-{
-    if (!(x > 0.0 && x <= 1.7976931348623157e308)) return log2(x);
-    double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
-    int e = __builtin_amdgcn_frexp_exp(x);
-    const bool low = m < 0.70710678118654752440;
-    m = low ? m + m : m;
-    e = low ? e - 1 : e;
-    const double s = (m - 1.0) * rcp64(m + 1.0);
-    const double z = s * s;
-    double q = 1.0 / 21.0;
-    q = fma(q, z, 1.0 / 19.0);
-    q = fma(q, z, 1.0 / 17.0);
-    q = fma(q, z, 1.0 / 15.0);
-    q = fma(q, z, 1.0 / 13.0);
-    q = fma(q, z, 1.0 / 11.0);
-    q = fma(q, z, 1.0 / 9.0);
-    q = fma(q, z, 1.0 / 7.0);
-    q = fma(q, z, 1.0 / 5.0);
-    q = fma(q, z, 1.0 / 3.0);
-    const double t = 2.88539008177792681472 * s;  // 2 / ln 2
-    return (double)e + fma(t * z, q, t);
-}
-
-// The Box-Muller functions of the sampling, each to within one unit in the
-// last place, without the library's argument cases:
-//   log_64       x in (0, 1]: the same series in natural units, the quotient
-//                s corrected by its own remainder, ln 2 in two parts
-//   sqrt_64      x >= 0: rsq64 and one correction by the remainder
-//   sincospi_64  sin and cos of pi a, a in [0, 2): a = q/2 + f exactly, |f| <=
-//                1/4, and the Taylor series of both about 0 (nine terms leave
-//                1e-19 and 2e-18), pi in two parts
-__device__ __forceinline__ double log_64(double x)
-{
-    double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
-    int e = __builtin_amdgcn_frexp_exp(x);
-    const bool low = m < 0.70710678118654752440;
-    m = low ? m + m : m;
-    e = low ? e - 1 : e;
-    const double n = m - 1.0, d = m + 1.0, r = rcp64(d);
-    double s = n * r;
-    s = fma(r, fma(-s, d, n), s);
-    const double z = s * s;
-    double q = 1.0 / 21.0;
-    q = fma(q, z, 1.0 / 19.0);
-    q = fma(q, z, 1.0 / 17.0);
-    q = fma(q, z, 1.0 / 15.0);
-    q = fma(q, z, 1.0 / 13.0);
-    q = fma(q, z, 1.0 / 11.0);
-    q = fma(q, z, 1.0 / 9.0);
-    q = fma(q, z, 1.0 / 7.0);
-    q = fma(q, z, 1.0 / 5.0);
-    q = fma(q, z, 1.0 / 3.0);
-    const double t = s + s;
-    const double small = fma(t * z, q, (double)e * 2.31904681384629955842e-17);
-    return fma((double)e, 0.693147180559945286227, t + small);
-}
-
-__device__ __forceinline__ double sqrt_64(double x)
-{
-    const double y = rsq64(x);
-    const double g = x * y;
-    return x > 0.0 ? fma(0.5 * y, fma(-g, g, x), g) : 0.0;
-}
-
-__device__ __forceinline__ void sincospi_64(double a, double& sn, double& cs)
-{
-    const double h = __builtin_rint(a + a);
-    const int q = (int)h;
-    const double f = fma(-0.5, h, a);
-    const double z = f * f;
-    double p = 7.95205400147551261113e-07;
-    p = fma(p, z, -2.19153534478302172922e-05);
-    p = fma(p, z, 4.66302805767612553716e-04);
-    p = fma(p, z, -7.37043094571435044443e-03);
-    p = fma(p, z, 8.21458866111282326461e-02);
-    p = fma(p, z, -5.99264529320792105338e-01);
-    p = fma(p, z, 2.55016403987734552317e+00);
-    p = fma(p, z, -5.16771278004997025590e+00);
-    p = fma(p, z, 1.22464679914735320717e-16);
-    const double s0 = fma(f, p, f * 3.14159265358979311600);
-    double c = 4.30306958703294729370e-06;
-    c = fma(c, z, -1.04638104924845704697e-04);
-    c = fma(c, z, 1.92957430940392314460e-03);
-    c = fma(c, z, -2.58068913900140611828e-02);
-    c = fma(c, z, 2.35330630358893205800e-01);
-    c = fma(c, z, -1.33526276885458949906e+00);
-    c = fma(c, z, 4.05871212641676848421e+00);
-    c = fma(c, z, -4.93480220054467899615e+00);
-    const double c0 = fma(c, z, 1.0);
-    const bool odd = (q & 1) != 0;
-    const double u = odd ? c0 : s0, w = odd ? s0 : c0;
-    sn = (q & 2) ? -u : u;
-    cs = ((q + 1) & 2) ? -w : w;
 }
 
 template <typename R>
