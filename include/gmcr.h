@@ -578,9 +578,10 @@ int gm_deposit(const double* x, const double* w, const int64_t* cell_off, int64_
  * it sits on the cell's edge) and nonsingular; in 2D it is not dominant but
  * nonsingular for generic positions.  The iteration's scalars stay on the
  * device; the call reads them back once (meshes of up to about 131072 cells,
- * with nx <= 512 in 2D, solved in one launch) or, on other meshes, once per
- * 8 iterations and per restart, so it synchronises `stream` and cannot be
- * captured in a graph; the empty cell check and GM_ENOCONV come from those
+ * with nx <= 512 in 2D, solved in one launch that needs a free CU per 1024
+ * cells or less) or, on other meshes and where such solves of other threads
+ * hold the CUs, once per 8 iterations and per restart, so it synchronises
+ * `stream` and cannot be captured in a graph; the empty cell check and GM_ENOCONV come from those
  * reads, after kernels on the workspace were enqueued.  iters_out (iterations) and resid_out (final
  * true relative residual) are host pointers, may be NULL.  Returns
  * GM_ENOCONV, with the weights corrected by the last iterate, when the
@@ -601,6 +602,19 @@ int gm_gauss_correct(const double* x, double* w, const int64_t* cell_off, int64_
  * threads at once, nor during stream capture. */
 void gm_profile_enable(int on);
 int gm_profile_read(double* ms, int n);
+
+/* gm_gauss_correct with its one-launch solve's limits set and its path
+ * reported (for tests of both paths).  diag may be NULL. */
+typedef struct gm_gauss_diag {
+    int32_t wait_us;  /* in: longest wait of a workgroup for another in microseconds; 0: the
+                         solve gives up at its first exchange; < 0: the built-in limit */
+    int32_t places;   /* in: at most this many of the device's CUs; < 0: all */
+    int32_t path;     /* out: 0 launch by launch alone, 1 in one launch, 2 in one launch without
+                         convergence, then launch by launch */
+} gm_gauss_diag;
+int gm_gauss_correct_diag(const double* x, double* w, const int64_t* cell_off, int64_t n_cells, int32_t dx,
+                          int32_t nx, const double* dep_target, double tol, int32_t max_iter, void* ws,
+                          size_t ws_bytes, void* stream, int32_t* iters_out, double* resid_out, gm_gauss_diag* diag);
 
 /* Human-readable text for a return code. */
 const char* gm_strerror(int code);

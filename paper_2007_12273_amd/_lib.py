@@ -37,6 +37,10 @@ class GmMix(ctypes.Structure):
                                  "visits")]
 
 
+class GmGaussDiag(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("wait_us", "places", "path")]
+
+
 class GmInit(ctypes.Structure):
     _fields_ = [(n, P) for n in ("K", "omega", "mu", "sigma")]
 
@@ -45,7 +49,7 @@ EXPORTS = ("gm_opts_default", "gm_compress_workspace", "gm_compress", "gm_compre
            "gm_compress_warm_workspace", "gm_warm_model_kmax", "gm_warm_infer", "gm_autotune", "gm_autotune_set", "gm_autotune_reset",
            "gm_autotune_get", "gm_autotune_save", "gm_autotune_load",
            "gm_reconstruct_workspace", "gm_reconstruct_tensor", "gm_project", "gm_gauss_workspace", "gm_deposit",
-           "gm_gauss_correct", "gm_compress_standard_workspace", "gm_compress_standard",
+           "gm_gauss_correct", "gm_gauss_correct_diag", "gm_compress_standard_workspace", "gm_compress_standard",
            "gm_reconstruct", "gm_warm_param_count", "gm_warm_create", "gm_warm_destroy", "gm_warm_get_params",
            "gm_warm_set_params", "gm_warm_gradients", "gm_warm_save", "gm_warm_load", "gm_warm_features", "gm_warm_forward_workspace",
            "gm_warm_forward", "gm_warm_decode", "gm_warm_targets", "gm_warm_train_step", "gm_warm_train_workspace",
@@ -115,6 +119,8 @@ def load():
     L.gm_gauss_correct.argtypes = [P, P, P, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, P, ctypes.c_double,
                                    ctypes.c_int32, P, ctypes.c_size_t, P, P, P]
     L.gm_gauss_correct.restype = ctypes.c_int
+    L.gm_gauss_correct_diag.argtypes = L.gm_gauss_correct.argtypes + [ctypes.POINTER(GmGaussDiag)]
+    L.gm_gauss_correct_diag.restype = ctypes.c_int
     L.gm_compress_standard_workspace.argtypes = [ctypes.c_int64, ctypes.c_int64, P]
     L.gm_compress_standard_workspace.restype = ctypes.c_size_t
     L.gm_compress_standard.argtypes = [P, P, P, ctypes.c_int64, ctypes.c_int64, P, ctypes.c_int32, ctypes.c_int32,

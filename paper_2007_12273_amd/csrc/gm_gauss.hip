@@ -25,6 +25,7 @@
 //               of up to 131072 cells run the whole solve in one launch
 //               (k_solve).
 //   k_apply_dA  w_p += dA_{cell(p)} (eq. new-p-weight)
+#include <atomic>
 #include <cmath>
 
 #include "gm_device.h"
@@ -359,10 +360,14 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(const double* st, con
 // workgroup waits for all tags and adds the partials in workgroup order, so
 // all take the same decisions.  Buffers alternate by the parity of the
 // exchange: a workgroup two exchanges ahead would need every tag of the one
-// between.  The grid (at most kSolveMaxGroups workgroups, one per CU) is
-// resident as a whole; should it ever not be, the waits are bounded and every
-// workgroup leaves.  A solve that did not converge here, for that or for
-// numerical reasons, leaves the weights alone, and the host then takes the
+// between.  The exchanges need the whole grid (at most kSolveMaxGroups
+// workgroups, one per CU) resident.  The host launches it only where the device
+// has that many CUs that no other such solve of the process holds (SolvePlaces);
+// where another process or a long kernel keeps some of its workgroups out all
+// the same, a wait gives up after kSolveWaitUs and marks its tags, on which
+// every other workgroup leaves too, those that start later at their first
+// exchange.  A solve that did not converge here, for that or for numerical
+// reasons, leaves the weights alone, and the host then takes the
 // launch-per-step path, whose recurrences cancel less.
 // ---------------------------------------------------------------------------
 constexpr int kSolveThreads = 512;
@@ -370,7 +375,13 @@ constexpr int kSolveOwn = 2 * kSolveThreads;   // cells a workgroup owns
 constexpr int kSolveHalo = kSolveThreads;      // cells of one halo row
 constexpr int kSolveMaxGroups = 128;
 constexpr int kSolvePart = 8;                  // doubles per workgroup and exchange
-constexpr int kSolveSpin = 1 << 20;            // polls (each with a sleep) before a wait gives up
+constexpr int kSolveMaxPolls = 1 << 20;        // bounds a wait whatever the clock says
+// A wait is some microseconds where the grid is resident.  The limit is about
+// the launch-per-step solve's time on the largest mesh taken here: giving up
+// later would cost more than that solve, giving up earlier would leave grids
+// whose start another stream's kernels delay.
+constexpr int kSolveWaitUs = 2000;
+constexpr unsigned long long kSolveGone = ~0ull;  // tag of a workgroup that gave up
 
 struct SolveArgs {
     const double* colM;
@@ -382,6 +393,7 @@ struct SolveArgs {
     int per;              // rows (dx = 2) or cells (dx = 1) per workgroup
     double tol;
     int max_iter, max_restarts;
+    long long wait;       // longest wait in ticks of the wall clock; 0: gives up at once
     double* x;            // [n] the corrections dA
     double* halo[2];      // [n] v or t (or dA, r at a restart), alternating
     double* part;         // [2][groups][kSolvePart]
@@ -511,17 +523,23 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         bool ok = true;
         if (tid < G) {
             ok = false;
-            for (int spin = 0; spin < kSolveSpin; ++spin) {
-                if (__hip_atomic_load(A.tag + (size_t)par * G + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                    epoch) {
-                    ok = true;
-                    break;
-                }
+            long long t0 = 0;  // the clock is read in long waits only
+            for (int poll = 0; A.wait > 0 && poll < kSolveMaxPolls; ++poll) {
+                const unsigned long long seen =
+                    __hip_atomic_load(A.tag + (size_t)par * G + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ok = seen == epoch;
+                if (ok || seen == kSolveGone) break;
+                if (poll == 32) t0 = wall_clock64();
+                if (poll > 32 && wall_clock64() - t0 >= A.wait) break;
                 __builtin_amdgcn_s_sleep(1);
             }
         }
         const bool all = __syncthreads_and(ok);
-        if (!all) return false;
+        if (!all) {
+            if (tid < 2)
+                __hip_atomic_store(A.tag + (size_t)tid * G + g, kSolveGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
         if (wid < 5) {
             // value wid over the workgroups: a lane adds its two, then the wave
             double a = 0.0;
@@ -741,12 +759,54 @@ constexpr int kChunk = 8;
 // restarts from the true residual before the solve gives up
 constexpr int kMaxRestarts = 8;
 
+// The one-launch solves of the process at once, per device: their workgroups
+// together take at most a CU each, so none keeps part of another's grid out.
+// A call holds its places until its solve has ended.
+constexpr int kMaxDevices = 64;
+std::atomic<int> g_solve_held[kMaxDevices];
+
+// a device attribute, looked up once per device; 0 if it cannot be had
+int device_attribute(std::atomic<int> (&known)[kMaxDevices], hipDeviceAttribute_t which, int dev)
+{
+    int x = known[dev].load(std::memory_order_relaxed);
+    if (x == 0 && hipDeviceGetAttribute(&x, which, dev) == hipSuccess) known[dev].store(x, std::memory_order_relaxed);
+    return x;
+}
+std::atomic<int> g_cus[kMaxDevices], g_clock_khz[kMaxDevices];
+
+struct SolvePlaces {
+    int dev = -1, held = 0, khz = 0;  // khz: of the device's wall clock
+    // `groups` places of the device's CUs, or of `places` where that is not
+    // negative; false if they are not free
+    bool take(int groups, int places)
+    {
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
+        int cus = device_attribute(g_cus, hipDeviceAttributeMultiprocessorCount, dev);
+        khz = device_attribute(g_clock_khz, hipDeviceAttributeWallClockRate, dev);
+        if (khz <= 0) return false;
+        if (places >= 0 && places < cus) cus = places;
+        held = groups;
+        if (g_solve_held[dev].fetch_add(groups) + groups <= cus) return true;
+        release();
+        return false;
+    }
+    void release()
+    {
+        if (held) g_solve_held[dev].fetch_sub(held);
+        held = 0;
+    }
+    ~SolvePlaces() { release(); }
+};
+
 template <int DX>
 int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n, int nx, int ny,
                        const double* target, double tol, int max_iter, const GaussWs& g, hipStream_t st,
-                       int32_t* iters_out, double* resid_out)
+                       int32_t* iters_out, double* resid_out, gm_gauss_diag* diag)
 {
     using namespace gm;
+    int ignored = 0;
+    int32_t& path = diag ? diag->path : ignored;
+    path = 0;
     const unsigned nb = (unsigned)vec_blocks(n);
     const dim3 vb(kVecThreads);
     double hs[S_COUNT];
@@ -764,7 +824,9 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
     // Longer rows and larger meshes are launched step by step.
     const int per = DX == 1 ? kSolveOwn : (nx <= kSolveHalo ? kSolveOwn / nx : 0);
     const int64_t ngroups = per > 0 ? ((DX == 1 ? n : (int64_t)ny) + per - 1) / per : 0;
-    const bool one_launch = per > 0 && ngroups <= kSolveMaxGroups;
+    SolvePlaces place;
+    const bool one_launch =
+        per > 0 && ngroups <= kSolveMaxGroups && place.take((int)ngroups, diag ? diag->places : -1);
     const int groups = one_launch ? (int)ngroups : 0;
     hipLaunchKernelGGL(k_stencil<DX>, dim3(stencil_blocks(n)), dim3(kStencilThreads), 0, st, x, w, off, n, g.colM,
                        g.colW, (unsigned long long*)g.t, one_launch ? 2 * groups : 0);
@@ -781,6 +843,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
         a.tol = tol;
         a.max_iter = max_iter;
         a.max_restarts = kMaxRestarts;
+        a.wait = (long long)place.khz * (diag && diag->wait_us >= 0 ? diag->wait_us : kSolveWaitUs) / 1000;
         a.x = g.x;
         a.halo[0] = g.p;
         a.halo[1] = g.v;
@@ -789,7 +852,9 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
         a.st = g.st;
         hipLaunchKernelGGL(k_solve<DX>, dim3(groups), dim3(kSolveThreads), 0, st, a);
         hipLaunchKernelGGL(k_apply_dA, dim3((unsigned)n), dim3(256), 0, st, w, off, g.x, g.st);
+        path = 1;
         if (!read_state()) return GM_EHIP;
+        place.release();
         if (hs[S_EMPTY] != 0.0) return GM_EINVAL;  // a cell without particles: M is singular
         const double rel = hs[S_TOL2B2] > 0.0 ? std::sqrt(hs[S_R2] / hs[S_TOL2B2]) : 0.0;
         if (hs[S_DONE] == 1.0 && std::isfinite(rel)) {
@@ -797,6 +862,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
             if (resid_out) *resid_out = rel;
             return GM_OK;
         }
+        path = 2;
     }
     hipLaunchKernelGGL(k_setup<DX>, dim3(nb), vb, 0, st, g.colM, g.colW, target, off, n, nx, ny, g.dinv, g.b, g.x,
                        g.partial);
@@ -880,9 +946,9 @@ int gm_deposit(const double* x, const double* w, const int64_t* cell_off, int64_
     return hipGetLastError() == hipSuccess ? GM_OK : GM_EHIP;
 }
 
-int gm_gauss_correct(const double* x, double* w, const int64_t* cell_off, int64_t n_cells, int32_t dx, int32_t nx,
-                     const double* dep_target, double tol, int32_t max_iter, void* ws, size_t ws_bytes, void* stream,
-                     int32_t* iters_out, double* resid_out)
+int gm_gauss_correct_diag(const double* x, double* w, const int64_t* cell_off, int64_t n_cells, int32_t dx,
+                          int32_t nx, const double* dep_target, double tol, int32_t max_iter, void* ws,
+                          size_t ws_bytes, void* stream, int32_t* iters_out, double* resid_out, gm_gauss_diag* diag)
 {
     if (!mesh_ok(n_cells, dx, nx) || !(tol > 0.0) || !(tol < 1.0) || max_iter < 1) return GM_EINVAL;
     if (!x || !w || !cell_off || !dep_target) return GM_EINVAL;
@@ -892,9 +958,17 @@ int gm_gauss_correct(const double* x, double* w, const int64_t* cell_off, int64_
     const int NX = dx == 1 ? (int)n_cells : nx, NY = dx == 1 ? 1 : (int)(n_cells / nx);
     if (dx == 1)
         return gauss_correct_impl<1>(x, w, cell_off, n_cells, NX, NY, dep_target, tol, max_iter, g, st, iters_out,
-                                     resid_out);
+                                     resid_out, diag);
     return gauss_correct_impl<2>(x, w, cell_off, n_cells, NX, NY, dep_target, tol, max_iter, g, st, iters_out,
-                                 resid_out);
+                                 resid_out, diag);
+}
+
+int gm_gauss_correct(const double* x, double* w, const int64_t* cell_off, int64_t n_cells, int32_t dx, int32_t nx,
+                     const double* dep_target, double tol, int32_t max_iter, void* ws, size_t ws_bytes, void* stream,
+                     int32_t* iters_out, double* resid_out)
+{
+    return gm_gauss_correct_diag(x, w, cell_off, n_cells, dx, nx, dep_target, tol, max_iter, ws, ws_bytes, stream,
+                                 iters_out, resid_out, nullptr);
 }
 
 }  // extern "C"
