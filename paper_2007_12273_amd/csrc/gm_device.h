@@ -151,7 +151,7 @@ __device__ __forceinline__ float swap_add(float a, float b)
 }
 
 template <int W>
-__device__ __forceinline__ double swap_add(double a, double b)
+__device__ __forceinline__ void swap_pair(double a, double b, double& p, double& q)
 {
     const uint64_t x = (uint64_t)__double_as_longlong(a), y = (uint64_t)__double_as_longlong(b);
     const unsigned xl = (unsigned)x, xh = (unsigned)(x >> 32), yl = (unsigned)y, yh = (unsigned)(y >> 32);
@@ -159,8 +159,38 @@ __device__ __forceinline__ double swap_add(double a, double b)
                            : __builtin_amdgcn_permlane16_swap(xl, yl, false, false);
     const auto h = W == 32 ? __builtin_amdgcn_permlane32_swap(xh, yh, false, false)
                            : __builtin_amdgcn_permlane16_swap(xh, yh, false, false);
-    return __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[0] << 32) | (unsigned)l[0])) +
-           __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[1] << 32) | (unsigned)l[1]));
+    p = __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[0] << 32) | (unsigned)l[0]));
+    q = __longlong_as_double((int64_t)(((uint64_t)(unsigned)h[1] << 32) | (unsigned)l[1]));
+}
+
+template <int W>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    double p, q;
+    swap_pair<W>(a, b, p, q);
+    return p + q;
+}
+
+// the same swaps of two sums carried as hi + lo
+template <int W>
+__device__ __forceinline__ Sum2 swap_add(const Sum2& a, const Sum2& b)
+{
+    Sum2 x, y;
+    swap_pair<W>(a.hi, b.hi, x.hi, y.hi);
+    swap_pair<W>(a.lo, b.lo, x.lo, y.lo);
+    add2(x, y);
+    return x;
+}
+
+template <int CTRL>
+__device__ __forceinline__ void dpp_add(Sum2& a)
+{
+    add2(a, Sum2{dpp_get<CTRL>(a.hi), dpp_get<CTRL>(a.lo)});
+}
+template <int CTRL, typename T>
+__device__ __forceinline__ void dpp_add(T& a)
+{
+    a += dpp_get<CTRL>(a);
 }
 
 template <int NV, typename T>
@@ -173,13 +203,13 @@ __device__ __forceinline__ void wave_sums_transposed(const T (&x)[NV], T (&b)[(N
 #pragma unroll
     for (int j = 0; j < NB; ++j) b[j] = swap_add<16>(a[2 * j], a[2 * j + 1 < NA ? 2 * j + 1 : 2 * j]);
 #pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0xB1>(b[j]);   // quad_perm [1,0,3,2]
+    for (int j = 0; j < NB; ++j) dpp_add<0xB1>(b[j]);   // quad_perm [1,0,3,2]
 #pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x4E>(b[j]);   // quad_perm [2,3,0,1]
+    for (int j = 0; j < NB; ++j) dpp_add<0x4E>(b[j]);   // quad_perm [2,3,0,1]
 #pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x141>(b[j]);  // row_half_mirror
+    for (int j = 0; j < NB; ++j) dpp_add<0x141>(b[j]);  // row_half_mirror
 #pragma unroll
-    for (int j = 0; j < NB; ++j) b[j] += dpp_get<0x140>(b[j]);  // row_mirror
+    for (int j = 0; j < NB; ++j) dpp_add<0x140>(b[j]);  // row_mirror
 }
 
 // Workgroup-wide sum of NV values; every thread receives the totals.  Lane

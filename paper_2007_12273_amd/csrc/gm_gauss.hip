@@ -346,7 +346,10 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(const double* st, con
 // two exchanges: after v = M dinv p the workgroups publish v and their part
 // of rh.v, after t = M dinv s they publish t and their parts of t.s, t.t,
 // rh.s, rh.t and s.s; omega, the new rho = rh.s - omega rh.t and the new |r|^2
-// = s.s - 2 omega t.s + omega^2 t.t follow from those, and every workgroup
+// = s.s - 2 omega t.s + omega^2 t.t follow from those.  These differences
+// cancel (rho lost up to four times what a dot product with r rounds off, |r|^2
+// three of its digits), so all five sums, and the differences, are carried in
+// two parts; they then hold more than the dot products would.  Every workgroup
 // updates p, r and s of its halo itself from the neighbours' v and t.  The
 // restarts from the true residual b - M dA, which alone decides convergence,
 // run inside as well.  Launched one kernel per step the solve was bound by
@@ -374,7 +377,7 @@ constexpr int kSolveThreads = 512;
 constexpr int kSolveOwn = 2 * kSolveThreads;   // cells a workgroup owns
 constexpr int kSolveHalo = kSolveThreads;      // cells of one halo row
 constexpr int kSolveMaxGroups = 128;
-constexpr int kSolvePart = 8;                  // doubles per workgroup and exchange
+constexpr int kSolvePart = 16;                 // doubles per workgroup and exchange: five sums at 0, their low parts at 8
 constexpr int kSolveMaxPolls = 1 << 20;        // bounds a wait whatever the clock says
 // A wait is some microseconds where the grid is resident.  The limit is about
 // the launch-per-step solve's time on the largest mesh taken here: giving up
@@ -410,6 +413,26 @@ __device__ __forceinline__ double agent_load(const double* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// the exchange's sums, in one part or two
+__device__ __forceinline__ void agent_store(double* p, const Sum2& v)
+{
+    agent_store(p, v.hi);
+    agent_store(p + 8, v.lo);
+}
+__device__ __forceinline__ void agent_load(const double* p, double& v) { v = agent_load(p); }
+__device__ __forceinline__ void agent_load(const double* p, Sum2& v) { v = Sum2{agent_load(p), agent_load(p + 8)}; }
+__device__ __forceinline__ void add2(double& a, double b) { a += b; }
+__device__ __forceinline__ Sum2 sum2(double v) { return Sum2{v, 0.0}; }
+__device__ __forceinline__ Sum2 sum2(const Sum2& v) { return v; }
+template <typename T>
+__device__ __forceinline__ T as(const Sum2& v)
+{
+    if constexpr (std::is_same<T, double>::value)
+        return v.hi;
+    else
+        return v;
+}
+
 // Waits until this wave's stores have reached the point of coherence.  All
 // that the workgroups share goes through agent-scope atomics, which pass the
 // XCD's L2 by; a release fence would write the L2's other lines back as well,
@@ -422,8 +445,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
     constexpr int NS = kSlots<DX>;
     constexpr int NC = 2;                       // own cells per thread, and halo cells per thread
     __shared__ double vec[kSolveOwn + 2 * kSolveHalo];
-    __shared__ double red[kSolveThreads / 64][kSolvePart];
-    __shared__ double tot[kSolvePart];
+    __shared__ Sum2 red[8][kSolveThreads / 64];
+    __shared__ Sum2 tot[5];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int G = gridDim.x, g = blockIdx.x;
     const int H = DX == 1 ? 1 : A.nx;           // cells of one halo row
@@ -491,30 +514,34 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
     unsigned long long epoch = 0;
     // publish val of the own cells, add up q over the grid (into tot), and
     // return the neighbours' val on the halo; false when a wait gave up
-    auto exchange = [&](const double (&val)[NC], const double (&q)[5], double (&hval)[NC]) -> bool {
+    auto exchange = [&](const double (&val)[NC], const auto& q, double (&hval)[NC]) -> bool {
+        using T = std::remove_cv_t<std::remove_reference_t<decltype(q[0])>>;  // double or Sum2
+        constexpr int NQ = sizeof(q) / sizeof(T), NB = (NQ + 3) / 4;
         ++epoch;
         const int par = (int)(epoch & 1);
         double* halo = A.halo[par];
 #pragma unroll
         for (int k = 0; k < NC; ++k)
             if (gi[k] >= 0) agent_store(halo + gi[k], val[k]);
-        double w[5];
+        // sum u ends in register u / 4 of every lane of row tv_row(u)
+        T w[NB];
+        wave_sums_transposed<NQ>(q, w);
+        if ((lane & 15) == 15) {
+            const int row = lane >> 4, first = 2 * (row & 1) + (row >> 1);
 #pragma unroll
-        for (int u = 0; u < 5; ++u) w[u] = q[u];
-        wave_sums(w);
-        if (lane == 0)
-#pragma unroll
-            for (int u = 0; u < 5; ++u) red[wid][u] = w[u];
+            for (int j = 0; j < NB; ++j) red[4 * j + first][wid] = sum2(w[j]);
+        }
         stores_done();  // this wave's part is out before the tag below
         __syncthreads();
         double* part = A.part + (size_t)par * G * kSolvePart;
-        if (tid < 5) {
-            double a = 0.0;
-#pragma unroll
-            for (int u = 0; u < kSolveThreads / 64; ++u) a += red[u][tid];
-            agent_store(part + (size_t)g * kSolvePart + tid, a);
-        }
         if (wid == 0) {
+            // sum lane / 8 over the waves
+            static_assert(kSolveThreads / 64 == 8, "eight lanes of a row hold a sum's waves");
+            T a = as<T>(red[lane >> 3][lane & 7]);
+            dpp_add<0xB1>(a);
+            dpp_add<0x4E>(a);
+            dpp_add<0x141>(a);
+            if ((lane & 7) == 0 && lane < 8 * NQ) agent_store(part + (size_t)g * kSolvePart + (lane >> 3), a);
             stores_done();
             if (lane == 0)
                 __hip_atomic_store(A.tag + (size_t)par * G + g, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -540,13 +567,17 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 __hip_atomic_store(A.tag + (size_t)tid * G + g, kSolveGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
-        if (wid < 5) {
+        if (wid < NQ) {
             // value wid over the workgroups: a lane adds its two, then the wave
-            double a = 0.0;
-            if (lane < G) a = agent_load(part + (size_t)lane * kSolvePart + wid);
-            if (lane + 64 < G) a += agent_load(part + (size_t)(lane + 64) * kSolvePart + wid);
-            a = wave_sum(a);
-            if (lane == 0) tot[wid] = a;
+            T a[1] = {}, b[1];
+            const double* at = part + (size_t)lane * kSolvePart + wid;
+            if (lane < G) agent_load(at, a[0]);
+            if (lane + 64 < G) {
+                agent_load(at + 64 * kSolvePart, b[0]);
+                add2(a[0], b[0]);
+            }
+            wave_sums_transposed<1>(a, b);
+            if (lane == 15) tot[wid] = sum2(b[0]);
         }
 #pragma unroll
         for (int k = 0; k < NC; ++k) hval[k] = hi[k] >= 0 ? agent_load(halo + hi[k]) : 0.0;
@@ -571,24 +602,20 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         }
     };
 
-    double hx[NC], q[5], a_[NC], ha_[NC];
-    auto zero5 = [&]() {
-#pragma unroll
-        for (int u = 0; u < 5; ++u) q[u] = 0.0;
-    };
+    double hx[NC], a_[NC], ha_[NC];
     int done = 0, iters = 0;
     double b2 = 0.0, r2 = 0.0, true_r2 = 0.0, empty = 0.0;
     // b.b and the number of empty cells
-    zero5();
+    double qb[2] = {0.0, 0.0};
 #pragma unroll
     for (int k = 0; k < NC; ++k) {
-        q[0] += b[k] * b[k];
-        if (gi[k] >= 0 && A.off[gi[k] + 1] <= A.off[gi[k]]) q[1] += 1.0;
+        qb[0] += b[k] * b[k];
+        if (gi[k] >= 0 && A.off[gi[k] + 1] <= A.off[gi[k]]) qb[1] += 1.0;
     }
-    bool ok = exchange(x, q, hx);
+    bool ok = exchange(x, qb, hx);
     if (ok) {
-        b2 = true_r2 = tot[0];
-        empty = tot[1];
+        b2 = true_r2 = tot[0].hi;
+        empty = tot[1].hi;
     }
     const double tol2b2 = A.tol * A.tol * b2;
     if (empty != 0.0 || b2 == 0.0) done = 1;
@@ -596,7 +623,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         // the true residual of the current dA (zero at first), and r on the halo
         product(x, hx, a_);
         double rho = 0.0, alpha = 1.0, omega = 1.0, beta = 0.0;
-        zero5();
+        double q[1] = {0.0};
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
             r[k] = rh[k] = b[k] - a_[k];
@@ -606,7 +633,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         }
         ok = exchange(r, q, hr);
         if (!ok) break;
-        r2 = true_r2 = rho = tot[0];
+        r2 = true_r2 = rho = tot[0].hi;
         if (r2 <= tol2b2) {
             done = 1;
             break;
@@ -625,12 +652,12 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 ha_[k] = hdinv[k] * hp[k];
             }
             product(a_, ha_, v);
-            zero5();
+            q[0] = 0.0;
 #pragma unroll
             for (int k = 0; k < NC; ++k) q[0] += rh[k] * v[k];
             ok = exchange(v, q, hv);
             if (!ok) break;
-            const double rv = tot[0];
+            const double rv = tot[0].hi;
             if (rv == 0.0 || !isfinite(rv)) break;  // breakdown: restart
             alpha = rho / rv;
 #pragma unroll
@@ -641,20 +668,20 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 ha_[k] = hdinv[k] * hs[k];
             }
             product(a_, ha_, t);
-            zero5();
+            Sum2 qt[5] = {};
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
-                q[0] += t[k] * sv[k];
-                q[1] += t[k] * t[k];
-                q[2] += rh[k] * sv[k];
-                q[3] += rh[k] * t[k];
-                q[4] += sv[k] * sv[k];
+                mul_add2(qt[0], t[k], sv[k]);
+                mul_add2(qt[1], t[k], t[k]);
+                mul_add2(qt[2], rh[k], sv[k]);
+                mul_add2(qt[3], rh[k], t[k]);
+                mul_add2(qt[4], sv[k], sv[k]);
             }
             double ht[NC];
-            ok = exchange(t, q, ht);
+            ok = exchange(t, qt, ht);
             if (!ok) break;
-            const double ts = tot[0], tt = tot[1], rhs = tot[2], rht = tot[3], ss = tot[4];
-            omega = tt > 0.0 ? ts / tt : 0.0;
+            const Sum2 ts = tot[0], tt = tot[1];
+            omega = value2(tt) > 0.0 ? value2(ts) / value2(tt) : 0.0;
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
                 x[k] += dinv[k] * (alpha * p[k] + omega * sv[k]);
@@ -662,8 +689,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 hr[k] = hs[k] - omega * ht[k];
             }
             ++iters;
-            r2 = ss - omega * (2.0 * ts - omega * tt);
-            const double rho1 = rhs - omega * rht;
+            r2 = value2(sub_scaled2(tot[4], omega, sub_scaled2(Sum2{2.0 * ts.hi, 2.0 * ts.lo}, omega, tt)));
+            const double rho1 = value2(sub_scaled2(tot[2], omega, tot[3]));
             // converged by the recurrence (or below its rounding): checked
             // against the true residual
             if (r2 <= tol2b2) stop = true;
@@ -675,7 +702,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         }
         if (!ok) break;
         // dA on the halo for the next true residual
-        zero5();
+        q[0] = 0.0;
         ok = exchange(x, q, hx);
     }
 #pragma unroll
@@ -847,7 +874,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
         a.x = g.x;
         a.halo[0] = g.p;
         a.halo[1] = g.v;
-        a.part = g.s;  // 128 B per group: the vector holds 8 B per cell, at least 256
+        a.part = g.s;  // 256 B per group: the vector holds 8 B per cell, at least 256 in all
         a.tag = (unsigned long long*)g.t;
         a.st = g.st;
         hipLaunchKernelGGL(k_solve<DX>, dim3(groups), dim3(kSolveThreads), 0, st, a);

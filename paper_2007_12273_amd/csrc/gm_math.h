@@ -146,4 +146,34 @@ __device__ __forceinline__ void sincospi_64(double a, double& sn, double& cs)
     cs = ((q + 1) & 2) ? -v : v;
 }
 
+// A sum carried as hi + lo (the exact error of every addition to hi goes to
+// lo; Knuth's two-sum, and the product's error by fma): differences of such
+// sums may cancel without losing what single ones would.
+struct Sum2 {
+    double hi, lo;
+};
+__device__ __forceinline__ void add2(Sum2& a, const Sum2& b)
+{
+#pragma clang fp contract(off)
+    const double s = a.hi + b.hi, t = s - a.hi;
+    a.lo += b.lo + ((a.hi - (s - t)) + (b.hi - t));
+    a.hi = s;
+}
+// a += x y
+__device__ __forceinline__ void mul_add2(Sum2& a, double x, double y)
+{
+#pragma clang fp contract(off)
+    const double p = x * y;
+    add2(a, Sum2{p, fma(x, y, -p)});
+}
+// a - w b
+__device__ __forceinline__ Sum2 sub_scaled2(Sum2 a, double w, const Sum2& b)
+{
+#pragma clang fp contract(off)
+    const double p = w * b.hi;
+    add2(a, Sum2{-p, -fma(w, b.lo, fma(w, b.hi, -p))});
+    return a;
+}
+__device__ __forceinline__ double value2(const Sum2& a) { return a.hi + a.lo; }
+
 }  // namespace gm
