@@ -582,7 +582,10 @@ int gm_deposit(const double* x, const double* w, const int64_t* cell_off, int64_
  * cells or less) or, on other meshes and where such solves of other threads
  * hold the CUs, once per 8 iterations and per restart, so it synchronises
  * `stream` and cannot be captured in a graph; the empty cell check and GM_ENOCONV come from those
- * reads, after kernels on the workspace were enqueued.  iters_out (iterations) and resid_out (final
+ * reads, after kernels on the workspace were enqueued.  A one-launch solve that
+ * breaks down, or uses up max_iter within 1000 tol of its end or after a
+ * restart, is run again launch by launch, with max_iter iterations of its own.
+ * iters_out (iterations of the solve that gave the weights) and resid_out (final
  * true relative residual) are host pointers, may be NULL.  Returns
  * GM_ENOCONV, with the weights corrected by the last iterate, when the
  * tolerance was not reached. */
@@ -609,8 +612,8 @@ typedef struct gm_gauss_diag {
     int32_t wait_us;  /* in: longest wait of a workgroup for another in microseconds; 0: the
                          solve gives up at its first exchange; < 0: the built-in limit */
     int32_t places;   /* in: at most this many of the device's CUs; < 0: all */
-    int32_t path;     /* out: 0 launch by launch alone, 1 in one launch, 2 in one launch without
-                         convergence, then launch by launch */
+    int32_t path;     /* out: 0 launch by launch alone, 1 in one launch, 2 in one launch first,
+                         then launch by launch */
 } gm_gauss_diag;
 int gm_gauss_correct_diag(const double* x, double* w, const int64_t* cell_off, int64_t n_cells, int32_t dx,
                           int32_t nx, const double* dep_target, double tol, int32_t max_iter, void* ws,

@@ -76,6 +76,29 @@ def test_a_wait_that_gives_up_leaves_the_solve_to_the_other_path(dx, nx, ny):
     assert p.solve()[:2] == (0, 1)  # the workspace holds no mark of it
 
 
+@pytest.mark.parametrize("dx,nx,ny", [(1, 4096, 1), (2, 256, 256)])
+def test_iterations_used_up_far_from_the_tolerance_are_not_run_twice(dx, nx, ny):
+    """Three iterations: the one-launch solve's iterate is the answer.  Against
+    the other path's: the same iterations with sums in another order, whose
+    relative error stays below 65536 x 2^-53 = 7e-12 in each of their scalars;
+    1e-9 leaves a factor for how three iterations carry it on."""
+    p = Problem(dx, nx, ny)
+    rc, path, it, res, w = p.solve(max_iter=3)
+    assert (rc, path, it) == (_lib.GM_ENOCONV, 1, 3) and res > 1e-10
+    rc, path, it, sres, steps = p.solve(max_iter=3, places=0)
+    assert (rc, path, it) == (_lib.GM_ENOCONV, 0, 3) and abs(res - sres) <= 1e-9 * sres
+    assert float((w - steps).abs().max()) <= 1e-9 * float((steps - p.w0).abs().max())
+
+
+def test_iterations_used_up_near_the_tolerance_are_left_to_the_other_path():
+    p = Problem(2, 256, 256)
+    need = p.solve()[2]
+    for max_iter in (need - 1, need):
+        rc, path, it, res, w = p.solve(max_iter=max_iter)
+        assert path == (2 if max_iter < need else 1) and it <= max_iter
+        assert rc == (0 if res <= 1e-13 else _lib.GM_ENOCONV)
+
+
 def test_solves_of_several_threads_share_the_places():
     """Six threads with 128 workgroups each: the device has places for two such
     grids at once, the others solve launch by launch (and a grid that the other
