@@ -15,10 +15,10 @@ int launch_compress_d1_float(int, int, int, int, const CompressArgs&, int, hipSt
 int launch_compress_d3_float(int, int, int, int, const CompressArgs&, int, hipStream_t);
 int launch_compress_d1_double(int, int, int, int, const CompressArgs&, int, hipStream_t);
 int launch_compress_d3_double(int, int, int, int, const CompressArgs&, int, hipStream_t);
-int launch_compress_span_d1_float(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
-int launch_compress_span_d3_float(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
-int launch_compress_span_d1_double(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
-int launch_compress_span_d3_double(int, const CompressArgs&, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d1_float(int, const CompressArgs&, int, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d3_float(int, const CompressArgs&, int, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d1_double(int, const CompressArgs&, int, int, int, int, int64_t, hipStream_t);
+int launch_compress_span_d3_double(int, const CompressArgs&, int, int, int, int, int64_t, hipStream_t);
 int grid_compress_d1_float(int, int, int, int);
 int grid_compress_d3_float(int, int, int, int);
 int grid_compress_d1_double(int, int, int, int);
@@ -202,25 +202,28 @@ int launch_em_big(int D, bool fp64, int kt, gm::CompressArgs& a, int64_t n_cells
     return fp64 ? gm::launch_compress_big_d3_double(kt, a, g, st) : gm::launch_compress_big_d3_float(kt, a, g, st);
 }
 
-// The built-in plan's EM phase: at most five launches that walk several
-// buckets each (k_em_span), plus those of the buckets whose densities do not
-// stay in registers and of the larger cells.  A launch of 8, 6, 4 or 1 waves
-// per workgroup takes the buckets of cells that many waves or a little fewer
-// fit (the 4-wave launch every narrower one too), with FP64 iterations on
-// more waves than the plan's codes say (em_default), so no cell waits behind
-// another bucket's slowest fit whatever hardware queues the streams share:
-// with HIP's default of four, one launch per bucket ran up to four of them
-// one after another.  Released as in launch_em_phase.
+// The built-in plan's EM phase: up to four launches that walk several buckets
+// each (k_em_span), one for each bucket whose densities do not stay in registers
+// (one with FP32 iterations and eight slots, up to five with FP64 ones) and one
+// for the larger cells.  A launch of 8, 6, 4 or 1 waves per workgroup takes the
+// buckets of cells that many waves or a little fewer fit (the 4-wave launch
+// every narrower one too, the 8-wave one the 6-wave one's while it lasts), with
+// FP64 iterations on more waves than the plan's codes say (em_default).  With
+// one launch per bucket, HIP's default of four hardware queues ran up to four
+// of them one after another; of these, only launches of buckets whose densities
+// do not stay in registers share a queue with others (FP64 above 2048 particles
+// and 1V FP32 with sixteen slots), which can then wait for each other.
+// Released as in launch_em_phase.
 int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArgs& a, int64_t n_cells, hipStream_t st)
 {
     Fork* fk = fork_for_device();
     if (!fk) return -1;
-    auto span = [&](int waves, int hi, int lo, hipStream_t s) {
+    auto span = [&](int waves, int hi, int lo, int help, hipStream_t s) {
         if (D == 1)
-            return fp64 ? gm::launch_compress_span_d1_double(kt, a, waves, hi, lo, n_cells, s)
-                        : gm::launch_compress_span_d1_float(kt, a, waves, hi, lo, n_cells, s);
-        return fp64 ? gm::launch_compress_span_d3_double(kt, a, waves, hi, lo, n_cells, s)
-                    : gm::launch_compress_span_d3_float(kt, a, waves, hi, lo, n_cells, s);
+            return fp64 ? gm::launch_compress_span_d1_double(kt, a, waves, hi, lo, help, n_cells, s)
+                        : gm::launch_compress_span_d1_float(kt, a, waves, hi, lo, help, n_cells, s);
+        return fp64 ? gm::launch_compress_span_d3_double(kt, a, waves, hi, lo, help, n_cells, s)
+                    : gm::launch_compress_span_d3_float(kt, a, waves, hi, lo, help, n_cells, s);
     };
     auto run_as = [&](int b) { return D == 1 ? gm::em_default<1>(kt, fp64, b) : gm::em_default<3>(kt, fp64, b); };
     auto spanned = [&](int b) { return run_as(b).span; };
@@ -228,10 +231,11 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
     // down to the narrowest
     constexpr int kWidths = 4;
     constexpr int kWaves[kWidths] = {8, 6, 4, 1}, kAbove[kWidths] = {6, 4, 0, 0};
-    // The 6-wave launch follows the 8-wave one on its stream (both have few
-    // cells): on one of its own it shared a hardware queue with the 4-wave
-    // launch, which then waited for its slowest fit (1024 1V cells of about
-    // 2000: 17.6 ms against 21.4).
+    // The 6-wave launch follows the 8-wave one on its stream: on one of its
+    // own it shared a hardware queue with the 4-wave launch, which then waited
+    // for its slowest fit (1024 1V cells of about 2000: 17.6 ms against 21.4).
+    // Its cells do not wait for the 8-wave launch's slowest fit: workgroups of
+    // that launch take them meanwhile.
     constexpr int kLane[kWidths] = {0, 0, 2, kLanes - 1};
     int hi[kWidths], lo[kWidths];
     bool lane_used[kLanes] = {};
@@ -264,18 +268,18 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
         if (lane_used[i] && hipStreamWaitEvent(fk->aux[i], fk->fork, 0) != hipSuccess) return -1;
     for (int i = 0; i < nrest; ++i)
         if (launch_em_bucket(D, fp64, kt, rest[i], p, a, n_cells, fk->aux[kRestLane[i]])) return -1;
-    for (int w = 0; w < 2; ++w)
-        if (hi[w] >= 0 && span(kWaves[w], hi[w], lo[w], fk->aux[kLane[w]])) return -1;
+    if (hi[0] >= 0 && span(kWaves[0], hi[0], lo[0], std::min(lo[0], lo[1]), fk->aux[kLane[0]])) return -1;
+    if (hi[1] >= 0 && span(kWaves[1], hi[1], lo[1], lo[1], fk->aux[kLane[1]])) return -1;
     if (launch_em_big(D, fp64, kt, a, n_cells, fk->aux[kRestLane[0]])) return -1;
     k_hold<<<1, 64, 0, st>>>(fk->hold_ticks, a.plan, heavy_mask);
     if (hipGetLastError() != hipSuccess) return -1;
     if (hi[2] >= 0) {
         hipStream_t s4 = fk->aux[kLane[2]];
         if (hipEventRecord(fk->fork2, st) != hipSuccess || hipStreamWaitEvent(s4, fk->fork2, 0) != hipSuccess ||
-            span(kWaves[2], hi[2], lo[2], s4))
+            span(kWaves[2], hi[2], lo[2], lo[2], s4))
             return -1;
     }
-    if (hi[3] >= 0 && span(kWaves[3], hi[3], lo[3], st)) return -1;
+    if (hi[3] >= 0 && span(kWaves[3], hi[3], lo[3], lo[3], st)) return -1;
     for (int i = 0; i < kLanes - 1; ++i) {
         if (!lane_used[i]) continue;
         if (hipEventRecord(fk->join[i], fk->aux[i]) != hipSuccess) return -1;

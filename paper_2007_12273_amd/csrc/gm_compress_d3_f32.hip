@@ -29,10 +29,10 @@ int launch_compress_big_d3_float(int kmax_tpl, const CompressArgs& a, int grid, 
     return launch_big_dr<3, float>(kmax_tpl, a, grid, st);
 }
 
-int launch_compress_span_d3_float(int kmax_tpl, const CompressArgs& a, int waves, int b_hi, int b_lo, int64_t n_cells,
-                                hipStream_t st)
+int launch_compress_span_d3_float(int kmax_tpl, const CompressArgs& a, int waves, int b_hi, int b_lo, int b_help,
+                                int64_t n_cells, hipStream_t st)
 {
-    return launch_span_dr<3, float>(kmax_tpl, a, waves, b_hi, b_lo, n_cells, st);
+    return launch_span_dr<3, float>(kmax_tpl, a, waves, b_hi, b_lo, b_help, n_cells, st);
 }
 
 }  // namespace gm
