@@ -186,9 +186,10 @@ int gm_compress_noalloc(const double* v, const double* alpha, const int64_t* cel
  * particles at kmax <= 8; 128, 256, 512, 768, 1024, 1280, 1536, 1792, 2048,
  * 2560, 4096, 8192 at kmax > 8), whose
  * persistent workgroups take cells from a queue.  The built-in plan runs in
- * a few launches that walk several buckets each (four or five streams; with
- * FP64 iterations a cell of up to 2048 particles runs on more waves than
- * the plan's codes, the variants of a plan installed by hand, say).  A plan
+ * a few launches that walk several buckets each (on four streams with FP32
+ * iterations, up to eight with FP64 ones and in 1V with kmax > 8; with
+ * FP64 iterations a cell of up to 2048 particles does not run on the waves
+ * that the plan's codes say, see gm_autotune_get).  A plan
  * tuned or installed by hand runs one launch per bucket, each on a library
  * stream of its own (cells of more than 8192 particles run on the caller's
  * stream), so that all thirteen launches run concurrently.  The launches of
@@ -249,7 +250,8 @@ int gm_autotune(const double* v, const double* alpha, const int64_t* cell_off, i
  * Built: standard 1, 2, 4, 8 register-resident (8 for FP32 only at kmax
  * > 8; 5, 6, 7 for FP32 at kmax > 8) and 8, 16 recomputed; lean (FP32
  * only) 1, 2 register-resident and 4, 8 recomputed.
- * GM_EINVAL otherwise. */
+ * GM_EINVAL otherwise.  The plan runs as given, one launch per bucket, also
+ * where its codes are those gm_autotune_get reports for the built-in plan. */
 int gm_autotune_set(int32_t D, int32_t kmax, int32_t fp64, int32_t warm, const int32_t* variant,
                     const int32_t* lane);
 
@@ -262,16 +264,23 @@ int gm_autotune_reset(void);
  * arrays of 12.  Returns 1 for a plan installed by gm_autotune (also where
  * it kept the built-in plan), gm_autotune_set or gm_autotune_load, 0 where
  * none is installed (the built-in plan; also when no device is visible),
- * GM_EINVAL for bad arguments. */
+ * GM_EINVAL for bad arguments.  Of the built-in plan, which does not launch
+ * per bucket, these are the codes of its one-launch-per-bucket form: with
+ * FP32 iterations cells run on the waves they say (so the form gives the same
+ * bits), with FP64 ones cells of up to 2048 particles run on other numbers of
+ * waves, in 1V max_n / 256 (one up to 256 particles), in 3V max_n / 128 up to
+ * 1024 (one up to 128) and eight above, max_n the bucket's largest cell. */
 int gm_autotune_get(int32_t D, int32_t kmax, int32_t fp64, int32_t warm, int32_t* variant, int32_t* lane,
                     int32_t* order);
 
 /* Launch-plan cache file (plain text, one plan per line:
  *   gmcr-plan 1 <arch> <CUs> <D> <kmax class 8|16> <fp64> <warm>
- *   variant[12] lane[12] order[12]),
+ *   variant[12] lane[12] order[12] <builtin|buckets>),
  * keyed by the device (architecture name and CU count), D, kmax class,
  * precision and kind of start, with the variant, stream and launch order of
- * every length bucket.  gm_autotune_save writes the current device's
+ * every length bucket and whether the plan is the built-in one (kept by the
+ * tuner) or launches per bucket; a line without the last word is the built-in
+ * plan if it has that plan's numbers.  gm_autotune_save writes the current device's
  * installed plans (those gm_autotune_get reports as 1) to `path`, keeping the lines of other devices already in the file;
  * GM_EINVAL (NULL or empty path), GM_EHIP (no device), GM_EIO.
  * gm_autotune_load reads `path` and installs the plans whose device key is

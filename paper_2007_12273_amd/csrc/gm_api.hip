@@ -138,6 +138,7 @@ struct EmPlan {
     int8_t lane[gm::kNumBuckets];
     int8_t order[gm::kNumBuckets];  // launch order, first launched first
     bool tuned;
+    bool builtin;  // runs as the built-in launches, whatever the codes above say
 };
 
 // bucket b on library stream b
@@ -157,6 +158,7 @@ EmPlan default_plan(int D, int kt, bool fp64)
         p.order[b] = (int8_t)(gm::kNumBuckets - 1 - b);  // largest cells first
     }
     p.tuned = false;
+    p.builtin = true;
     return p;
 }
 
@@ -295,11 +297,11 @@ bool same_launches(const EmPlan& p, const EmPlan& q)
            memcmp(p.lane, q.lane, sizeof(p.lane)) == 0 && memcmp(p.order, q.order, sizeof(p.order)) == 0;
 }
 
-// the EM phase of plan p: the built-in plan in its own launches; any other
+// the EM phase of plan p: a built-in plan in its own launches; any other
 // forked onto the lanes, one launch per bucket in plan order, and joined
 int launch_em_phase(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArgs& a, int64_t n_cells, hipStream_t st)
 {
-    if (same_launches(p, default_plan(D, kt, fp64))) return launch_em_builtin(D, fp64, kt, p, a, n_cells, st);
+    if (p.builtin) return launch_em_builtin(D, fp64, kt, p, a, n_cells, st);
     Fork* fk = fork_for_device();
     if (!fk) return -1;
     hipStream_t lanes[kLanes];
@@ -771,6 +773,7 @@ int gm_autotune(const double* v, const double* alpha, const int64_t* cell_off, i
             t.order[i] = (int8_t)b;
         }
         t.tuned = true;
+        t.builtin = false;
         return t;
     };
     int pref_c[gm::kNumBuckets];
@@ -876,15 +879,20 @@ int plan_from_codes(int D, int kt, bool fp64, const int32_t* variant, const int3
         }
     }
     p.tuned = true;
+    p.builtin = false;
     return GM_OK;
 }
 
 // ---- launch-plan file ----
 // One line per tuned plan:
-//   gmcr-plan 1 <arch> <CUs> <D> <kmax class> <fp64> <warm> v[12] lane[12] order[12]
+//   gmcr-plan 1 <arch> <CUs> <D> <kmax class> <fp64> <warm> v[12] lane[12] order[12] [builtin|buckets]
 // The device key is the architecture name and CU count of the device the
-// plan was tuned on; a file may hold the plans of several devices.
+// plan was tuned on; a file may hold the plans of several devices.  The last
+// word says whether the plan runs as the built-in launches or one per bucket; a
+// line without it dates from when the codes alone told, so one with the built-in
+// plan's codes, streams and order is that plan.
 constexpr const char* kPlanTag = "gmcr-plan";
+constexpr const char* kPlanForms[] = {"buckets", "builtin"};
 constexpr int kPlanFileVersion = 1;
 
 bool device_key(char* arch, size_t n, int& cus)
@@ -903,6 +911,7 @@ struct PlanLine {
     char arch[64];
     int cus, D, kt, fp64, warm;
     int32_t v[gm::kNumBuckets], lane[gm::kNumBuckets], order[gm::kNumBuckets];
+    int form;  // index into kPlanForms, -1: not said
 };
 
 // parse one line; false if it is not a well-formed plan line
@@ -923,6 +932,15 @@ bool parse_plan_line(const char* line, PlanLine& pl)
             dst[f][b] = x;
             q += k;
         }
+    char word[16];
+    int k = 0;
+    pl.form = -1;
+    if (sscanf(q, "%15s%n", word, &k) == 1) {
+        for (int f = 0; f < 2; ++f)
+            if (strcmp(word, kPlanForms[f]) == 0) pl.form = f;
+        if (pl.form < 0) return false;
+        q += k;
+    }
     while (*q == ' ' || *q == '\t' || *q == '\r' || *q == '\n') ++q;
     return *q == 0 && (pl.D == 1 || pl.D == 3) && (pl.kt == 8 || pl.kt == 16) && (pl.fp64 == 0 || pl.fp64 == 1) &&
            (pl.warm == 0 || pl.warm == 1);
@@ -991,7 +1009,7 @@ int gm_autotune_save(const char* path)
                         ok &= fprintf(f, " %d", gm::em_variant_code(p->per_thread[b], p->waves[b], p->mode[b])) > 0;
                     for (int b = 0; b < gm::kNumBuckets; ++b) ok &= fprintf(f, " %d", p->lane[b]) > 0;
                     for (int b = 0; b < gm::kNumBuckets; ++b) ok &= fprintf(f, " %d", p->order[b]) > 0;
-                    ok &= fputc('\n', f) != EOF;
+                    ok &= fprintf(f, " %s\n", kPlanForms[p->builtin ? 1 : 0]) > 0;
                 }
     ok &= fclose(f) == 0;
     return ok ? GM_OK : GM_EIO;
@@ -1021,6 +1039,10 @@ int gm_autotune_load(const char* path)
         if (strcmp(pl.arch, arch) != 0 || pl.cus != cus) continue;  // another device's plan
         EmPlan p;
         rc = plan_from_codes(pl.D, pl.kt, pl.fp64 != 0, pl.v, pl.lane, pl.order, p);
+        if (pl.form >= 0)
+            p.builtin = pl.form == 1;
+        else if (rc == GM_OK)
+            p.builtin = same_launches(p, default_plan(pl.D, pl.kt, pl.fp64 != 0));
         if (rc == GM_OK) plans.emplace_back(pl, p);
     }
     const bool read_err = ferror(f) != 0;
