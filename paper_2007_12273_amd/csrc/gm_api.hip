@@ -81,9 +81,14 @@ struct Fork {
     hipEvent_t fork2;  // releases the launches that do not fill a CU
     hipEvent_t join[kLanes - 1];
     long long hold_ticks;  // kHoldUs in ticks of the device's wall clock
+    // held while an EM phase is enqueued: a wait enqueued for an event means its
+    // last record, so another thread's record in between would let this call's
+    // launches start before its own plan kernels have ended
+    std::mutex mu;
 };
 constexpr int kMaxDevices = 64;
 Fork* g_fork[kMaxDevices] = {};
+std::mutex g_fork_mu;  // guards g_fork
 
 // The EM phase releases its launches in two steps.  A bucket whose
 // workgroups fill a CU's register file (eight or more waves of a standard
@@ -111,6 +116,7 @@ Fork* fork_for_device()
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+    std::lock_guard<std::mutex> lock(g_fork_mu);
     if (g_fork[dev]) return g_fork[dev];
     Fork* f = new Fork;
     for (int i = 0; i < kLanes - 1; ++i) {
@@ -220,6 +226,7 @@ int launch_em_builtin(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArg
 {
     Fork* fk = fork_for_device();
     if (!fk) return -1;
+    std::lock_guard<std::mutex> lock(fk->mu);
     auto span = [&](int waves, int hi, int lo, int help, hipStream_t s) {
         if (D == 1)
             return fp64 ? gm::launch_compress_span_d1_double(kt, a, waves, hi, lo, help, n_cells, s)
@@ -304,6 +311,7 @@ int launch_em_phase(int D, bool fp64, int kt, const EmPlan& p, gm::CompressArgs&
     if (p.builtin) return launch_em_builtin(D, fp64, kt, p, a, n_cells, st);
     Fork* fk = fork_for_device();
     if (!fk) return -1;
+    std::lock_guard<std::mutex> lock(fk->mu);
     hipStream_t lanes[kLanes];
     for (int i = 0; i < kLanes - 1; ++i) lanes[i] = fk->aux[i];
     lanes[kLanes - 1] = st;
