@@ -76,17 +76,19 @@ __device__ __forceinline__ double log_sum(double e, double t, double small)
     return h + ((t - (h - e)) + small);
 }
 
-// log2 of a finite positive argument (others go to the library): 2 / ln 2 in
-// two parts
+// log2, 2 / ln 2 in two parts; of zero, infinities, negative values and NaN
+// what the library gives (chosen at the end: a branch per value costs the
+// iterations' builds registers)
 __device__ __forceinline__ double log2_64(double x)
 {
 #pragma clang fp contract(off)
-    if (!(x > 0.0 && x <= 1.7976931348623157e308)) return log2(x);
     const LogParts p = log_parts(x);
     const double c = 2.8853900817779268, cl = 4.0710547481862066e-17;
     const double t = c * p.s;
     const double tl = fma(c, p.s, -t) + fma(c, p.sl, cl * p.s);
-    return log_sum(p.e, t, fma(t * p.z, p.q, tl));
+    const double y = log_sum(p.e, t, fma(t * p.z, p.q, tl));
+    const double special = x > 0.0 ? x : (x == 0.0 ? -__builtin_inf() : __builtin_nan(""));
+    return x > 0.0 && x <= 1.7976931348623157e308 ? y : special;
 }
 
 // log of x in (0, 1]: ln 2 in two parts, the first with eleven trailing zero
