@@ -1,5 +1,5 @@
-"""Cells of the built-in plan's 8-wave and 6-wave launches are fitted side by
-side.  One cell of each, 400 replayed sweeps: fitted together they take the
+"""Cells of the built-in plan's 8-wave and 6-wave launches, and those of the
+largest bucket and larger ones, are fitted side by side.  One cell of each, 400 replayed sweeps: fitted together they take the
 longer one's time (one after the other, the sum), so the bar lies half of the
 shorter one's time above the longer one's."""
 import numpy as np
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 SWEEPS = 400
 
 
-@pytest.mark.parametrize("D,fp64,wide,narrow", [(3, False, 3500, 2500), (1, False, 4000, 3000), (1, True, 2000, 1400)])
+@pytest.mark.parametrize("D,fp64,wide,narrow", [(3, False, 3500, 2500), (1, False, 4000, 3000), (1, True, 2000, 1400),
+                                                   (3, False, 9000, 6000), (1, False, 9000, 6000)])
 def test_cells_of_neighbouring_launches_overlap(D, fp64, wide, narrow):
     from paper_2007_12273_amd import api
 
