@@ -88,7 +88,7 @@ JUDGE_REL = 1e-4
 # sources are the ones the counters were taken on.
 EM_TRAFFIC = {"weibel_3v": {"sources_sha256": "e45a8856a88d8dc9f93d1378d75020d2f04f2fd6cf6572d37755dae09789b9b0",
                             "bytes": 211514027, "plan": "built-in launch plan"}}
-EM_SOURCES = ("gm_compress_impl.h", "gm_compress_d3_f32.hip", "gm_device.h", "gm_launch.h", "gm_api.hip")
+EM_SOURCES = ("gm_compress_impl.h", "gm_compress_d3_f32.hip", "gm_device.h", "gm_math.h", "gm_launch.h", "gm_api.hip")
 
 
 def em_sources_digest():

@@ -154,6 +154,8 @@ size_t gm_compress_workspace(int64_t n_cells, const gm_opts* o);
  * weights; component-wise sweeps (E-step, M-step, annihilation when
  * N_k <= T/2, renormalisation) with T = D(D+3)/2; stop on the relative
  * change of eq. (lnL-GM); then the unpenalised joint FP64 step.
+ * Host threads may call it at once, each with a stream, a workspace and an
+ * output record of its own.
  */
 int gm_compress(const double* v, const double* alpha, const int64_t* cell_off, int64_t n_cells,
                 const gm_opts* o, const int32_t* fixed_sweeps, const gm_init* init, const gm_mix* out,

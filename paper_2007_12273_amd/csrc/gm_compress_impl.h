@@ -296,7 +296,9 @@ constexpr int kPlanThreads = 1024;
 constexpr int kPlanKeys = 256;
 static_assert((kNumBuckets + 1) * kPlanLevels <= kPlanKeys, "keys of the plan");
 // Batches up to this size are planned by one workgroup in one launch instead
-// of four (7 us for 4096 cells; the small 1V call 0.725 -> 0.709 ms).
+// of four.  k_moments and the plan of 3V cells of about 45 particles, one launch
+// against four: 13 against 19 us for 256 cells, 26 against 26 for 4096, 42
+// against 32 for 8192, 270 against 145 for 65536.
 constexpr int kPlanOneGroup = 4096;
 
 // key of a cell, -1 if it is not fitted
@@ -1355,8 +1357,8 @@ void k_em(CompressArgs A_in)
         if (idx >= count) break;
         const int c = uni(sh.A.list[base + idx]);
         if constexpr (LEAN && !STORE_E) {
-            // the fewest particles per thread that hold the cell, down to
-            // half the variant's
+            // the fewest particles per thread that hold the cell, from five
+            // of the eight-particle variant and three of the four-particle one
             const int n = uni(static_cast<const CellInfo<D>*>(sh.A.cells)[c].n);
             const int need = (n + 64 * nwaves - 1) / (64 * nwaves);
             auto fit = [&](auto p) {
@@ -2266,8 +2268,9 @@ int64_t resident_spans(int waves)
     return r;
 }
 
-// Builds of k_em_span.  With eight slots an FP32 wave fits in 168 registers
-// (a few values of cells with seven and eight particles per thread spill), so three
+// Builds of k_em_span.  With eight slots an FP32 wave is held to 168 registers
+// (16 values spill in 1V, 69 in 3V, 248 B per lane; the build for two waves per
+// SIMD spills none), so three
 // waves share a SIMD: 65536 3V cells 23.1 ms against 27.1 ms with two, 1024 1V
 // cells of about 2000 24.5 against 27.1 ms.  In 3V a batch that two waves per
 // SIMD hold as a whole gains nothing from that, and the build for two spills

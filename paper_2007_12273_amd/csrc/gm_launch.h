@@ -12,9 +12,10 @@ namespace gm {
 // ---- compress ------------------------------------------------------------
 struct CompressArgs;
 
-// Length buckets: cell n -> first bucket with n <= max_n (64 * 2^b).  Each
-// bucket is run by one persistent launch of 64 * waves threads per
-// workgroup, each thread holding `per_thread` particles.  `store_e` buckets
+// Length buckets: cell n -> first bucket with n <= max_n.  In a plan that
+// launches per bucket, each is run by one persistent launch of 64 * waves
+// threads per workgroup, each thread holding `per_thread` particles (the
+// built-in plan's launches walk several, em_default below).  `store_e` buckets
 // keep every density term in registers, so the particles per thread depend
 // on the number of component slots (KMAX): the register file holds
 // (KMAX + D + 2) values per particle.
@@ -164,6 +165,13 @@ __host__ __device__ constexpr EmDefault em_default(int kt, bool fp64, int b)
     // what every wave computes alike); two up to 1024 particles in 3V, whose
     // four-particle build spills 196 B per lane (7.7-9.3 against 6.1-8.0 ms
     // for 512 cells of 256 on average).  Eight spill inside the update.
+    // With sixteen slots, 40 replayed sweeps of one cell and of 512 cells, one
+    // launch per bucket: 1V cells of 1000 1.07 and 1.5 ms with four particles per
+    // thread, 1.00 and 2.1 with two; 3V cells of 1000 2.2 and 4.1 with four, 1.2
+    // and 2.5 with two, of 500 1.6 and 2.5 against 0.8 and 1.4 (these launches,
+    // whose build also holds four, 1.6 and 3.5, 1.0 and 1.7).  Against eight
+    // particles per thread, 60 sweeps: 3V cells of 1000 7.2 -> 1.6 ms, of 2000 15.8
+    // -> 4.9 ms, 1V cells of 2000 15.4 -> 2.3 ms.
     if (fp64 && c.max_n <= 2048) {
         const int most = D == 3 && c.max_n <= 1024 ? 2 : 4;
         const int P = c.max_n <= 64 * most ? c.max_n / 64 : most;

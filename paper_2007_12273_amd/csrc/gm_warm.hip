@@ -288,8 +288,10 @@ static int gemm(const GemmArgs& a, hipStream_t st)
 // launches, 20-160 workgroups each, the loss on one thread per row) a step of
 // 1024 rows took 204 us of kernels; these two take 18 and 11 us, and an epoch
 // of four such steps 0.21 ms against 0.91 ms.  Every product accumulates in
-// the order it had there, with the same MFMA, and the sums likewise, so the
-// trained parameters are the same bit for bit.
+// the order it had there, with the same MFMA, and the bias gradients likewise, so
+// the trained parameters are the same bit for bit; a row's loss, which no
+// parameter depends on, is summed across the wave instead of in slot order and
+// differs by FP32 rounding.
 // ---------------------------------------------------------------------------
 constexpr int kTrainRows = 16;
 constexpr int kTrainThreads = 1024;
