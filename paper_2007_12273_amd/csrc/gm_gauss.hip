@@ -344,20 +344,21 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(const double* st, con
 // kSolveOwn cells, two per thread; a thread keeps its cells' mass-matrix rows
 // and vectors in registers and the workgroup the scaled vector it multiplies
 // in LDS, with one row (one cell) of halo on either side.  An iteration needs
-// two exchanges: after v = M dinv p the workgroups publish v and their part
-// of rh.v, after t = M dinv s they publish t and their parts of t.s, t.t,
-// rh.s, rh.t and s.s; omega, the new rho = rh.s - omega rh.t and the new |r|^2
-// = s.s - 2 omega t.s + omega^2 t.t follow from those.  These differences
-// cancel (rho lost up to four times what a dot product with r rounds off, |r|^2
-// three of its digits), so all five sums, and the differences, are carried in
-// two parts; they then hold more than the dot products would.  Every workgroup
+// two exchanges: after v = M dinv p the workgroups publish v and their parts
+// of rh.v and of the |r|^2 that the iteration before left, after t = M dinv s
+// they publish t and their parts of t.s, t.t, rh.s and rh.t; omega and the new
+// rho = rh.s - omega rh.t follow from those.  That difference cancels (in one
+// part it lost up to four times what a dot product with r rounds off), so its
+// two sums and the difference are carried in two parts; it then holds more than
+// the dot product would.  Every workgroup
 // updates p, r and s of its halo itself from the neighbours' v and t.  The
 // restarts from the true residual b - M dA, which alone decides convergence,
 // run inside as well.  Launched one kernel per step the solve was bound by
 // its eight launches and a host round trip per eight iterations: 23 us an
 // iteration.  Solve on the 65536-cell grid (64 workgroups, 27 iterations)
-// 0.26 ms against 0.74 ms and four host round trips, on 4096 cells in 1D (4
-// workgroups) 0.09 ms against 0.36 ms; what is left is the two exchanges.
+// 0.29 ms against 0.74 ms and four host round trips, on 4096 cells in 1D (4
+// workgroups) 0.10 ms against 0.36 ms; what is left is the two exchanges, 5 us
+// each (4.5 with the sums in one part).
 //
 // An exchange: each workgroup stores its halo-visible values and partial
 // sums, then, once they are out, a tag with the exchange's number; every
@@ -383,7 +384,7 @@ constexpr int kSolveThreads = 512;
 constexpr int kSolveOwn = 2 * kSolveThreads;   // cells a workgroup owns
 constexpr int kSolveHalo = kSolveThreads;      // cells of one halo row
 constexpr int kSolveMaxGroups = 128;
-constexpr int kSolvePart = 16;                 // doubles per workgroup and exchange: five sums at 0, their low parts at 8
+constexpr int kSolvePart = 8;                  // doubles per workgroup and exchange: two sums, two in two parts (2 3, 6 7)
 constexpr int kSolveMaxPolls = 1 << 20;        // bounds a wait whatever the clock says
 // A wait is some microseconds where the grid is resident.  The limit is about
 // the launch-per-step solve's time on the largest mesh taken here: giving up
@@ -424,21 +425,12 @@ __device__ __forceinline__ double agent_load(const double* p)
 __device__ __forceinline__ void agent_store(double* p, const Sum2& v)
 {
     agent_store(p, v.hi);
-    agent_store(p + 8, v.lo);
+    agent_store(p + 4, v.lo);
 }
 __device__ __forceinline__ void agent_load(const double* p, double& v) { v = agent_load(p); }
-__device__ __forceinline__ void agent_load(const double* p, Sum2& v) { v = Sum2{agent_load(p), agent_load(p + 8)}; }
+__device__ __forceinline__ void agent_load(const double* p, Sum2& v) { v = Sum2{agent_load(p), agent_load(p + 4)}; }
 __device__ __forceinline__ void add2(double& a, double b) { a += b; }
-__device__ __forceinline__ Sum2 sum2(double v) { return Sum2{v, 0.0}; }
-__device__ __forceinline__ Sum2 sum2(const Sum2& v) { return v; }
-template <typename T>
-__device__ __forceinline__ T as(const Sum2& v)
-{
-    if constexpr (std::is_same<T, double>::value)
-        return v.hi;
-    else
-        return v;
-}
+struct NoSums {};
 
 // Waits until this wave's stores have reached the point of coherence.  All
 // that the workgroups share goes through agent-scope atomics, which pass the
@@ -452,8 +444,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
     constexpr int NS = kSlots<DX>;
     constexpr int NC = 2;                       // own cells per thread, and halo cells per thread
     __shared__ double vec[kSolveOwn + 2 * kSolveHalo];
-    __shared__ Sum2 red[8][kSolveThreads / 64];
-    __shared__ Sum2 tot[5];
+    constexpr int NW = kSolveThreads / 64;
+    __shared__ double red[4][NW], tot[2];       // of the sums in one part
+    __shared__ Sum2 red2[4][NW], tot2[2];       // of those in two
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int G = gridDim.x, g = blockIdx.x;
     const int H = DX == 1 ? 1 : A.nx;           // cells of one halo row
@@ -521,34 +514,45 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
     unsigned long long epoch = 0;
     // publish val of the own cells, add up q over the grid (into tot), and
     // return the neighbours' val on the halo; false when a wait gave up
-    auto exchange = [&](const double (&val)[NC], const auto& q, double (&hval)[NC]) -> bool {
-        using T = std::remove_cv_t<std::remove_reference_t<decltype(q[0])>>;  // double or Sum2
-        constexpr int NQ = sizeof(q) / sizeof(T), NB = (NQ + 3) / 4;
+    auto exchange = [&](const double (&val)[NC], const double (&q)[2], const auto& q2, double (&hval)[NC]) -> bool {
+        constexpr bool TWO = !std::is_same<std::remove_cv_t<std::remove_reference_t<decltype(q2)>>, NoSums>::value;
         ++epoch;
         const int par = (int)(epoch & 1);
         double* halo = A.halo[par];
 #pragma unroll
         for (int k = 0; k < NC; ++k)
             if (gi[k] >= 0) agent_store(halo + gi[k], val[k]);
-        // sum u ends in register u / 4 of every lane of row tv_row(u)
-        T w[NB];
-        wave_sums_transposed<NQ>(q, w);
-        if ((lane & 15) == 15) {
-            const int row = lane >> 4, first = 2 * (row & 1) + (row >> 1);
-#pragma unroll
-            for (int j = 0; j < NB; ++j) red[4 * j + first][wid] = sum2(w[j]);
+        // sum u ends in every lane of row tv_row(u)
+        double w[1];
+        wave_sums_transposed<2>(q, w);
+        const int row = lane >> 4, sum = 2 * (row & 1) + (row >> 1);
+        if ((lane & 15) == 15) red[sum][wid] = w[0];
+        if constexpr (TWO) {
+            Sum2 w2[1];
+            wave_sums_transposed<2>(q2, w2);
+            if ((lane & 15) == 15) red2[sum][wid] = w2[0];
         }
         stores_done();  // this wave's part is out before the tag below
         __syncthreads();
         double* part = A.part + (size_t)par * G * kSolvePart;
         if (wid == 0) {
-            // sum lane / 8 over the waves
-            static_assert(kSolveThreads / 64 == 8, "eight lanes of a row hold a sum's waves");
-            T a = as<T>(red[lane >> 3][lane & 7]);
+            // sum u of the waves in the lanes 8 u .. 8 u + 7
+            static_assert(NW == 8, "eight lanes hold a sum's waves");
+            const int u = (lane >> 3) & 3;
+            double* mine = part + (size_t)g * kSolvePart + u;
+            const bool first = (lane & 7) == 0 && lane < 16;
+            double a = red[u][lane & 7];
             dpp_add<0xB1>(a);
             dpp_add<0x4E>(a);
             dpp_add<0x141>(a);
-            if ((lane & 7) == 0 && lane < 8 * NQ) agent_store(part + (size_t)g * kSolvePart + (lane >> 3), a);
+            if (first) agent_store(mine, a);
+            if constexpr (TWO) {
+                Sum2 a2 = red2[u][lane & 7];
+                dpp_add<0xB1>(a2);
+                dpp_add<0x4E>(a2);
+                dpp_add<0x141>(a2);
+                if (first) agent_store(mine + 2, a2);
+            }
             stores_done();
             if (lane == 0)
                 __hip_atomic_store(A.tag + (size_t)par * G + g, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -574,17 +578,24 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 __hip_atomic_store(A.tag + (size_t)tid * G + g, kSolveGone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return false;
         }
-        if (wid < NQ) {
-            // value wid over the workgroups: a lane adds its two, then the wave
-            T a[1] = {}, b[1];
-            const double* at = part + (size_t)lane * kSolvePart + wid;
+        // wave u adds sum u over the workgroups: a lane its two, then the wave
+        auto total = [&](auto zero, int u) {
+            decltype(zero) a[1] = {zero}, b[1];
+            const double* at = part + (size_t)lane * kSolvePart + u;
             if (lane < G) agent_load(at, a[0]);
             if (lane + 64 < G) {
                 agent_load(at + 64 * kSolvePart, b[0]);
                 add2(a[0], b[0]);
             }
             wave_sums_transposed<1>(a, b);
-            if (lane == 15) tot[wid] = sum2(b[0]);
+            return b[0];  // in lane 15
+        };
+        if (wid < 2) {
+            const double a = total(0.0, wid);
+            if (lane == 15) tot[wid] = a;
+        } else if (TWO && wid < 4) {
+            const Sum2 a = total(Sum2{0.0, 0.0}, wid);
+            if (lane == 15) tot2[wid - 2] = a;
         }
 #pragma unroll
         for (int k = 0; k < NC; ++k) hval[k] = hi[k] >= 0 ? agent_load(halo + hi[k]) : 0.0;
@@ -619,10 +630,10 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         qb[0] += b[k] * b[k];
         if (gi[k] >= 0 && A.off[gi[k] + 1] <= A.off[gi[k]]) qb[1] += 1.0;
     }
-    bool ok = exchange(x, qb, hx);
+    bool ok = exchange(x, qb, NoSums{}, hx);
     if (ok) {
-        b2 = true_r2 = tot[0].hi;
-        empty = tot[1].hi;
+        b2 = true_r2 = tot[0];
+        empty = tot[1];
     }
     const double tol2b2 = A.tol * A.tol * b2;
     if (empty != 0.0 || b2 == 0.0) done = 1;
@@ -630,7 +641,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         // the true residual of the current dA (zero at first), and r on the halo
         product(x, hx, a_);
         double rho = 0.0, alpha = 1.0, omega = 1.0, beta = 0.0;
-        double q[1] = {0.0};
+        double q[2] = {0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
             r[k] = rh[k] = b[k] - a_[k];
@@ -638,9 +649,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
             hp[k] = hv[k] = 0.0;
             q[0] += r[k] * r[k];
         }
-        ok = exchange(r, q, hr);
+        ok = exchange(r, q, NoSums{}, hr);
         if (!ok) break;
-        r2 = true_r2 = rho = tot[0].hi;
+        r2 = true_r2 = rho = tot[0];
         if (r2 <= tol2b2) {
             done = 1;
             break;
@@ -659,13 +670,18 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 ha_[k] = hdinv[k] * hp[k];
             }
             product(a_, ha_, v);
-            q[0] = 0.0;
+            q[0] = q[1] = 0.0;
 #pragma unroll
-            for (int k = 0; k < NC; ++k) q[0] += rh[k] * v[k];
-            ok = exchange(v, q, hv);
+            for (int k = 0; k < NC; ++k) {
+                q[0] += rh[k] * v[k];
+                q[1] += r[k] * r[k];
+            }
+            ok = exchange(v, q, NoSums{}, hv);
             if (!ok) break;
-            const double rv = tot[0].hi;
-            if (rv == 0.0 || !isfinite(rv)) break;  // breakdown: restart
+            // converged by the recurrence: checked against the true residual
+            if (tot[1] <= tol2b2) break;
+            const double rv = tot[0];
+            if (rv == 0.0 || !isfinite(rv) || !isfinite(tot[1])) break;  // breakdown: restart
             alpha = rho / rv;
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
@@ -675,20 +691,19 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 ha_[k] = hdinv[k] * hs[k];
             }
             product(a_, ha_, t);
-            Sum2 qt[5] = {};
+            q[0] = q[1] = 0.0;
+            Sum2 q2[2] = {};
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
-                mul_add2(qt[0], t[k], sv[k]);
-                mul_add2(qt[1], t[k], t[k]);
-                mul_add2(qt[2], rh[k], sv[k]);
-                mul_add2(qt[3], rh[k], t[k]);
-                mul_add2(qt[4], sv[k], sv[k]);
+                q[0] += t[k] * sv[k];
+                q[1] += t[k] * t[k];
+                mul_add2(q2[0], rh[k], sv[k]);
+                mul_add2(q2[1], rh[k], t[k]);
             }
             double ht[NC];
-            ok = exchange(t, qt, ht);
+            ok = exchange(t, q, q2, ht);
             if (!ok) break;
-            const Sum2 ts = tot[0], tt = tot[1];
-            omega = value2(tt) > 0.0 ? value2(ts) / value2(tt) : 0.0;
+            omega = tot[1] > 0.0 ? tot[0] / tot[1] : 0.0;
 #pragma unroll
             for (int k = 0; k < NC; ++k) {
                 x[k] += dinv[k] * (alpha * p[k] + omega * sv[k]);
@@ -696,12 +711,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
                 hr[k] = hs[k] - omega * ht[k];
             }
             ++iters;
-            r2 = value2(sub_scaled2(tot[4], omega, sub_scaled2(Sum2{2.0 * ts.hi, 2.0 * ts.lo}, omega, tt)));
-            const double rho1 = value2(sub_scaled2(tot[2], omega, tot[3]));
-            // converged by the recurrence (or below its rounding): checked
-            // against the true residual
-            if (r2 <= tol2b2) stop = true;
-            else if (omega == 0.0 || rho1 == 0.0 || !isfinite(r2) || !isfinite(rho1)) stop = true;
+            const double rho1 = value2(sub_scaled2(tot2[0], omega, tot2[1]));
+            if (omega == 0.0 || rho1 == 0.0 || !isfinite(rho1)) stop = true;
             else {
                 beta = (rho1 / rho) * (alpha / omega);
                 rho = rho1;
@@ -709,8 +720,8 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(SolveArgs A)
         }
         if (!ok) break;
         // dA on the halo for the next true residual
-        q[0] = 0.0;
-        ok = exchange(x, q, hx);
+        q[0] = q[1] = 0.0;
+        ok = exchange(x, q, NoSums{}, hx);
     }
 #pragma unroll
     for (int k = 0; k < NC; ++k)
@@ -854,7 +865,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
     };
     // The one-launch solve: rows that fit a workgroup with their halo, and a
     // mesh that a resident grid covers (131072 cells; at 65536, half of that,
-    // it takes a third of the other path's time, and at one workgroup a quarter).
+    // it takes two fifths of the other path's time, and at one workgroup a quarter).
     // Longer rows and larger meshes are launched step by step.
     const int per = DX == 1 ? kSolveOwn : (nx <= kSolveHalo ? kSolveOwn / nx : 0);
     const int64_t ngroups = per > 0 ? ((DX == 1 ? n : (int64_t)ny) + per - 1) / per : 0;
@@ -881,7 +892,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
         a.x = g.x;
         a.halo[0] = g.p;
         a.halo[1] = g.v;
-        a.part = g.s;  // 256 B per group: the vector holds 8 B per cell, at least 256 in all
+        a.part = g.s;  // 128 B per group: the vector holds 8 B per cell, at least 256 in all
         a.tag = (unsigned long long*)g.t;
         a.st = g.st;
         hipLaunchKernelGGL(k_solve<DX>, dim3(groups), dim3(kSolveThreads), 0, st, a);

@@ -84,7 +84,7 @@ def trace(path):
               % (i, len(c), (t1 - t0) * 1e-6, busy * 1e-6))
         if "Queue_Id" in c[0]:
             print("           " + "  ".join(
-                "%s +%.2f %.2f q%s" % (r["Kernel_Name"].split("gm::")[-1].split("(")[0].replace(" ", ""),
+                "%s +%.2f %.2f q%s" % (r["Kernel_Name"].split("(")[0].split("gm::")[-1].replace(" ", ""),
                                        (int(r["Start_Timestamp"]) - t0) * 1e-6,
                                        (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-6, r["Queue_Id"])
                 for r in sorted(c, key=lambda r: int(r["Start_Timestamp"]))))

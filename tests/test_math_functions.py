@@ -42,19 +42,14 @@ using std::fma;
 #define EACH(name) extern "C" void t_##name(const double* x, double* y, long n) { for (long i = 0; i < n; ++i) y[i] = gm::name(x[i]); }
 EACH(rcp64) EACH(rsq64) EACH(log2_64) EACH(log_64) EACH(sqrt_64)
 extern "C" void t_sincospi(const double* x, double* s, double* c, long n) { for (long i = 0; i < n; ++i) gm::sincospi_64(x[i], s[i], c[i]); }
-extern "C" void t_new_sums(const double* s, const double* t, const double* rh, double omega, long n, double* out)
+extern "C" double t_new_rho(const double* s, const double* t, const double* rh, double omega, long n)
 {
-    gm::Sum2 q[5] = {};
+    gm::Sum2 q[2] = {};
     for (long i = 0; i < n; ++i) {
-        gm::mul_add2(q[0], t[i], s[i]);
-        gm::mul_add2(q[1], t[i], t[i]);
-        gm::mul_add2(q[2], rh[i], s[i]);
-        gm::mul_add2(q[3], rh[i], t[i]);
-        gm::mul_add2(q[4], s[i], s[i]);
+        gm::mul_add2(q[0], rh[i], s[i]);
+        gm::mul_add2(q[1], rh[i], t[i]);
     }
-    const gm::Sum2 ts2 = {2.0 * q[0].hi, 2.0 * q[0].lo};
-    out[0] = gm::value2(gm::sub_scaled2(q[4], omega, gm::sub_scaled2(ts2, omega, q[1])));
-    out[1] = gm::value2(gm::sub_scaled2(q[2], omega, q[3]));
+    return gm::value2(gm::sub_scaled2(q[0], omega, q[1]));
 }
 """
 
@@ -125,21 +120,20 @@ def test_special_arguments(lib):
 
 
 def test_cancelling_sums_of_the_solve(lib):
-    """|r|^2 and rh.r of r = s - omega t from the sums of s, t and rh alone, t
-    so near s / omega that r is a thousandth of s: as near to the exact value
-    for the rounded r as the rounding of r allows, one unit of |r|^2 and of sum
-    |rh_i r_i| (the sums in one part lose a thousand times that and more)."""
+    """rh.r of r = s - omega t from rh.s and rh.t, t so near s / omega that r is a
+    thousandth of s: as near to the exact value for the rounded r as the rounding
+    of r allows, one unit of sum |rh_i r_i| (the sums in one part lose some fifty
+    times that)."""
     from fractions import Fraction as F
     rng = np.random.default_rng(5)
     n, omega = 2000, 0.7310585786300049
     s, rh = rng.standard_normal(n), rng.standard_normal(n)
     t = (s * (1 + 1e-3 * rng.standard_normal(n))) / omega
-    out = np.empty(2)
     p = lambda a: ctypes.c_void_p(a.ctypes.data)
-    lib.t_new_sums(p(s), p(t), p(rh), ctypes.c_double(omega), ctypes.c_long(n), p(out))
+    lib.t_new_rho.restype = ctypes.c_double
+    got = lib.t_new_rho(p(s), p(t), p(rh), ctypes.c_double(omega), ctypes.c_long(n))
     r = [float(F(a) - F(omega) * F(b)) for a, b in zip(s, t)]  # rounded once
-    r2, rho = sum(F(x) ** 2 for x in r), sum(F(x) * F(y) for x, y in zip(r, rh))
-    assert abs(F(out[0]) - r2) <= F(2.0 ** -52) * r2
-    assert abs(F(out[1]) - rho) <= F(2.0 ** -52) * sum(abs(F(x) * F(y)) for x, y in zip(r, rh))
-    one = [float(np.dot(s, s) - omega * (2 * np.dot(t, s) - omega * np.dot(t, t))), float(np.dot(rh, s) - omega * np.dot(rh, t))]
-    print("in one part: %.1e, %.1e" % (abs(F(one[0]) - r2) / r2, abs(F(one[1]) - rho) / rho))
+    rho, unit = sum(F(x) * F(y) for x, y in zip(r, rh)), F(2.0 ** -52) * sum(abs(F(x) * F(y)) for x, y in zip(r, rh))
+    assert abs(F(got) - rho) <= unit
+    one = float(np.dot(rh, s) - omega * np.dot(rh, t))
+    print("in one part: %.0f units" % (abs(F(one) - rho) / unit))

@@ -35,6 +35,7 @@ def _write(path, extra):
 def test_trace_of_both_forms(tmp_path, capsys):
     profsum.main(["trace", _write(tmp_path / "t.csv", {})])
     out = capsys.readouterr().out
+    assert "k_em<3,16,8,false,float,true>+0.001.00q3" in out.replace(" ", "")
     assert "call  0:  4 EM dispatches, span    4.000 ms" in out and "call  1:  2 EM dispatches, span    2.000 ms" in out
 
 
