@@ -356,9 +356,9 @@ __global__ __launch_bounds__(kVecThreads) void k_update_xr(const double* st, con
 // run inside as well.  Launched one kernel per step the solve was bound by
 // its eight launches and a host round trip per eight iterations: 23 us an
 // iteration.  Solve on the 65536-cell grid (64 workgroups, 27 iterations)
-// 0.29 ms against 0.74 ms and four host round trips, on 4096 cells in 1D (4
-// workgroups) 0.10 ms against 0.36 ms; what is left is the two exchanges, 5 us
-// each (4.5 with the sums in one part).
+// 0.27 ms against 0.74 ms and four host round trips, on 4096 cells in 1D (4
+// workgroups) 0.10 ms against 0.36 ms; what is left is the two exchanges, 4.6 us
+// each.
 //
 // An exchange: each workgroup stores its halo-visible values and partial
 // sums, then, once they are out, a tag with the exchange's number; every
@@ -865,7 +865,7 @@ int gauss_correct_impl(const double* x, double* w, const int64_t* off, int64_t n
     };
     // The one-launch solve: rows that fit a workgroup with their halo, and a
     // mesh that a resident grid covers (131072 cells; at 65536, half of that,
-    // it takes two fifths of the other path's time, and at one workgroup a quarter).
+    // it takes 0.36 of the other path's time, and at one workgroup a quarter).
     // Longer rows and larger meshes are launched step by step.
     const int per = DX == 1 ? kSolveOwn : (nx <= kSolveHalo ? kSolveOwn / nx : 0);
     const int64_t ngroups = per > 0 ? ((DX == 1 ? n : (int64_t)ny) + per - 1) / per : 0;
